@@ -82,8 +82,6 @@ __host__ __device__ inline WgradBalance wgrad_balance_geometry(int m_tiles, int 
   return WgradBalance{1, 1};
 }
 constexpr int kPlanJobsLds = 1024;      // work lists up to this length are balanced (longer ones keep load order)
-constexpr int kBalanceBins = 64;        // ... if the geometry has at most this many bins and jobs x bins <= kBalanceWork
-constexpr int kBalanceWork = 16384;     // (one thread deals the jobs out)
 
 struct WgradPlanShared {
   int cnt[FLEXMOE_MAX_VEXPERTS], own[FLEXMOE_MAX_VEXPERTS];
@@ -92,36 +90,61 @@ struct WgradPlanShared {
   int boff[FLEXMOE_MAX_EXPERTS + 1];
   int4 jobs[kPlanJobsLds];
   int njobs;
-  int bal_load[2][kBalanceBins], bal_count[2][kBalanceBins];
 };
-// One thread: deals the work list (in load order in LDS) out to dst as described above; dst holds -1 everywhere on
+// Smallest of a value over the wave, the same in every lane (DPP inside rows of 16 lanes, then the four rows' results).
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xf, 0xf, true));       // lane ^ 1
+  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xf, 0xf, true));       // lane ^ 2
+  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xf, 0xf, true));      // mirror inside 8 lanes
+  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xf, 0xf, true));      // mirror inside 16 lanes
+  const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
+  const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
+  return min(min(a, b), min(c, d));
+}
+
+// One wave: deals the work list (in load order in LDS) out to dst as described above; dst holds -1 everywhere on
 // entry.  Returns the positions in use.  A group's list may grow to twice the even share of positions, so that
 // 2 seg_rows_max positions always suffice.
-__device__ inline int balance_jobs(WgradPlanShared& sh, int which, WgradBalance geo, int seg_tiles, int positions,
+// The deal is a serial chain over the jobs (each goes to the bin that the earlier ones left least loaded), so it is the
+// length of one link that counts: lane q keeps bin q's load and count in registers and the least loaded bin comes from
+// a DPP minimum over (load, bin).  With one thread walking the bins in LDS the plan took 82 us of the Swin-like layer's
+// backward pass and 27 us of the GPT-medium-like one; like this the two layers' steps are 61 and 17 us shorter.
+__device__ inline int balance_jobs(const WgradPlanShared& sh, WgradBalance geo, int seg_tiles, int positions,
                                    int4* __restrict__ dst) {
+  const int lane = threadIdx.x & (kWave - 1);
   const int J = sh.njobs, nb = geo.groups * geo.per_slot;      // position p belongs to bin p % nb
   const int rounds_max = positions / nb;                       // what fits the list
-  if (geo.groups <= 1 || nb > kBalanceBins || J * nb > kBalanceWork || rounds_max * nb < J) {
-    for (int j = 0; j < J; ++j) dst[j] = sh.jobs[j];
+  if (geo.groups <= 1 || nb > kWave || rounds_max * nb < J) {
+    for (int j = lane; j < J; j += kWave) dst[j] = sh.jobs[j];
     return J;
   }
-  int* load = sh.bal_load[which];
-  int* count = sh.bal_count[which];
-  for (int c = 0; c < nb; ++c) load[c] = count[c] = 0;
+  uint32_t load = 0;      // of bin `lane`: below 2^26 (at most 2^25 K tiles of 32 assignments, a few more per job)
+  int count = 0;
   // jobs per bin at most: twice the even share (once, twice and three times measured the same to 0.5 %)
   const int limit = min(2 * ((J + nb - 1) / nb), rounds_max);
   int rounds = 0;
-  for (int j = 0; j < J; ++j) {
-    int c = -1;
-    for (int q = 0; q < nb; ++q)
-      if (count[q] < limit && (c < 0 || load[q] < load[c])) c = q;
-    const int4 job = sh.jobs[j];
-    const int Te = sh.tiles[job.x];
-    const int len = job.z > 1 ? min(seg_tiles, Te - job.y * seg_tiles) : Te;
-    load[c] += max(4, (len + 3) & ~3) + 6;               // K tiles of the job + its fixed cost per output tile
-    dst[count[c] * nb + c] = job;
-    count[c] += 1;
-    rounds = max(rounds, count[c]);
+  for (int j0 = 0; j0 < J; j0 += kWave) {
+    int4 job = make_int4(-1, 0, 0, 0);
+    int cost = 0;
+    if (j0 + lane < J) {
+      job = sh.jobs[j0 + lane];
+      const int Te = sh.tiles[job.x];
+      const int len = job.z > 1 ? min(seg_tiles, Te - job.y * seg_tiles) : Te;
+      cost = max(4, (len + 3) & ~3) + 6;                 // K tiles of the job + its fixed cost per output tile
+    }
+    const int n = min(J - j0, kWave);
+    for (int j = 0; j < n; ++j) {
+      const uint32_t least = wave_min_u32(lane < nb && count < limit ? (load << 6) | (uint32_t)lane : ~0u);
+      const int c = (int)(least & 63u);
+      const int at = __builtin_amdgcn_readlane(count, c);
+      const int w = __builtin_amdgcn_readlane(cost, j);
+      if (lane == c) {
+        load += (uint32_t)w;
+        count += 1;
+      }
+      if (lane == j) dst[at * nb + c] = job;
+      rounds = max(rounds, at + 1);
+    }
   }
   return rounds * nb;
 }
@@ -220,7 +243,7 @@ __device__ __forceinline__ void wgrad_plan_block(const int32_t* __restrict__ vof
     }
     for (int e = lane; e < E; e += kWave) plan.etiles[e] = sh.tiles[e];
   }
-  // the two products' lists, dealt out so that their XCD groups get equal work (one thread of waves 1 and 2 each;
+  // the two products' lists, dealt out so that their XCD groups get equal work (waves 1 and 2;
   // the bucket lists below are written meanwhile)
   if (seg_rows_max <= kPlanJobsLds) {
     for (int w = threadIdx.x; w < 2 * seg_rows_max; w += kGemmThreads) {
@@ -229,8 +252,9 @@ __device__ __forceinline__ void wgrad_plan_block(const int32_t* __restrict__ vof
     }
     __threadfence_block();
     __syncthreads();
-    if (threadIdx.x == kWave) plan.njobs[0] = balance_jobs(sh, 0, geo0, seg_tiles, 2 * seg_rows_max, plan.jobs);
-    if (threadIdx.x == 2 * kWave) plan.njobs[1] = balance_jobs(sh, 1, geo1, seg_tiles, 2 * seg_rows_max, plan.jobs_other);
+    const int wave = threadIdx.x / kWave;
+    if (wave == 1) plan.njobs[0] = balance_jobs(sh, geo0, seg_tiles, 2 * seg_rows_max, plan.jobs);
+    if (wave == 2) plan.njobs[1] = balance_jobs(sh, geo1, seg_tiles, 2 * seg_rows_max, plan.jobs_other);
   } else {
     __syncthreads();
     for (int w = sh.njobs + threadIdx.x; w < 2 * seg_rows_max; w += kGemmThreads) {
