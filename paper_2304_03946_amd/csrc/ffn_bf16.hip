@@ -54,6 +54,7 @@
 #include "ffn_bf16_tile.h"
 #include "ffn_bf16_dma.h"
 #include "ffn_bf16_persist.h"
+#include "ffn_bf16_small.h"
 #include "ffn_bf16_wgrad.h"
 
 namespace flexmoe {
@@ -100,6 +101,27 @@ static size_t wgrad_tail_bytes(int A, int d, int f, int V) {
   return align_up((size_t)wgrad_partial_slots(A, V, seg_tiles) * d * f * sizeof(float), 256);
 }
 
+// Which rows kernels a call of these sizes takes: 32 or 64 = rows_gemm_small_bf16 with row tiles of that many rows,
+// 0 = the 256 x 256 kernels.  By the mean rows per expert, since the loads are not known here (skewed: a few experts have
+// ten times the mean, most have less).  Measured, both products of a forward pass in us:
+//   1 row per expert  (16 tokens, d 1024, f 4096, E 32, k 2):     32-row tiles 59, 64-row 69, 256-row 162
+//   8 rows            (256 tokens, d 2048, f 8192, E 64, k 2):    610, 562, 1135
+//   62 rows           (2000 tokens, the same layer):              1381, 1078, 1412
+//   94 rows           (1500 tokens, d 1024, f 4096, E 32, k 2):   226, 179, 208
+//   128 rows          (4096 tokens, d 512, f 1024, E 128, k 4):   149, 115, 143
+constexpr int kSmall32Rows = 4, kSmall64Rows = 160;
+static int small_rows(int A, int d, int f, int E) {
+  if ((long long)A * std::max(d, f) >= 1ll << 30) return 0;      // 32-bit byte offsets of the row loads
+  if (A <= kSmall32Rows * E) return 32;
+  return A <= kSmall64Rows * E ? 64 : 0;
+}
+static size_t small_ws_bytes(int A, int d, int f, int E) {
+  const int bm = small_rows(A, d, f, E);
+  if (!bm) return 0;
+  return align_up((size_t)(A / bm + E + 1) * sizeof(i32x4), 256) + align_up((size_t)A * sizeof(int32_t), 256) +
+         align_up(kSmallSlots * sizeof(int), 256) + (size_t)kSmallSlots * bm * SN * sizeof(float);
+}
+
 size_t ffn_ws_bytes(int A, int d, int f, int E, int V, int dtype) {
   const size_t s = dtype == FLEXMOE_BF16 ? 2 : 4;
   size_t need = align_up((size_t)A * f * s, 256) * 2;      // dHpre (or H in forward) + H
@@ -108,6 +130,7 @@ size_t ffn_ws_bytes(int A, int d, int f, int E, int V, int dtype) {
     need += rows_split_bytes(A, V, f, d);          // GEMM2 / dXp: partial tiles of the split last round
     need += align_up(wgrad_plan_bytes(wgrad_seg_rows_max(A, d, f, E, V), E, V), 256);   // work list of the weight gradients
     need += align_up(rows_tab_bytes(max_row_tiles(A, V)), 256);                         // row tiles of the bucket list
+    need += small_ws_bytes(A, d, f, E);            // plan and partial tiles of the small rows kernels
   }
   return need;
 }
@@ -116,11 +139,54 @@ static i32x4* rows_tab_ws(const FfnArgs& a, void* ws) {
                   rows_split_bytes(a.A, a.V, a.f, a.d) +
                   align_up(wgrad_plan_bytes(wgrad_seg_rows_max(a.A, a.d, a.f, a.E, a.V), a.E, a.V), 256));
 }
-// The row-tile table the persistent rows kernels of one call read.
-static void launch_rows_plan(const FfnArgs& a, void* ws, hipStream_t s) {
-  const int blocks = std::max(1, std::min(64, (max_row_tiles(a.A, a.V) + kGemmThreads - 1) / kGemmThreads));
-  hipLaunchKernelGGL(rows_plan_kernel, dim3(blocks), dim3(kGemmThreads), 0, s, a.voff, a.owner, a.V, rows_tab_ws(a, ws));
+// The small rows kernels' share of the workspace, behind the row-tile table.
+static SmallPlan small_plan_ws(const FfnArgs& a, void* ws, float** partial = nullptr) {
+  SmallPlan pl;
+  pl.A = a.A;
+  pl.bm = small_rows(a.A, a.d, a.f, a.E);
+  char* at = (char*)rows_tab_ws(a, ws) + align_up(rows_tab_bytes(max_row_tiles(a.A, a.V)), 256);
+  pl.tab = (i32x4*)at;
+  if (pl.bm) at += align_up((size_t)(a.A / pl.bm + a.E + 1) * sizeof(i32x4), 256);
+  pl.rowmap = (int32_t*)at;
+  at += align_up((size_t)a.A * sizeof(int32_t), 256);
+  pl.counters = (int*)at;
+  at += align_up(kSmallSlots * sizeof(int), 256);
+  if (partial) *partial = (float*)at;
+  return pl;
 }
+static int plan_blocks(const FfnArgs& a) {
+  if (small_rows(a.A, a.d, a.f, a.E)) return 1 + (a.V + 3) / 4;      // the first: row tiles; the others: a wave per bucket
+  return std::max(1, std::min(64, (max_row_tiles(a.A, a.V) + kGemmThreads - 1) / kGemmThreads));
+}
+// What the rows kernels of one forward call look up: the row-tile table of the persistent kernels, or the small kernels'
+// row list.
+static void launch_rows_plan(const FfnArgs& a, void* ws, hipStream_t s) {
+  const SmallPlan small = small_plan_ws(a, ws);
+  if (small.bm) hipLaunchKernelGGL(small_plan_kernel, dim3(plan_blocks(a)), dim3(kGemmThreads), 0, s, a.voff, a.owner, a.E, a.V, small);
+  else hipLaunchKernelGGL(rows_plan_kernel, dim3(plan_blocks(a)), dim3(kGemmThreads), 0, s, a.voff, a.owner, a.V, rows_tab_ws(a, ws));
+}
+
+template <int BM, bool WT, int EPI>
+static void launch_small_t(const SmallArgs& p, unsigned grid, hipStream_t s) {
+  hipLaunchKernelGGL((rows_gemm_small_bf16<BM, WT, EPI>), dim3(grid), dim3(kSmallThreads), 0, s, p);
+}
+template <bool WT, int EPI>
+static hipError_t launch_small(const FfnArgs& a, const void* in, const void* w, const void* bias, int K, int NC,
+                               const void* hpre_in, void* out0, void* out1, void* ws, hipStream_t s, const int32_t* gsrc,
+                               int gk, const int32_t* scatter_rows) {
+  float* partial;
+  const SmallPlan pl = small_plan_ws(a, ws, &partial);
+  const int lut = EPI == EPI_PLAIN || a.act == FLEXMOE_RELU ? -1 : a.act == FLEXMOE_GELU_ERF ? 0 : 1;
+  const SmallArgs p{(const bf16_t*)in, (const bf16_t*)w, (const bf16_t*)bias, pl.tab, pl.rowmap, K, NC, (NC + SN - 1) / SN,
+                    (const bf16_t*)hpre_in, (bf16_t*)out0, (bf16_t*)out1, gsrc, gk, scatter_rows, lut, partial, pl.counters};
+  // two workgroups per compute unit walk the tiles
+  const long long most = (long long)(a.A / pl.bm + a.E) * p.col_tiles;
+  const unsigned grid = (unsigned)std::min<long long>(kSmallSplitTarget, std::max<long long>(most * kSmallSplitMax, 1));
+  if (pl.bm == 32) launch_small_t<32, WT, EPI>(p, grid, s);
+  else launch_small_t<64, WT, EPI>(p, grid, s);
+  return hipGetLastError();
+}
+
 static void* wgrad_plan_ws(const FfnArgs& a, void* ws) {
   return (char*)ws + 2 * align_up((size_t)a.A * a.f * sizeof(bf16_t), 256) + 2 * wgrad_tail_bytes(a.A, a.d, a.f, a.V) +
          rows_split_bytes(a.A, a.V, a.f, a.d);
@@ -177,6 +243,7 @@ static hipError_t launch_rows(const FfnArgs& a, const void* in, const void* w, c
                               const void* hpre_in, void* out0, void* out1, void* ws, hipStream_t s,
                               const int32_t* gsrc = nullptr, int gk = 1, void* split_ws = nullptr,
                               const int32_t* scatter_rows = nullptr) {
+  if (small_rows(a.A, a.d, a.f, a.E)) return launch_small<WT, EPI>(a, in, w, bias, K, NC, hpre_in, out0, out1, ws, s, gsrc, gk, scatter_rows);
   const i32x4* tab = rows_tab_ws(a, ws);
   if (EPI == EPI_PLAIN)
     return launch_rows_t<WT, EPI, FLEXMOE_RELU>(a, in, w, bias, K, NC, hpre_in, out0, out1, s, gsrc, gk, split_ws,
@@ -210,7 +277,7 @@ static WgradDmaArgs wgrad_dma_args(const FfnArgs& a, const void* L, const void* 
 // of its rows products: one small launch.
 static void launch_bwd_plan(const FfnArgs& a, void* ws, hipStream_t s) {
   const int seg_rows_max = wgrad_seg_rows_max(a.A, a.d, a.f, a.E, a.V);
-  const int row_blocks = a.A > 0 ? std::max(1, std::min(64, (max_row_tiles(a.A, a.V) + kGemmThreads - 1) / kGemmThreads)) : 0;
+  const int row_blocks = a.A > 0 ? plan_blocks(a) : 0;
   const int f_tiles = (a.f + BM - 1) / BM, d_tiles = (a.d + BM - 1) / BM;
   const bool whole = a.f % BM == 0 && a.d % BN == 0;
   hipLaunchKernelGGL(ffn_bwd_plan_kernel, dim3(1 + row_blocks), dim3(kGemmThreads), 0, s, a.voff, a.owner, a.E, a.V,
@@ -218,7 +285,7 @@ static void launch_bwd_plan(const FfnArgs& a, void* ws, hipStream_t s) {
                      wgrad_plan_at(wgrad_plan_ws(a, ws), seg_rows_max, a.E, a.V, 0),
                      // (only the persistent kernels skip the holes that balancing leaves in a list)
                      whole ? wgrad_balance_geometry(f_tiles, d_tiles) : WgradBalance{1, 1},
-                     whole ? wgrad_balance_geometry(d_tiles, f_tiles) : WgradBalance{1, 1}, rows_tab_ws(a, ws));
+                     whole ? wgrad_balance_geometry(d_tiles, f_tiles) : WgradBalance{1, 1}, rows_tab_ws(a, ws), small_plan_ws(a, ws));
 }
 
 static void launch_wgrad_reduce(const FfnArgs& a, const WgradDmaArgs& g, hipStream_t s) {

@@ -53,7 +53,7 @@ struct SmallArgs {
   const int32_t* gsrc;           // gathered rows of `in`: row gsrc[bucket row] / gk; or null
   int gk;
   const int32_t* scatter_rows;   // bucket row p is stored as row scatter_rows[p] of out0; or null
-  const ActLutEntry* lut;        // activation table, null: ReLU
+  int lut;                       // which of g_act_lut's tables, -1: ReLU
   float* partial;                // kSmallSlots partial tiles
   int* counters;                 // one per tile that is cut into segments, zeroed by the plan
 };
@@ -66,7 +66,8 @@ __host__ __device__ inline int small_segments(int tiles, int k_tiles) {
 }
 
 // ---- plan: expert-major row list and row tiles ----------------------------------------------
-// Every workgroup derives the prefixes again and writes its share of the rows and tiles.
+// Every workgroup derives the prefixes; the first writes the row tiles, the others the row list, bucket by bucket (an
+// expert's buckets in ascending vExpert id).
 struct SmallPlan {
   i32x4* tab;
   int32_t* rowmap;
@@ -75,23 +76,32 @@ struct SmallPlan {
 };
 __device__ __forceinline__ void small_plan_block(const int32_t* __restrict__ voff, const int32_t* __restrict__ owner, int E, int V,
                                                  const SmallPlan& plan, int block, int nblocks) {
-  const int A = plan.A, bm = plan.bm;
-  i32x4* __restrict__ tab = plan.tab;
-  int32_t* __restrict__ rowmap = plan.rowmap;
-  int* __restrict__ counters = plan.counters;
-  __shared__ int off[FLEXMOE_MAX_VEXPERTS + 1], own[FLEXMOE_MAX_VEXPERTS], pos0[FLEXMOE_MAX_VEXPERTS];
-  __shared__ int rows_e[FLEXMOE_MAX_EXPERTS + 1], tile0[FLEXMOE_MAX_EXPERTS + 1];
-  __shared__ int wsum[2][kGemmThreads / kWave];
+  const int bm = plan.bm;
+  __shared__ int rows_e[FLEXMOE_MAX_EXPERTS], start_e[FLEXMOE_MAX_EXPERTS], wsum[2][kGemmThreads / kWave];
+  __shared__ int2 bucket[FLEXMOE_MAX_VEXPERTS];          // {expert, rows}
+  __shared__ int pos0[FLEXMOE_MAX_VEXPERTS], off[FLEXMOE_MAX_VEXPERTS];
+  static_assert(kGemmThreads == FLEXMOE_MAX_EXPERTS && 2 * kGemmThreads == FLEXMOE_MAX_VEXPERTS, "a thread per expert, two buckets per thread");
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-  for (int v = t; v <= V; v += kGemmThreads) {
-    off[v] = voff[v];
-    if (v < V) own[v] = owner[v];
+  int own[2], cnt[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int v = t + h * kGemmThreads;
+    own[h] = -1;
+    cnt[h] = 0;
+    if (v < V) {
+      own[h] = owner[v];
+      off[v] = voff[v];
+      cnt[h] = voff[v + 1] - off[v];
+    }
+    bucket[v] = make_int2(own[h], cnt[h]);
   }
   rows_e[t] = 0;
   __syncthreads();
-  for (int v = t; v < V; v += kGemmThreads) atomicAdd(&rows_e[own[v]], off[v + 1] - off[v]);      // integer sums: order does not matter
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    if (own[h] >= 0) atomicAdd(&rows_e[own[h]], cnt[h]);      // integer sums: order does not matter
   __syncthreads();
-  // exclusive prefixes over the experts (one per thread): rows, row tiles
+  // exclusive prefixes over the experts: rows, row tiles
   const int r = t < E ? rows_e[t] : 0, n = (r + bm - 1) / bm;
   int ir = r, in = n;
 #pragma unroll
@@ -107,47 +117,38 @@ __device__ __forceinline__ void small_plan_block(const int32_t* __restrict__ vof
     wsum[1][wave] = in;
   }
   __syncthreads();
-  int br = 0, bn = 0;
+  int row0 = ir - r, tile0 = in - n;
   for (int w = 0; w < wave; ++w) {
-    br += wsum[0][w];
-    bn += wsum[1][w];
+    row0 += wsum[0][w];
+    tile0 += wsum[1][w];
   }
-  rows_e[t] = br + ir - r;                               // now: the expert's first position
-  tile0[t] = bn + in - n;
-  if (t == kGemmThreads - 1) {
-    rows_e[kGemmThreads] = br + ir;
-    tile0[kGemmThreads] = bn + in;
+  if (block == 0) {
+    for (int i = 0; i < n; ++i) plan.tab[1 + tile0 + i] = i32x4{row0 + i * bm, min(bm, r - i * bm), t, 0};
+    if (t == kGemmThreads - 1) plan.tab[0] = i32x4{tile0 + n, 0, 0, 0};
+    for (int i = t; i < kSmallSlots; i += kGemmThreads) plan.counters[i] = 0;
+    return;
+  }
+  start_e[t] = row0;
+  __syncthreads();
+  {
+    int before[2] = {0, 0};      // rows of the same expert in earlier buckets
+#pragma unroll 8
+    for (int u = 0; u < V; ++u) {
+      const int2 b = bucket[u];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (b.x == own[h] && u < t + h * kGemmThreads) before[h] += b.y;
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (own[h] >= 0) pos0[t + h * kGemmThreads] = start_e[own[h]] + before[h];
   }
   __syncthreads();
-  const int tiles = tile0[kGemmThreads];
-  for (int v = t; v < V; v += kGemmThreads) {
-    int p = rows_e[own[v]];
-    for (int u = 0; u < v; ++u) p += own[u] == own[v] ? off[u + 1] - off[u] : 0;
-    pos0[v] = p;
+  constexpr int kWaves = kGemmThreads / kWave;           // a wave per bucket
+  for (int v = (block - 1) * kWaves + wave; v < V; v += (nblocks - 1) * kWaves) {
+    const int lo = off[v], len = bucket[v].y, to = pos0[v];
+    for (int i = lane; i < len; i += kWave) plan.rowmap[to + i] = lo + i;
   }
-  __syncthreads();
-  const int g = block * kGemmThreads + t, stride = nblocks * kGemmThreads;
-  for (int p = g; p < A; p += stride) {
-    int lo = 0, hi = V;                                  // last v with off[v] <= p
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (off[mid] <= p) lo = mid;
-      else hi = mid;
-    }
-    rowmap[pos0[lo] + p - off[lo]] = p;
-  }
-  for (int i = g; i < tiles; i += stride) {
-    int lo = 0, hi = kGemmThreads;                       // last expert with tile0[e] <= i
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (tile0[mid] <= i) lo = mid;
-      else hi = mid;
-    }
-    const int first = rows_e[lo] + (i - tile0[lo]) * bm;
-    tab[1 + i] = i32x4{first, min(bm, rows_e[lo + 1] - first), lo, 0};
-  }
-  for (int i = g; i < kSmallSlots; i += stride) counters[i] = 0;
-  if (g == 0) tab[0] = i32x4{tiles, 0, 0, 0};
 }
 __global__ __launch_bounds__(kGemmThreads) void small_plan_kernel(const int32_t* __restrict__ voff,
                                                                   const int32_t* __restrict__ owner, int E, int V, SmallPlan plan) {
@@ -354,13 +355,13 @@ __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const S
       __syncthreads();                                   // the flag has been read
     }
 
-    const bool use_lut = EPI != EPI_PLAIN && p.lut != nullptr;
+    const bool use_lut = EPI != EPI_PLAIN && p.lut >= 0;
     if (use_lut) {
       // the stages are free: the activation table (28 KB, from L2) goes there
 #pragma unroll
       for (int q = 0; q < kLutBytes / 1024 / kSmallWaves; ++q) {
         const int i = wave * (kLutBytes / 1024 / kSmallWaves) + q;
-        small_load_at((const bf16_t*)((const char*)p.lut + i * 1024 + lane * 16), lds0 + i * 1024);
+        small_load_at((const bf16_t*)((const char*)g_act_lut[p.lut] + i * 1024 + lane * 16), lds0 + i * 1024);
       }
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();

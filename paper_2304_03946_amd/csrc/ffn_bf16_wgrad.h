@@ -4,6 +4,7 @@
 #include "common.h"
 #include "ffn_bf16_dma.h"
 #include "ffn_bf16_persist.h"
+#include "ffn_bf16_small.h"
 namespace flexmoe {
 // Work list of the weight-gradient kernels.  Experts are taken by descending load (ties by
 // ascending id: the long contractions start first).  An expert's contraction runs over its
@@ -284,13 +285,15 @@ __device__ __forceinline__ void wgrad_plan_block(const int32_t* __restrict__ vof
 }
 
 // Everything the kernels of a backward call look up, in one launch: workgroup 0 writes the work list of the
-// weight gradients, the others (if any) the row-tile table of the rows products (see rows_plan_block).
+// weight gradients, the others (if any) what the rows products read: the expert-major row list (small.bm > 0, see
+// small_plan_block) or the row-tile table (see rows_plan_block).
 __global__ __launch_bounds__(kGemmThreads) void ffn_bwd_plan_kernel(const int32_t* __restrict__ voff,
                                                                     const int32_t* __restrict__ owner, int E, int V,
                                                                     int seg_tiles, int seg_rows_max, WgradPlan plan,
                                                                     WgradBalance geo0, WgradBalance geo1,
-                                                                    i32x4* __restrict__ row_tab) {
+                                                                    i32x4* __restrict__ row_tab, SmallPlan small) {
   if (blockIdx.x == 0) wgrad_plan_block(voff, owner, E, V, seg_tiles, seg_rows_max, plan, geo0, geo1);
+  else if (small.bm) small_plan_block(voff, owner, E, V, small, blockIdx.x - 1, gridDim.x - 1);
   else rows_plan_block(voff, owner, V, row_tab, blockIdx.x - 1, gridDim.x - 1);
 }
 

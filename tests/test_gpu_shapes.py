@@ -1,9 +1,11 @@
 """GPU parity at the sizes where the kernels' dispatch changes or their tiles end: stage by stage against the oracle,
 with the tolerances of test_gpu_parity (bf16 2e-2, fp32 1e-5 of the reference's maximum, also per expert and bucket)."""
+import numpy as np
 import pytest
+import torch
 
 from paper_2304_03946_amd import workloads as W
-from test_gpu_parity import api, run_stagewise  # noqa: F401  (api: module fixture)
+from test_gpu_parity import api, run_stagewise, upload  # noqa: F401  (api: module fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -18,3 +20,34 @@ def stagewise(api, cfg, seed=3):  # noqa: F811
 @pytest.mark.parametrize("N,d,f,E,V", [(2100, 256, 1024, 12, 17), (1300, 256, 2048, 6, 9), (4200, 512, 1024, 5, 8), (3000, 256, 512, 70, 80)])
 def test_weight_gradient_work_lists(api, N, d, f, E, V):  # noqa: F811
     stagewise(api, W.scaled(W.CONFIGS["gpt_m"], N=N, d=d, f=f, E=E, V=V, max_rep=3))
+
+
+# rows kernels for few rows per expert: 32-row tiles (at most 4 rows per expert on average; N = 1: two experts with a
+# single row, the contraction cut into its most segments), 64-row tiles up to 160 rows, and the first size past either
+# line; K with a partial last tile (d, f multiples of 8 only), K below one tile, ragged column tiles, 512 buckets
+@pytest.mark.parametrize("N,d,f,E,k,V,act", [
+    (1, 1024, 4096, 32, 2, 48, W.ACT_GELU_ERF), (31, 264, 520, 16, 2, 21, W.ACT_GELU_TANH), (33, 264, 520, 16, 2, 21, W.ACT_RELU),
+    (7, 48, 8, 4, 1, 6, W.ACT_GELU_ERF), (640, 136, 392, 8, 2, 12, W.ACT_GELU_ERF), (641, 136, 392, 8, 2, 12, W.ACT_GELU_ERF),
+    (130, 512, 2048, 8, 2, 9, W.ACT_RELU), (900, 128, 256, 256, 4, 512, W.ACT_GELU_ERF)])
+def test_rows_products_with_few_rows_per_expert(api, N, d, f, E, k, V, act):  # noqa: F811
+    stagewise(api, W.scaled(W.CONFIGS["gpt_m"], N=N, d=d, f=f, E=E, k=k, V=V, act=act, max_rep=3))
+
+
+@pytest.mark.parametrize("N,d,f,E,V,k", [(3, 256, 1024, 16, 20, 1), (100, 384, 640, 8, 13, 1), (300, 128, 1024, 64, 96, 2)])
+def test_forward_variants_with_few_rows_per_expert(api, N, d, f, E, V, k):  # noqa: F811
+    """Gathered loads, the scattered store of the top-1 call and the replayed contraction segments: the staged forward's bits."""
+    binding, layer_mod = api
+    cfg = W.scaled(W.CONFIGS["gpt_m"], N=N, d=d, f=f, E=E, V=V, k=k, backward=False, max_rep=3)
+    inp = W.make_layer_inputs(cfg)
+    dev = upload(layer_mod, inp)
+    rng = np.random.default_rng(4)
+    b1, b2 = (layer_mod.to_device(W.Bf16Tensor.from_f32((rng.standard_normal((E, n)) * 0.3).astype(np.float32))) for n in (f, d))
+    rep = W.placement_from_loads(W.prior_loads(cfg), cfg.V, cfg.max_rep, shuffle_seed=11)
+    L = layer_mod.MoELayer.for_config(cfg)
+    L.forward(dev["x"], dev["wg"], dev["w1"], dev["w2"], *rep, b1, b2)
+    want = L.y.clone()
+    for fwd in [L.forward, L.forward_fused] + ([L.forward_top1] if k == 1 else []):
+        for _ in range(3):      # the segment counters are left as they were found
+            L.y.zero_()
+            fwd(dev["x"], dev["wg"], dev["w1"], dev["w2"], *rep, b1, b2, keep_hpre=False)
+            assert torch.equal(L.y, want)
