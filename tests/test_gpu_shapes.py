@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2304_03946_amd import workloads as W
-from test_gpu_parity import api, run_stagewise, upload  # noqa: F401  (api: module fixture)
+from test_gpu_parity import api, check_gate, run_stagewise, upload  # noqa: F401  (api: module fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +51,26 @@ def test_forward_variants_with_few_rows_per_expert(api, N, d, f, E, V, k):  # no
             L.y.zero_()
             fwd(dev["x"], dev["wg"], dev["w1"], dev["w2"], *rep, b1, b2, keep_hpre=False)
             assert torch.equal(L.y, want)
+
+
+# fp32: tiles of 64 x 64 outputs and 32-wide K tiles (below one tile, whole tiles, ragged in every dimension), experts
+# without tokens, one token, more buckets than a wave has lanes, a contraction over many buckets of one expert
+@pytest.mark.parametrize("N,d,f,E,k,V,act", [
+    (1, 8, 8, 2, 1, 2, W.ACT_RELU), (65, 64, 96, 3, 1, 5, W.ACT_GELU_ERF), (300, 40, 136, 5, 2, 9, W.ACT_GELU_TANH),
+    (513, 128, 256, 4, 4, 6, W.ACT_GELU_ERF), (400, 72, 64, 100, 3, 180, W.ACT_GELU_ERF), (128, 256, 512, 1, 1, 3, W.ACT_RELU)])
+def test_fp32_layer(api, N, d, f, E, k, V, act):  # noqa: F811
+    stagewise(api, W.scaled(W.CONFIGS["tiny"], N=N, d=d, f=f, E=E, k=k, V=V, act=act, max_rep=3, backward=True))
+
+
+# groups of 1 .. 64 lanes per token and four experts per lane; features below, at and past the pieces held in LDS
+@pytest.mark.parametrize("N,d,E,k", [(1, 8, 1, 1), (17, 128, 2, 2), (50, 136, 6, 3), (330, 136, 64, 8), (210, 40, 65, 2), (700, 72, 256, 4), (95, 264, 33, 3)])
+def test_fp32_gate(api, N, d, E, k):  # noqa: F811
+    binding, layer_mod = api
+    rng = np.random.default_rng(N + E)
+    x = rng.standard_normal((N, d)).astype(np.float32)
+    wg = (rng.standard_normal((d, E)) / np.sqrt(d)).astype(np.float32)
+    idx = torch.full((N, k), -1, dtype=torch.int32, device="cuda")
+    w = torch.zeros((N, k), dtype=torch.float32, device="cuda")
+    ws = torch.empty(1 << 16, dtype=torch.uint8, device="cuda")
+    binding.flexmoe_gate_topk(layer_mod.to_device(x), layer_mod.to_device(wg), k, idx, w, ws)
+    check_gate(idx.cpu().numpy(), w.cpu().numpy(), x, wg, k, W.DT_F32)
