@@ -11,7 +11,7 @@
 // W_g^T travel global -> LDS with direct loads that fetch whole 128-byte lines of a row (eight
 // rows per instruction), several 64-wide K tiles in flight per workgroup, and the MFMA fragments
 // are read from LDS.  Otherwise (gate_bf16_kernel): one workgroup per 32 tokens, operands read
-// straight into the MFMA register layout, the contraction split over the four waves and the
+// straight into the MFMA register layout, the contraction split over the waves and the
 // partial logits summed in a fixed order through LDS.
 //
 // fp32 path: a group of lanes per token, sequential fp32 FMA per logit out of LDS, butterfly arg-max per pick.
@@ -113,35 +113,32 @@ __device__ __forceinline__ void gate_select_store(f32x16 (&acc)[NT], int t, int 
   }
 }
 
-// One workgroup = 32*CT tokens (CT = 1 in every launch).  The contraction is split over the four wavefronts (wave w takes
-// the 64-wide K chunks w, w+4, ...), so even a small batch puts four waves on every compute
-// unit and each wave keeps two chunks of loads in flight; the partial logits are then added in
-// a fixed order (3, 2, 1, 0) through LDS, so results do not depend on timing, and wave 0 selects.
+// One workgroup = 32 tokens.  The contraction is split over its WAVES wavefronts (wave w takes the 64-wide K chunks w,
+// w + WAVES, ...), then every partial logit is summed in wave order through LDS, so results do not depend on timing, and
+// wave 0 selects.  What bounds it is the latency of the chunks' round trips, one after another in a wave: the fewer the
+// workgroups, the more waves share the chunks (launch_gate).
 // DIRECT: `wgt` is W_g itself, [d, E]: a lane gathers the eight values of a fragment with 2-byte
 // loads (stride E) instead of reading a transposed copy -- 32 NT small loads per chunk from a
 // matrix that sits in L2, which saves the launch that writes the copy.  Lanes of experts >= E
 // re-read expert E-1 (their logits are discarded) and rows past d re-read row d-1 (x is zero there).
-template <int NT, int CT, bool DIRECT>   // NT tiles of 32 experts, CT tiles of 32 tokens
-__global__ __launch_bounds__(kGateThreads) void gate_bf16_kernel(const bf16_t* __restrict__ x,
+template <int NT, int WAVES, bool DIRECT>   // NT tiles of 32 experts
+__global__ __launch_bounds__(WAVES * kWave) void gate_bf16_kernel(const bf16_t* __restrict__ x,
                                                                  const bf16_t* __restrict__ wgt, int N, int d,
                                                                  int E, int k, int32_t* __restrict__ topk_idx,
                                                                  float* __restrict__ topk_w) {
-  __shared__ float4 partial[NT * CT * 4 * kWave];
+  constexpr int kPieces = NT * 4;                       // float4 pieces of a lane's logits
+  __shared__ float4 partial[WAVES][kPieces][kWave];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int j = lane & 31, h = lane >> 5;
-  const int t0 = blockIdx.x * (32 * CT);
+  const int t0 = blockIdx.x * 32;
 
-  f32x16 acc[CT][NT];
+  f32x16 acc[NT];
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct)
+  for (int r = 0; r < NT; ++r)
 #pragma unroll
-    for (int r = 0; r < NT; ++r)
-#pragma unroll
-      for (int n = 0; n < 16; ++n) acc[ct][r][n] = 0.f;
+    for (int n = 0; n < 16; ++n) acc[r][n] = 0.f;
 
-  const bf16_t* xrow[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct) xrow[ct] = x + (size_t)min(t0 + ct * 32 + j, N - 1) * d + 32 * h;   // clamp the ragged last tile
+  const bf16_t* xrow = x + (size_t)min(t0 + j, N - 1) * d + 32 * h;   // clamp the ragged last tile
   const bf16_t* wrow = wgt + (size_t)j * d + 32 * h;
   const int nchunks = (d + 63) / 64;
   // DIRECT: column of W_g for the lane's expert in tile r, at row 32 h
@@ -159,12 +156,10 @@ __global__ __launch_bounds__(kGateThreads) void gate_bf16_kernel(const bf16_t* _
   };
 
   // lane reads k = 64c + 32h + 8s .. +8 of its row for s = 0..3 (64 contiguous bytes); pieces past d are zero
-  auto load_chunk = [&](int c, Frag (&xb)[CT][4], Frag (&wa)[NT][4]) {
+  auto load_chunk = [&](int c, Frag (&xb)[4], Frag (&wa)[NT][4]) {
     if (c * 64 + 64 <= d) {
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) xb[ct][s].u = *(const uint4*)(xrow[ct] + c * 64 + s * 8);
+      for (int s = 0; s < 4; ++s) xb[s].u = *(const uint4*)(xrow + c * 64 + s * 8);
 #pragma unroll
       for (int r = 0; r < NT; ++r)
 #pragma unroll
@@ -174,8 +169,7 @@ __global__ __launch_bounds__(kGateThreads) void gate_bf16_kernel(const bf16_t* _
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         const bool ok = c * 64 + 32 * h + s * 8 < d;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) xb[ct][s].u = ok ? *(const uint4*)(xrow[ct] + c * 64 + s * 8) : make_uint4(0, 0, 0, 0);
+        xb[s].u = ok ? *(const uint4*)(xrow + c * 64 + s * 8) : make_uint4(0, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < NT; ++r) {
           if (DIRECT) wa[r][s].u = gather_w(r, c * 64 + s * 8, false);
@@ -184,66 +178,55 @@ __global__ __launch_bounds__(kGateThreads) void gate_bf16_kernel(const bf16_t* _
       }
     }
   };
-  auto mma_chunk = [&](const Frag (&xb)[CT][4], const Frag (&wa)[NT][4]) {
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-      for (int r = 0; r < NT; ++r)
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-          acc[ct][r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[r][s].v, xb[ct][s].v, acc[ct][r], 0, 0, 0);
-  };
-
-  // kSets chunks of loads in flight per wave (register sets used in rotation): the kernel is bound by
-  // the latency of these round trips, so with few experts (small fragments) a third set pays
-  constexpr int kSets = NT <= 2 ? 3 : (NT == 8 ? 1 : 2);     // 256 experts: one set, or the fragments spill
-  Frag xb[kSets][CT][4], wa[kSets][NT][4];
-  int c = wave;
-#pragma unroll
-  for (int q = 0; q < kSets; ++q)
-    if (c + 4 * q < nchunks) load_chunk(c + 4 * q, xb[q], wa[q]);
-  for (; c < nchunks; c += 4 * kSets) {
-#pragma unroll
-    for (int q = 0; q < kSets; ++q)
-      if (c + 4 * q < nchunks) {
-        mma_chunk(xb[q], wa[q]);
-        if (c + 4 * (q + kSets) < nchunks) load_chunk(c + 4 * (q + kSets), xb[q], wa[q]);
-      }
-  }
-
-  // fixed-order sum of the four partial results: wave 3 writes, waves 2 and 1 add, wave 0 finishes
-#pragma unroll
-  for (int turn = 3; turn >= 1; --turn) {
-    if (wave == turn) {
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int r = 0; r < NT; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float4* slot = &partial[((ct * NT + r) * 4 + q) * kWave + lane];
-            float4 v = make_float4(acc[ct][r][4 * q], acc[ct][r][4 * q + 1], acc[ct][r][4 * q + 2], acc[ct][r][4 * q + 3]);
-            if (turn != 3) {
-              const float4 o = *slot;
-              v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
-            }
-            *slot = v;
-          }
-    }
-    __syncthreads();
-  }
-  if (wave != 0) return;
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
+  auto mma_chunk = [&](const Frag (&xb)[4], const Frag (&wa)[NT][4]) {
 #pragma unroll
     for (int r = 0; r < NT; ++r)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 o = partial[((ct * NT + r) * 4 + q) * kWave + lane];
-        acc[ct][r][4 * q] += o.x; acc[ct][r][4 * q + 1] += o.y; acc[ct][r][4 * q + 2] += o.z; acc[ct][r][4 * q + 3] += o.w;
+      for (int s = 0; s < 4; ++s) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[r][s].v, xb[s].v, acc[r], 0, 0, 0);
+  };
+
+  // chunks of loads in flight per wave (register sets used in rotation), as many as the registers of WAVES waves hold
+  constexpr int kSets = NT == 8 ? 1 : NT == 4 || WAVES == 8 ? 2 : 3;
+  Frag xb[kSets][4], wa[kSets][NT][4];
+  int c = wave;
+#pragma unroll
+  for (int q = 0; q < kSets; ++q)
+    if (c + WAVES * q < nchunks) load_chunk(c + WAVES * q, xb[q], wa[q]);
+  for (; c < nchunks; c += WAVES * kSets) {
+#pragma unroll
+    for (int q = 0; q < kSets; ++q)
+      if (c + WAVES * q < nchunks) {
+        mma_chunk(xb[q], wa[q]);
+        if (c + WAVES * (q + kSets) < nchunks) load_chunk(c + WAVES * (q + kSets), xb[q], wa[q]);
       }
-    if (t0 + ct * 32 < N) gate_select_store<NT>(acc[ct], t0 + ct * 32 + j, N, E, k, topk_idx, topk_w);
   }
+
+  // every piece of the logits is summed over the waves in ascending order, the pieces dealt to the waves
+#pragma unroll
+  for (int r = 0; r < NT; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      partial[wave][r * 4 + q][lane] = make_float4(acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]);
+  __syncthreads();
+  for (int i = wave; i < kPieces; i += WAVES) {
+    float4 v = partial[0][i][lane];
+#pragma unroll
+    for (int ww = 1; ww < WAVES; ++ww) {
+      const float4 o = partial[ww][i][lane];
+      v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+    }
+    partial[0][i][lane] = v;
+  }
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int r = 0; r < NT; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 o = partial[0][r * 4 + q][lane];
+      acc[r][4 * q] = o.x; acc[r][4 * q + 1] = o.y; acc[r][4 * q + 2] = o.z; acc[r][4 * q + 3] = o.w;
+    }
+  gate_select_store<NT>(acc, t0 + j, N, E, k, topk_idx, topk_w);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -458,6 +441,12 @@ __global__ __launch_bounds__(kGateThreads) void gate_f32_kernel(const float* __r
   }
 }
 
+// Tokens that the split-K kernel takes in one round: 256 workgroups of eight waves with 33 to 64 experts, 512 of four
+// below.  Past that the streaming kernel is ahead, in us (split-K, streaming; tokens x features): 64 experts 8000 x 2048
+// 17.5, 21.3; 12000 x 2048 31.1, 21.9; 16000 x 512 12.2, 10.3; 30000 x 1536 49.8, 32.4; 32 experts 16384 x 1024 10.7, 11.8;
+// 30000 x 2048 32.1, 23.5; 30000 x 256 8.2, 7.2.
+static bool gate_streams(int N, int nt) { return nt <= 2 && N > (nt == 2 ? 8192 : 16384); }
+
 hipError_t launch_gate(const void* x, const void* wg, int N, int d, int E, int k, int dtype, int32_t* idx, float* w,
                        void* ws, hipStream_t s) {
   if (N == 0) return hipSuccess;
@@ -478,7 +467,7 @@ hipError_t launch_gate(const void* x, const void* wg, int N, int d, int E, int k
   const int epad = nt * 32;
   bf16_t* wgt = (bf16_t*)ws;
   const bf16_t* xb = (const bf16_t*)x;
-  if (nt <= 2 && N >= 32768) {
+  if (gate_streams(N, nt)) {
     // large batches: direct-to-LDS streaming, four waves (two below 65536 tokens) share a weight tile
     const int dpad = gate_dpad(d);
     hipLaunchKernelGGL(gate_transpose_wg_kernel, dim3((dpad + 255) / 256, epad), dim3(256), 0, s, (const bf16_t*)wg, d,
@@ -496,20 +485,27 @@ hipError_t launch_gate(const void* x, const void* wg, int N, int d, int E, int k
 #undef FLEXMOE_GATE_LAUNCH
     return hipGetLastError();
   }
-  // small batches (a few waves per compute unit at most) and more than 64 experts: split-K kernel
-  const dim3 block(kGateThreads);
+  // small batches (a few waves per compute unit at most) and more than 64 experts: split-K kernel.
+  // Eight waves per workgroup where the fragments of W_g are many and a wave had several rounds of chunks, four otherwise.
+  // Four -> eight, in us (tokens x features, experts): 256 x 2048, 64: 20.4 -> 13.6; 12000 x 2048, 64: 54.0 -> 32.4;
+  // 30000 x 1536, 64: 65.9 -> 48.6; 4096 x 512, 128: 15.7 -> 14.6; but 16384 x 1024, 32: 10.7 -> 11.7.
   const dim3 grid((N + 31) / 32);
-  if (nt <= 2) {
-    // up to 64 experts: the fragments of W_g are gathered from the matrix as stored (one launch)
-    const bf16_t* wgb = (const bf16_t*)wg;
-    if (nt == 1) hipLaunchKernelGGL((gate_bf16_kernel<1, 1, true>), grid, block, 0, s, xb, wgb, N, d, E, k, idx, w);
-    else hipLaunchKernelGGL((gate_bf16_kernel<2, 1, true>), grid, block, 0, s, xb, wgb, N, d, E, k, idx, w);
-    return hipGetLastError();
+  const int waves = d >= 512 && (nt == 2 || nt == 4) ? 8 : 4;
+  const bool direct = nt <= 2;      // the fragments of W_g are gathered from the matrix as stored (one launch)
+  if (!direct)
+    hipLaunchKernelGGL(gate_transpose_wg_kernel, dim3((d + 255) / 256, epad), dim3(256), 0, s, (const bf16_t*)wg, d, E, epad, d, wgt);
+  const bf16_t* wgb = direct ? (const bf16_t*)wg : wgt;
+#define FLEXMOE_GATE_LAUNCH(NT_, WAVES_, DIRECT_) \
+  hipLaunchKernelGGL((gate_bf16_kernel<NT_, WAVES_, DIRECT_>), grid, dim3(WAVES_* kWave), 0, s, xb, wgb, N, d, E, k, idx, w)
+  switch (nt * 100 + waves) {
+    case 104: FLEXMOE_GATE_LAUNCH(1, 4, true); break;
+    case 204: FLEXMOE_GATE_LAUNCH(2, 4, true); break;
+    case 208: FLEXMOE_GATE_LAUNCH(2, 8, true); break;
+    case 404: FLEXMOE_GATE_LAUNCH(4, 4, false); break;
+    case 408: FLEXMOE_GATE_LAUNCH(4, 8, false); break;
+    default: FLEXMOE_GATE_LAUNCH(8, 4, false); break;
   }
-  hipLaunchKernelGGL(gate_transpose_wg_kernel, dim3((d + 255) / 256, epad), dim3(256), 0, s, (const bf16_t*)wg, d, E,
-                     epad, d, wgt);
-  if (nt == 4) hipLaunchKernelGGL((gate_bf16_kernel<4, 1, false>), grid, block, 0, s, xb, wgt, N, d, E, k, idx, w);
-  else hipLaunchKernelGGL((gate_bf16_kernel<8, 1, false>), grid, block, 0, s, xb, wgt, N, d, E, k, idx, w);
+#undef FLEXMOE_GATE_LAUNCH
   return hipGetLastError();
 }
 

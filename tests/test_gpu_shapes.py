@@ -74,3 +74,20 @@ def test_fp32_gate(api, N, d, E, k):  # noqa: F811
     ws = torch.empty(1 << 16, dtype=torch.uint8, device="cuda")
     binding.flexmoe_gate_topk(layer_mod.to_device(x), layer_mod.to_device(wg), k, idx, w, ws)
     check_gate(idx.cpu().numpy(), w.cpu().numpy(), x, wg, k, W.DT_F32)
+
+
+# bf16 gate: the last size of the split-K kernel and the first of the streaming one, fewer chunks of features than waves,
+# a partial last chunk, padded expert tiles, W_g as stored and transposed.  (check_gate wants at most 5 % of the tokens within
+# its error bound of a tie; the bound grows as d^1.5, 5e-4 at d = 520, against gaps of about 0.2 between k + 1 neighbouring
+# logits: about 1 % per pick at d = 520 but 3 % at d = 1032, so the larger d come with k = 1.)
+@pytest.mark.parametrize("N,d,E,k", [(8192, 520, 64, 2), (8193, 520, 64, 2), (16384, 72, 20, 1), (16385, 72, 20, 1), (33, 512, 33, 2),
+                                     (400, 1032, 100, 1), (400, 520, 128, 2), (1, 8, 48, 8), (165, 504, 64, 3), (500, 776, 256, 1)])
+def test_bf16_gate(api, N, d, E, k):  # noqa: F811
+    binding, layer_mod = api
+    rng = np.random.default_rng(N + E)
+    x, wg = (W.Bf16Tensor.from_f32(a.astype(np.float32)) for a in (rng.standard_normal((N, d)), rng.standard_normal((d, E)) / np.sqrt(d)))
+    idx = torch.full((N, k), -1, dtype=torch.int32, device="cuda")
+    w = torch.zeros((N, k), dtype=torch.float32, device="cuda")
+    ws = torch.empty(4 << 20, dtype=torch.uint8, device="cuda")
+    binding.flexmoe_gate_topk(layer_mod.to_device(x), layer_mod.to_device(wg), k, idx, w, ws)
+    check_gate(idx.cpu().numpy(), w.cpu().numpy(), W.decode(x), W.decode(wg), k, W.DT_BF16)
