@@ -7,9 +7,12 @@
 //   dW_g[:,e] = sum over the assignments routed to e of dl * x  (same sum, seen from the weights)
 //   db2_e = sum of the rows of dYp in e's buckets, db1_e = the same for dHpre
 //
-// All of it is HBM-bound row traffic.  The per-expert sums run over the bucketed layout
-// (an expert's rows are contiguous per vExpert), in two stages with a fixed summation order, so
-// results are reproducible: no atomics.
+// All of it is HBM-bound row traffic, on small layers the latency of a few dependent loads per launch.  The
+// per-expert sums run over the bucketed layout (an expert's rows are contiguous per vExpert), in two stages with a
+// fixed summation order, so results are reproducible: no atomics.  What does not depend on each other shares a
+// launch: both bias gradients (two launches in all); the logit gradients and the transposed copy of W_g; then the
+// gate's share of dX and the partial sums of dW_g; then their final sums.  Eight launches of 4.6 - 15 us became five:
+// 5003 tokens (d 192, f 768, E 12) 57.6 -> 31.2 us, 1500 tokens (d 1024, f 4096, E 32) 61.9 -> 37.0.
 #include "common.h"
 
 namespace flexmoe {
@@ -17,18 +20,10 @@ namespace flexmoe {
 constexpr int kBwdThreads = 256;
 constexpr int kBwdWaves = kBwdThreads / kWave;
 constexpr int kChunkRows = 128;                    // rows of one bucket summed by one workgroup
+constexpr int kSumThreads = 512;                   // of the partial sums: every wave has its 16 rows in flight at once
+constexpr int kSumWaves = kSumThreads / kWave;
+constexpr int kMaxGridY = 65535;
 constexpr int kChunkCols = 512;                    // columns per workgroup: 64 lanes x 16 bytes of bf16
-
-// [rows, cols] -> [cols, rows], both row-major (the gate weights are small: no tiling)
-template <typename T>
-__global__ __launch_bounds__(kBwdThreads) void transpose_small_kernel(const T* __restrict__ in, int rows, int cols,
-                                                                      T* __restrict__ out) {
-  const int n = rows * cols;
-  for (int i = blockIdx.x * kBwdThreads + threadIdx.x; i < n; i += gridDim.x * kBwdThreads) {
-    const int c = i / rows, r = i % rows;          // consecutive threads write consecutive outputs
-    out[i] = in[(size_t)r * cols + c];
-  }
-}
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -36,31 +31,41 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// One wave per token: the k gate-value gradients, the logit gradients, and the gate path's
-// share of dX added in place.  wgT is W_g transposed ([E, d]) so that an expert's column is a row.
+// First launch of the gate's backward pass.  Workgroups below token_blocks, a wave per token: the k gate-value
+// gradients and the logit gradients.  The others: wgT = W_g transposed ([E, d]), so that an expert's column is a row
+// (the gate weights are small: no tiling).
 template <typename T>
-__global__ __launch_bounds__(kBwdThreads) void gate_bwd_token_kernel(
-    const T* __restrict__ dy, const T* __restrict__ yp, const int32_t* __restrict__ dest,
-    const int32_t* __restrict__ idx, const float* __restrict__ w, const T* __restrict__ wgT, int N, int k, int d,
-    float* __restrict__ dl, T* __restrict__ dx) {
+__global__ __launch_bounds__(kBwdThreads) void gate_bwd_logits_kernel(
+    const T* __restrict__ dy, const T* __restrict__ yp, const int32_t* __restrict__ dest, const float* __restrict__ w,
+    int N, int k, int d, float* __restrict__ dl, int token_blocks, const T* __restrict__ wg, int E, T* __restrict__ wgT) {
   constexpr int VN = Vec16<T>::n;
+  if ((int)blockIdx.x >= token_blocks) {
+    const int n = d * E, stride = (gridDim.x - token_blocks) * kBwdThreads;
+    for (int i = (blockIdx.x - token_blocks) * kBwdThreads + threadIdx.x; i < n; i += stride) {
+      const int e = i / d, r = i % d;              // consecutive threads write consecutive outputs
+      wgT[i] = wg[(size_t)r * E + e];
+    }
+    return;
+  }
   const int lane = threadIdx.x % kWave;
   const int wave = blockIdx.x * kBwdWaves + threadIdx.x / kWave;
-  const int nwaves = gridDim.x * kBwdWaves;
+  const int nwaves = token_blocks * kBwdWaves;
   const int vec_per_row = d / VN;
   for (int t = wave; t < N; t += nwaves) {
     const uint4* dy_row = (const uint4*)(dy + (size_t)t * d);
-    float dg[FLEXMOE_MAX_TOPK], g[FLEXMOE_MAX_TOPK], dlv[FLEXMOE_MAX_TOPK];
-    int e[FLEXMOE_MAX_TOPK];
+    float dg[FLEXMOE_MAX_TOPK], g[FLEXMOE_MAX_TOPK];
+    int row[FLEXMOE_MAX_TOPK];
     float inner = 0.f;
 #pragma unroll
     for (int j = 0; j < FLEXMOE_MAX_TOPK; ++j) {
+      row[j] = j < k ? dest[t * k + j] : 0;
+      g[j] = j < k ? w[t * k + j] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < FLEXMOE_MAX_TOPK; ++j) {
       dg[j] = 0.f;
-      g[j] = 0.f;
-      e[j] = 0;
       if (j < k) {
-        const int a = t * k + j;
-        const uint4* yp_row = (const uint4*)(yp + (size_t)dest[a] * d);
+        const uint4* yp_row = (const uint4*)(yp + (size_t)row[j] * d);
         float acc = 0.f;
         for (int c = lane; c < vec_per_row; c += kWave) {
           float u[VN], v[VN];
@@ -70,15 +75,30 @@ __global__ __launch_bounds__(kBwdThreads) void gate_bwd_token_kernel(
           for (int q = 0; q < VN; ++q) acc = fmaf(u[q], v[q], acc);
         }
         dg[j] = wave_sum(acc);
-        g[j] = w[a];
-        e[j] = idx[a];
         inner = fmaf(g[j], dg[j], inner);
       }
     }
 #pragma unroll
+    for (int j = 0; j < FLEXMOE_MAX_TOPK; ++j)
+      if (j < k && lane == 0) dl[t * k + j] = g[j] * (dg[j] - inner);
+  }
+}
+
+// The gate path's share of dX, added in place: a wave per token, wave `wave` of `nwaves`.
+template <typename T>
+__device__ __forceinline__ void gate_bwd_dx(const float* __restrict__ dl, const int32_t* __restrict__ idx,
+                                            const T* __restrict__ wgT, int N, int k, int d, T* __restrict__ dx, int wave,
+                                            int nwaves) {
+  constexpr int VN = Vec16<T>::n;
+  const int lane = threadIdx.x % kWave;
+  const int vec_per_row = d / VN;
+  for (int t = wave; t < N; t += nwaves) {
+    float dlv[FLEXMOE_MAX_TOPK];
+    int e[FLEXMOE_MAX_TOPK];
+#pragma unroll
     for (int j = 0; j < FLEXMOE_MAX_TOPK; ++j) {
-      dlv[j] = g[j] * (dg[j] - inner);
-      if (j < k && lane == 0) dl[t * k + j] = dlv[j];
+      dlv[j] = j < k ? dl[t * k + j] : 0.f;
+      e[j] = j < k ? idx[t * k + j] : 0;
     }
     uint4* dx_row = (uint4*)(dx + (size_t)t * d);
     for (int c = lane; c < vec_per_row; c += kWave) {
@@ -130,19 +150,28 @@ __device__ __forceinline__ void chunk_starts(const int32_t* __restrict__ voff, i
   __syncthreads();
 }
 
+// Columns per workgroup of stage 1: 64 lanes x 16 bytes.
+template <typename T> static constexpr int kSumCols = kChunkCols * Vec16<T>::n / 8;
+
 // Stage 1: partial[chunk, c] = sum over the chunk's rows of weight(row) * in[row, c], fp32.
 // WEIGHTED: weight(row p) = row_w[src[p]] (a value per assignment id); otherwise 1.
-// Wave w sums rows w, w+4, ... of the chunk in ascending order; the four waves' sums are added
-// in wave order through LDS.
+// Wave w sums rows w, w + 8, ... of the chunk in ascending order; the waves' sums are added in wave order through
+// LDS.  One workgroup sums the `chunk` it is given for the column blocks cb, cb + cb_step, ..: those of
+// the first matrix s0, then those of a second one, s1.
+template <typename T> struct SumInput {
+  const T* in;
+  int C, blocks;                                     // columns, column blocks (0: no such matrix)
+  float* partial;
+};
 template <typename T, bool WEIGHTED>
-__global__ __launch_bounds__(kBwdThreads) void bucket_colsum_partial_kernel(
-    const T* __restrict__ in, const float* __restrict__ row_w, const int32_t* __restrict__ src,
-    const int32_t* __restrict__ voff, int V, int C, float* __restrict__ partial) {
-  constexpr int VN = Vec16<T>::n;
+__device__ __forceinline__ void bucket_colsum_partial(const SumInput<T>& s0, const SumInput<T>& s1, const float* __restrict__ row_w,
+                                                      const int32_t* __restrict__ src, const int32_t* __restrict__ voff,
+                                                      int V, int chunk, int cb, int cb_step) {
+  constexpr int VN = Vec16<T>::n, U = kChunkRows / kSumWaves;
   __shared__ int chunk_start[FLEXMOE_MAX_VEXPERTS + 1];
-  __shared__ float red[kBwdWaves][kWave][VN];
+  __shared__ float red[kSumWaves][kWave][VN];
+  __shared__ float weight[kChunkRows];
   chunk_starts(voff, V, chunk_start);
-  const int chunk = blockIdx.x;
   if (chunk >= chunk_start[V]) return;               // uniform
   // bucket of this chunk: the last v with chunk_start[v] <= chunk (binary search, every thread)
   int lo = 0, hi = V - 1;
@@ -155,56 +184,86 @@ __global__ __launch_bounds__(kBwdThreads) void bucket_colsum_partial_kernel(
   const int row0 = voff[v] + (chunk - chunk_start[v]) * kChunkRows;
   const int rows = min(kChunkRows, voff[v + 1] - row0);
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int col = blockIdx.y * kChunkCols * VN / 8 + lane * VN;      // 512 bf16 or 256 fp32 columns per block
-  float acc[VN];
+  if (WEIGHTED) {
+    if ((int)threadIdx.x < rows) weight[threadIdx.x] = row_w[src[row0 + threadIdx.x]];
+    __syncthreads();
+  }
+  for (; cb < s0.blocks + s1.blocks; cb += cb_step) {
+    const SumInput<T>& m = cb < s0.blocks ? s0 : s1;
+    const int col = (cb < s0.blocks ? cb : cb - s0.blocks) * kSumCols<T> + lane * VN;
+    float acc[VN];
 #pragma unroll
-  for (int q = 0; q < VN; ++q) acc[q] = 0.f;
-  if (col < C) {
-    // eight rows in flight per wave; the sum itself stays in ascending row order
-    constexpr int U = 8;
-    for (int r0 = wave; r0 < rows; r0 += kBwdWaves * U) {
+    for (int q = 0; q < VN; ++q) acc[q] = 0.f;
+    if (col < m.C) {
       uint4 raw[U];
-      float wt[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        raw[i] = *(const uint4*)(m.in + (size_t)(row0 + min(wave + i * kSumWaves, rows - 1)) * m.C + col);
 #pragma unroll
       for (int i = 0; i < U; ++i) {
-        const int r = r0 + i * kBwdWaves;
-        const int p = row0 + min(r, rows - 1);
-        raw[i] = *(const uint4*)(in + (size_t)p * C + col);
-        wt[i] = r < rows ? (WEIGHTED ? row_w[src[p]] : 1.f) : 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < U; ++i) {
-        if (r0 + i * kBwdWaves < rows) {
+        const int r = wave + i * kSumWaves;
+        if (r < rows) {
+          const float wt = WEIGHTED ? weight[r] : 1.f;
           float u[VN];
           Vec16<T>::unpack(raw[i], u);
 #pragma unroll
-          for (int q = 0; q < VN; ++q) acc[q] = fmaf(wt[i], u[q], acc[q]);
+          for (int q = 0; q < VN; ++q) acc[q] = fmaf(wt, u[q], acc[q]);
         }
       }
     }
-  }
 #pragma unroll
-  for (int q = 0; q < VN; ++q) red[wave][lane][q] = acc[q];
-  __syncthreads();
-  if (wave == 0 && col < C) {
+    for (int q = 0; q < VN; ++q) red[wave][lane][q] = acc[q];
+    __syncthreads();
+    if (wave == 0 && col < m.C) {
 #pragma unroll
-    for (int q = 0; q < VN; ++q) {
-      float s = red[0][lane][q];
-      for (int ww = 1; ww < kBwdWaves; ++ww) s += red[ww][lane][q];
-      partial[(size_t)chunk * C + col + q] = s;
+      for (int q = 0; q < VN; ++q) {
+        float s = red[0][lane][q];
+#pragma unroll
+        for (int ww = 1; ww < kSumWaves; ++ww) s += red[ww][lane][q];
+        m.partial[(size_t)chunk * m.C + col + q] = s;
+      }
     }
+    __syncthreads();
   }
+}
+template <typename T>
+__global__ __launch_bounds__(kSumThreads) void bias_partial_kernel(SumInput<T> s0, SumInput<T> s1, const int32_t* __restrict__ voff, int V) {
+  bucket_colsum_partial<T, false>(s0, s1, nullptr, nullptr, voff, V, blockIdx.x, blockIdx.y, gridDim.y);
+}
+// Second launch of the gate's backward pass: blockIdx.y < token_rows adds the gate's share of dX, the others sum dW_g's chunks.
+template <typename T>
+__global__ __launch_bounds__(kSumThreads) void gate_bwd_apply_kernel(const float* __restrict__ dl, const int32_t* __restrict__ idx,
+                                                                    const T* __restrict__ wgT, int N, int k, int d,
+                                                                    T* __restrict__ dx, int token_rows, SumInput<T> xp,
+                                                                    const int32_t* __restrict__ src,
+                                                                    const int32_t* __restrict__ voff, int V) {
+  if ((int)blockIdx.y < token_rows)
+    gate_bwd_dx<T>(dl, idx, wgT, N, k, d, dx, (blockIdx.y * gridDim.x + blockIdx.x) * kSumWaves + threadIdx.x / kWave,
+                   token_rows * gridDim.x * kSumWaves);
+  else
+    bucket_colsum_partial<T, true>(xp, SumInput<T>{nullptr, 0, 0, nullptr}, dl, src, voff, V, blockIdx.x, blockIdx.y - token_rows,
+                                   gridDim.y - token_rows);
 }
 
 // Stage 2: out[e, c] = sum of the partials of e's chunks.  One workgroup per (expert, 64 columns):
 // the expert's chunks, numbered through its buckets in ascending vExpert id and ascending row
 // order, are dealt round-robin to the four waves; each wave adds its chunks in that order (four
 // loads in flight), then the waves' sums are added in wave order.  A fixed order: reproducible.
-// TRANSPOSED: out is [C, E] (the gate weights' layout).
+// TRANSPOSED: out is [C, E] (the gate weights' layout).  Up to two sets of sums: the second one's column blocks follow
+// the first one's.
+template <typename T> struct SumOutput {
+  const float* partial;
+  int C, blocks;                                      // columns, blocks of 64 of them
+  T* out;
+};
 template <typename T, bool TRANSPOSED>
-__global__ __launch_bounds__(kBwdThreads) void bucket_colsum_final_kernel(
-    const float* __restrict__ partial, const int32_t* __restrict__ voff, const int32_t* __restrict__ owner, int V,
-    int E, int C, T* __restrict__ out) {
+__global__ __launch_bounds__(kBwdThreads) void bucket_colsum_final_kernel(const SumOutput<T> s0, const SumOutput<T> s1,
+                                                                          const int32_t* __restrict__ voff,
+                                                                          const int32_t* __restrict__ owner, int V, int E) {
+  const bool second = (int)blockIdx.x >= s0.blocks;
+  const float* partial = second ? s1.partial : s0.partial;
+  const int C = second ? s1.C : s0.C;
+  T* out = second ? s1.out : s0.out;
   __shared__ int chunk_start[FLEXMOE_MAX_VEXPERTS + 1];
   __shared__ int list[FLEXMOE_MAX_VEXPERTS];          // the expert's buckets, ascending
   __shared__ int nlist;
@@ -242,7 +301,7 @@ __global__ __launch_bounds__(kBwdThreads) void bucket_colsum_final_kernel(
     }
     __syncthreads();
   }
-  const int c = blockIdx.x * kWave + lane;
+  const int c = (blockIdx.x - (second ? s0.blocks : 0)) * kWave + lane;
   float s = 0.f;
   if (c < C) {
     int ord = 0;                                       // running number of the expert's chunks
@@ -277,17 +336,17 @@ __global__ __launch_bounds__(kBwdThreads) void bucket_colsum_final_kernel(
 static int max_chunks(int A, int V) { return A / kChunkRows + V; }
 static size_t partial_bytes(int A, int V, int C) { return align_up((size_t)max_chunks(A, V) * C * sizeof(float), 256); }
 
-template <typename T, bool WEIGHTED, bool TRANSPOSED>
-static hipError_t bucket_colsum(const void* in, const float* row_w, const int32_t* src, const int32_t* voff,
-                                const int32_t* owner, int A, int V, int E, int C, float* partial, void* out,
-                                hipStream_t s) {
-  const int cols_per_block = kChunkCols * Vec16<T>::n / 8;
-  const dim3 grid1(max_chunks(A, V), (C + cols_per_block - 1) / cols_per_block);
-  hipLaunchKernelGGL((bucket_colsum_partial_kernel<T, WEIGHTED>), grid1, dim3(kBwdThreads), 0, s, (const T*)in, row_w,
-                     src, voff, V, C, partial);
-  const dim3 grid2((C + kWave - 1) / kWave, E);
-  hipLaunchKernelGGL((bucket_colsum_final_kernel<T, TRANSPOSED>), grid2, dim3(kBwdThreads), 0, s, partial, voff, owner,
-                     V, E, C, (T*)out);
+template <typename T> static SumInput<T> sum_input(const void* in, int C, float* partial) {
+  return SumInput<T>{(const T*)in, C, in ? (C + kSumCols<T> - 1) / kSumCols<T> : 0, partial};
+}
+template <typename T> static SumOutput<T> sum_output(const float* partial, int C, void* out) {
+  return SumOutput<T>{partial, C, out ? (C + kWave - 1) / kWave : 0, (T*)out};
+}
+template <typename T, bool TRANSPOSED>
+static hipError_t launch_final_sums(const SumOutput<T>& s0, const SumOutput<T>& s1, const int32_t* voff, const int32_t* owner,
+                                    int V, int E, hipStream_t s) {
+  hipLaunchKernelGGL((bucket_colsum_final_kernel<T, TRANSPOSED>), dim3(s0.blocks + s1.blocks, E), dim3(kBwdThreads), 0, s, s0, s1,
+                     voff, owner, V, E);
   return hipGetLastError();
 }
 
@@ -304,15 +363,20 @@ static hipError_t gate_bwd_t(const void* wg, const int32_t* idx, const float* w,
   T* wgT = (T*)ws;
   float* partial = (float*)((char*)ws + align_up((size_t)E * d * sizeof(T), 256));
   const int A = N * k;
-  if (N > 0) {
-    hipLaunchKernelGGL((transpose_small_kernel<T>), dim3(min(256, (d * E + kBwdThreads - 1) / kBwdThreads)),
-                       dim3(kBwdThreads), 0, s, (const T*)wg, d, E, wgT);
-    const int want = (N + kBwdWaves - 1) / kBwdWaves;
-    hipLaunchKernelGGL((gate_bwd_token_kernel<T>), dim3(min(want, 256 * 8)), dim3(kBwdThreads), 0, s, (const T*)dy,
-                       (const T*)yp, dest, idx, w, (const T*)wgT, N, k, d, dl, (T*)dx);
-  }
+  const int token_blocks = min((N + kBwdWaves - 1) / kBwdWaves, 256 * 8);
+  if (N > 0)
+    hipLaunchKernelGGL((gate_bwd_logits_kernel<T>), dim3(token_blocks + min(256, (d * E + kBwdThreads - 1) / kBwdThreads)),
+                       dim3(kBwdThreads), 0, s, (const T*)dy, (const T*)yp, dest, w, N, k, d, dl, token_blocks, (const T*)wg, E, wgT);
   // dW_g[:, e] = sum over e's bucket rows p of dl[src[p]] * Xp[p, :]
-  return bucket_colsum<T, true, true>(xp, dl, src, voff, owner, A, V, E, d, partial, dwg, s);
+  const SumInput<T> in = sum_input<T>(xp, d, partial);
+  if (N > 0) {
+    const int gx = max_chunks(A, V);
+    // a wave per token, in at most 1024 workgroups (four per compute unit)
+    const int token_rows = max(1, min(((N + kSumWaves - 1) / kSumWaves + gx - 1) / gx, 1024 / gx));
+    hipLaunchKernelGGL((gate_bwd_apply_kernel<T>), dim3(gx, token_rows + min(in.blocks, kMaxGridY - token_rows)), dim3(kSumThreads), 0,
+                       s, dl, idx, (const T*)wgT, N, k, d, (T*)dx, token_rows, in, src, voff, V);
+  }
+  return launch_final_sums<T, true>(sum_output<T>(partial, d, dwg), sum_output<T>(nullptr, 0, nullptr), voff, owner, V, E, s);
 }
 
 hipError_t launch_gate_bwd(const void* wg, const int32_t* idx, const float* w, const void* dy,
@@ -328,19 +392,21 @@ hipError_t launch_gate_bwd(const void* wg, const int32_t* idx, const float* w, c
 // are dead once the weight gradients are done, so the partial sums go there.
 size_t bias_grads_ws_bytes(int A, int d, int f, int V, int dtype) {
   const size_t s = dtype == FLEXMOE_BF16 ? 2 : 4;
-  return align_up((size_t)A * f * s, 256) + partial_bytes(A, V, d > f ? d : f);
+  return align_up((size_t)A * f * s, 256) + partial_bytes(A, V, d) + partial_bytes(A, V, f);
 }
 
 template <typename T>
 static hipError_t bias_grads_t(const void* dyp, const int32_t* voff, const int32_t* owner, int A, int d, int f, int E,
                                int V, void* db1, void* db2, void* ws, hipStream_t s) {
   const T* dhpre = (const T*)ws;
-  float* partial = (float*)((char*)ws + align_up((size_t)A * f * sizeof(T), 256));
-  hipError_t err = hipSuccess;
-  if (db1) err = bucket_colsum<T, false, false>(dhpre, nullptr, nullptr, voff, owner, A, V, E, f, partial, db1, s);
-  if (err != hipSuccess) return err;
-  if (db2) err = bucket_colsum<T, false, false>(dyp, nullptr, nullptr, voff, owner, A, V, E, d, partial, db2, s);
-  return err;
+  float* partial1 = (float*)((char*)ws + align_up((size_t)A * f * sizeof(T), 256));
+  float* partial2 = (float*)((char*)partial1 + partial_bytes(A, V, f));
+  if (!db1 && !db2) return hipSuccess;
+  const SumInput<T> s1 = sum_input<T>(db1 ? dhpre : nullptr, f, partial1), s2 = sum_input<T>(db2 ? dyp : nullptr, d, partial2);
+  if (A > 0)
+    hipLaunchKernelGGL((bias_partial_kernel<T>), dim3(max_chunks(A, V), min(s1.blocks + s2.blocks, kMaxGridY)), dim3(kSumThreads), 0, s,
+                       s1, s2, voff, V);
+  return launch_final_sums<T, false>(sum_output<T>(partial1, f, db1), sum_output<T>(partial2, d, db2), voff, owner, V, E, s);
 }
 
 hipError_t launch_bias_grads(const void* dyp, const int32_t* voff, const int32_t* owner, int A, int d, int f, int E,

@@ -91,3 +91,50 @@ def test_bf16_gate(api, N, d, E, k):  # noqa: F811
     ws = torch.empty(4 << 20, dtype=torch.uint8, device="cuda")
     binding.flexmoe_gate_topk(layer_mod.to_device(x), layer_mod.to_device(wg), k, idx, w, ws)
     check_gate(idx.cpu().numpy(), w.cpu().numpy(), W.decode(x), W.decode(wg), k, W.DT_BF16)
+
+
+# bias and gate gradients: chunks of 128 rows (one row, whole chunks, one row more), column blocks of 512 (bf16) or 256
+# (fp32) columns and ragged ones, experts without tokens, more token rows than chunks
+@pytest.mark.parametrize("dtype,N,d,f,E,k,V", [
+    ("bf16", 1, 8, 8, 2, 1, 2), ("bf16", 128, 512, 520, 1, 1, 1), ("bf16", 129, 520, 512, 1, 1, 1), ("bf16", 2100, 136, 1032, 5, 2, 8),
+    ("bf16", 300, 72, 64, 200, 4, 300), ("f32", 129, 256, 264, 1, 1, 1), ("f32", 700, 40, 520, 6, 3, 9)])
+def test_bias_and_gate_gradients(api, dtype, N, d, f, E, k, V):  # noqa: F811
+    """Against the same sums in float64.  Errors: the result's rounding (2^-8 in bf16) and 2^-22 per term summed in fp32."""
+    B, layer_mod = api
+    cfg = W.scaled(W.CONFIGS["gpt_m" if dtype == "bf16" else "tiny"], N=N, d=d, f=f, E=E, k=k, V=V, max_rep=3, backward=True)
+    inp = W.make_layer_inputs(cfg, seed=5)
+    dev = upload(layer_mod, inp)
+    L = layer_mod.MoELayer.for_config(cfg)
+    L.forward(dev["x"], dev["wg"], dev["w1"], dev["w2"], *W.placement_from_loads(W.prior_loads(cfg), V, 3, shuffle_seed=2))
+    dx0 = L.backward(dev["dy"], dev["w1"], dev["w2"])[0].clone()
+    A, tdt = N * k, L.dx.dtype
+    dhpre = L.ws[:A * f * L.dx.element_size()].view(tdt).view(A, f).double()
+    voff = L.vexpert_off.long()
+    row_e = torch.repeat_interleave(L.vexpert_owner.long(), voff[1:] - voff[:-1])
+
+    def check(got, ref, size, terms):
+        bound = (2.0 ** -8 if tdt == torch.bfloat16 and got.dtype == tdt else 2.0 ** -22) * (ref.abs() + 1e-30) + terms * 2.0 ** -22 * size
+        assert bool(((got.double() - ref).abs() <= bound).all()), ((got.double() - ref).abs() / bound).max()
+
+    def expert_sums(rows):
+        return torch.zeros(E, rows.shape[1], dtype=torch.float64, device="cuda").index_add_(0, row_e, rows)
+
+    want = [(t, expert_sums(t), expert_sums(t.abs())) for t in (dhpre, L.dyp.double())]
+    db1, db2 = torch.full((E, f), 7.0, dtype=tdt, device="cuda"), torch.full((E, d), 7.0, dtype=tdt, device="cuda")
+    for one, two in ((db1, None), (None, db2), (db1, db2)):      # either may be left out
+        B.flexmoe_expert_bias_grads(L.dyp, L.vexpert_off, L.vexpert_owner, f, E, one, two, L.ws)
+        for got, (_, ref, size) in zip((one, two), want):
+            if got is not None:
+                check(got, ref, size, A)
+                got.fill_(7.0)
+    dl, dwg = torch.zeros(N, k, device="cuda"), torch.full((d, E), 7.0, dtype=tdt, device="cuda")
+    B.flexmoe_gate_bwd(dev["wg"], L.topk_idx, L.topk_w, dev["dy"], L.yp, L.xp, L.dest, L.src, L.vexpert_off, L.vexpert_owner,
+                       dl, L.dx, dwg, L.ws)
+    g, yk = L.topk_w.double(), L.yp.double()[L.dest.long()].view(N, k, d)
+    dg, size = (dev["dy"].double()[:, None] * yk).sum(2), (dev["dy"].double()[:, None] * yk).abs().sum(2)
+    check(dl, g * (dg - (g * dg).sum(1, keepdim=True)), g * (size + (g * size).sum(1, keepdim=True)), d)
+    cols = dev["wg"].double().t()[L.topk_idx.long()]
+    step = (dl.double()[:, :, None] * cols)
+    check(L.dx, dx0.double() + step.sum(1), dx0.double().abs() + step.abs().sum(1), k + 1)
+    rows = dl.double().flatten()[L.src.long()][:, None] * L.xp.double()
+    check(dwg, expert_sums(rows).t(), expert_sums(rows.abs()).t(), A)
