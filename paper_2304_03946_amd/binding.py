@@ -102,17 +102,19 @@ def _ptr(t):
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous(), "device tensors must be contiguous CUDA tensors"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream():
-    """Handle of torch's current stream on the current device (the stream every call is enqueued on)."""
-    if _raw_stream is not None:
-        return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of torch's current stream on the current device (the stream every call is enqueued on).  Only ever called
+    behind a `_ptr` that has seen a CUDA tensor, so the runtime is initialised and the low-level queries are enough."""
+    if _raw_stream is not None and _device is not None:
+        return _raw_stream(_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check(status: int, where: str):
@@ -129,7 +131,10 @@ def dtype_code(t: torch.Tensor) -> int:
 
 
 def _host_i32(a):
-    return np.ascontiguousarray(np.asarray(a, dtype=np.int32))
+    """`a` as a contiguous int32 array, and its address (the array has to outlive the call the address goes to)."""
+    if type(a) is not np.ndarray or a.dtype != np.int32 or not a.flags.c_contiguous:
+        a = np.ascontiguousarray(np.asarray(a, dtype=np.int32))
+    return a, a.__array_interface__["data"][0]
 
 
 def flexmoe_workspace_bytes(N, d, f, E, k, V, dtype) -> int:
@@ -140,29 +145,27 @@ def flexmoe_gate_topk(x, wg, k, topk_idx, topk_w, ws):
     N, d = x.shape
     E = wg.shape[1]
     st = load_library().flexmoe_gate_topk(_ptr(x), _ptr(wg), N, d, E, k, dtype_code(x), _ptr(topk_idx), _ptr(topk_w),
-                                          _ptr(ws), ws.numel() * ws.element_size(), _stream())
+                                          _ptr(ws), ws.nbytes, _stream())
     _check(st, "flexmoe_gate_topk")
 
 
 def flexmoe_route(topk_idx, E, rep_off_host, rep_ids_host, expert_count, vexpert_count, vexpert_off, vexpert_owner,
                   dest, src, ws):
     N, k = topk_idx.shape
-    off, ids = _host_i32(rep_off_host), _host_i32(rep_ids_host)
+    (off, off_at), (ids, ids_at) = _host_i32(rep_off_host), _host_i32(rep_ids_host)
     V = int(ids.shape[0])
-    st = load_library().flexmoe_route(_ptr(topk_idx), N, k, E, V, off.ctypes.data_as(ctypes.c_void_p),
-                                      ids.ctypes.data_as(ctypes.c_void_p), _ptr(expert_count), _ptr(vexpert_count),
+    st = load_library().flexmoe_route(_ptr(topk_idx), N, k, E, V, off_at, ids_at, _ptr(expert_count), _ptr(vexpert_count),
                                       _ptr(vexpert_off), _ptr(vexpert_owner), _ptr(dest), _ptr(src), _ptr(ws),
-                                      ws.numel() * ws.element_size(), _stream())
+                                      ws.nbytes, _stream())
     _check(st, "flexmoe_route")
 
 
 def flexmoe_route_static(topk_idx, E, rep_off_host, rep_ids_host, expert_count, vexpert_count, vexpert_off,
                          vexpert_owner, dest, src):
     N, k = topk_idx.shape
-    off, ids = _host_i32(rep_off_host), _host_i32(rep_ids_host)
+    (off, off_at), (ids, ids_at) = _host_i32(rep_off_host), _host_i32(rep_ids_host)
     V = int(ids.shape[0])
-    st = load_library().flexmoe_route_static(_ptr(topk_idx), N, k, E, V, off.ctypes.data_as(ctypes.c_void_p),
-                                             ids.ctypes.data_as(ctypes.c_void_p), _ptr(expert_count),
+    st = load_library().flexmoe_route_static(_ptr(topk_idx), N, k, E, V, off_at, ids_at, _ptr(expert_count),
                                              _ptr(vexpert_count), _ptr(vexpert_off), _ptr(vexpert_owner), _ptr(dest),
                                              _ptr(src), _stream())
     _check(st, "flexmoe_route_static")
@@ -181,7 +184,7 @@ def flexmoe_expert_ffn_bwd_top1(dyp, xp, hpre, w1, w2, vexpert_off, vexpert_owne
     st = load_library().flexmoe_expert_ffn_bwd_top1(_ptr(dyp), _ptr(xp), _ptr(hpre), _ptr(h), _ptr(w1), _ptr(w2),
                                                     _ptr(vexpert_off), _ptr(vexpert_owner), _ptr(src), N, d, f, E, V,
                                                     act, dtype_code(xp), _ptr(dx), _ptr(dw1), _ptr(dw2), _ptr(ws),
-                                                    ws.numel() * ws.element_size(), _stream())
+                                                    ws.nbytes, _stream())
     _check(st, "flexmoe_expert_ffn_bwd_top1")
 
 
@@ -197,7 +200,7 @@ def flexmoe_expert_ffn_fwd(xp, vexpert_off, vexpert_owner, w1, b1, w2, b2, act, 
     V = vexpert_owner.shape[0]
     st = load_library().flexmoe_expert_ffn_fwd(_ptr(xp), _ptr(vexpert_off), _ptr(vexpert_owner), _ptr(w1), _ptr(b1),
                                                _ptr(w2), _ptr(b2), A, d, f, E, V, act, dtype_code(xp), _ptr(hpre),
-                                               _ptr(h), _ptr(yp), _ptr(ws), ws.numel() * ws.element_size(), _stream())
+                                               _ptr(h), _ptr(yp), _ptr(ws), ws.nbytes, _stream())
     _check(st, "flexmoe_expert_ffn_fwd")
 
 
@@ -208,7 +211,7 @@ def flexmoe_expert_ffn_fwd_top1(x, src, vexpert_off, vexpert_owner, w1, b1, w2, 
     st = load_library().flexmoe_expert_ffn_fwd_top1(_ptr(x), _ptr(src), _ptr(vexpert_off), _ptr(vexpert_owner),
                                                     _ptr(w1), _ptr(b1), _ptr(w2), _ptr(b2), N, d, f, E, V, act,
                                                     dtype_code(x), _ptr(hpre), _ptr(h), _ptr(y), _ptr(ws),
-                                                    ws.numel() * ws.element_size(), _stream())
+                                                    ws.nbytes, _stream())
     _check(st, "flexmoe_expert_ffn_fwd_top1")
 
 
@@ -218,7 +221,7 @@ def flexmoe_expert_ffn_bwd(dyp, xp, hpre, w1, w2, vexpert_off, vexpert_owner, ac
     V = vexpert_owner.shape[0]
     st = load_library().flexmoe_expert_ffn_bwd(_ptr(dyp), _ptr(xp), _ptr(hpre), _ptr(h), _ptr(w1), _ptr(w2), _ptr(vexpert_off),
                                                _ptr(vexpert_owner), A, d, f, E, V, act, dtype_code(xp), _ptr(dxp),
-                                               _ptr(dw1), _ptr(dw2), _ptr(ws), ws.numel() * ws.element_size(), _stream())
+                                               _ptr(dw1), _ptr(dw2), _ptr(ws), ws.nbytes, _stream())
     _check(st, "flexmoe_expert_ffn_bwd")
 
 
@@ -230,7 +233,7 @@ def flexmoe_gate_bwd(wg, topk_idx, topk_w, dy, yp, xp, dest, src, vexpert_off, v
     st = load_library().flexmoe_gate_bwd(_ptr(wg), _ptr(topk_idx), _ptr(topk_w), _ptr(dy), _ptr(yp), _ptr(xp),
                                          _ptr(dest), _ptr(src), _ptr(vexpert_off), _ptr(vexpert_owner), N, d, E, k, V,
                                          dtype_code(dy), _ptr(dl), _ptr(dx), _ptr(dwg), _ptr(ws),
-                                         ws.numel() * ws.element_size(), _stream())
+                                         ws.nbytes, _stream())
     _check(st, "flexmoe_gate_bwd")
 
 
@@ -239,7 +242,7 @@ def flexmoe_expert_bias_grads(dyp, vexpert_off, vexpert_owner, f, E, db1, db2, w
     V = vexpert_owner.shape[0]
     st = load_library().flexmoe_expert_bias_grads(_ptr(dyp), _ptr(vexpert_off), _ptr(vexpert_owner), A, d, f, E, V,
                                                   dtype_code(dyp), _ptr(db1), _ptr(db2), _ptr(ws),
-                                                  ws.numel() * ws.element_size(), _stream())
+                                                  ws.nbytes, _stream())
     _check(st, "flexmoe_expert_bias_grads")
 
 
@@ -250,5 +253,5 @@ def flexmoe_expert_ffn_fwd_gather(x, src, k, vexpert_off, vexpert_owner, w1, b1,
     st = load_library().flexmoe_expert_ffn_fwd_gather(_ptr(x), _ptr(src), _ptr(vexpert_off), _ptr(vexpert_owner),
                                                       _ptr(w1), _ptr(b1), _ptr(w2), _ptr(b2), N, k, d, f, E, V, act,
                                                       dtype_code(x), _ptr(hpre), _ptr(h), _ptr(yp), _ptr(ws),
-                                                      ws.numel() * ws.element_size(), _stream())
+                                                      ws.nbytes, _stream())
     _check(st, "flexmoe_expert_ffn_fwd_gather")
