@@ -102,18 +102,27 @@ static size_t wgrad_tail_bytes(int A, int d, int f, int V) {
 }
 
 // Which rows kernels a call of these sizes takes: 32 or 64 = rows_gemm_small_bf16 with row tiles of that many rows,
-// 0 = the 256 x 256 kernels.  By the mean rows per expert, since the loads are not known here (skewed: a few experts have
+// 0 = the 256 x 256 kernels.  First by the mean rows per expert, since the loads are not known here (skewed: a few experts have
 // ten times the mean, most have less).  Measured, both products of a forward pass in us:
 //   1 row per expert  (16 tokens, d 1024, f 4096, E 32, k 2):     32-row tiles 59, 64-row 69, 256-row 162
 //   8 rows            (256 tokens, d 2048, f 8192, E 64, k 2):    610, 562, 1135
 //   62 rows           (2000 tokens, the same layer):              1381, 1078, 1412
 //   94 rows           (1500 tokens, d 1024, f 4096, E 32, k 2):   226, 179, 208
 //   128 rows          (4096 tokens, d 512, f 1024, E 128, k 4):   149, 115, 143
+// And 64-row tiles for any number of rows per expert while the wider product does not fill 224 of the 256 x 256 tiles (a
+// tile per compute unit: most of the chip waits for a few long tiles, and for half-empty ones).  Whole training steps,
+// f = 4 d, k 2, in us, 256-row and 64-row tiles:
+//   d 128:  4800 rows of 12 experts 166, 148; 16000 of 40 190, 184;   past the line: 32000 of 40 229, 237
+//   d 192:  9600 of 12 (no whole 128-wide rounds) 223, 175
+//   d 256:  9600 of 12 217, 200; 8000 of 40 225, 207;                 past: 16000 of 40 262, 269; 19200 of 12 262, 275
+//   d 512:  4800 of 12 275, 240; 6400 of 4 289, 266;                  past: 9600 of 12 337, 343; 8000 of 40 379, 391
+//   d 1024: 2400 of 12 389, 339; 3200 of 4 384, 327;                  past: 4800 of 12 536, 550; 6400 of 4 554, 604
 constexpr int kSmall32Rows = 4, kSmall64Rows = 160;
+constexpr long long kSmallOutputs = 224ll * BM * BN;
 static int small_rows(int A, int d, int f, int E) {
   if ((long long)A * std::max(d, f) >= 1ll << 30) return 0;      // 32-bit byte offsets of the row loads
   if (A <= kSmall32Rows * E) return 32;
-  return A <= kSmall64Rows * E ? 64 : 0;
+  return A <= kSmall64Rows * E || (long long)A * std::max(d, f) <= kSmallOutputs ? 64 : 0;
 }
 static size_t small_ws_bytes(int A, int d, int f, int E) {
   const int bm = small_rows(A, d, f, E);

@@ -22,12 +22,14 @@ def test_weight_gradient_work_lists(api, N, d, f, E, V):  # noqa: F811
     stagewise(api, W.scaled(W.CONFIGS["gpt_m"], N=N, d=d, f=f, E=E, V=V, max_rep=3))
 
 
-# rows kernels for few rows per expert: 32-row tiles (at most 4 rows per expert on average; N = 1: two experts with a
-# single row, the contraction cut into its most segments), 64-row tiles up to 160 rows, and the first size past either
-# line; K with a partial last tile (d, f multiples of 8 only), K below one tile, ragged column tiles, 512 buckets
+# rows kernels for few rows per expert or little output: 32-row tiles (at most 4 rows per expert on average; N = 1: two
+# experts with a single row, the contraction cut into its most segments), 64-row tiles up to 160 rows or 224 256 x 256
+# tiles of outputs, and the first size past either line (K whole and not whole 128-wide rounds); K with a partial last
+# tile (d, f multiples of 8 only), K below one tile, ragged column tiles, 512 buckets
 @pytest.mark.parametrize("N,d,f,E,k,V,act", [
     (1, 1024, 4096, 32, 2, 48, W.ACT_GELU_ERF), (31, 264, 520, 16, 2, 21, W.ACT_GELU_TANH), (33, 264, 520, 16, 2, 21, W.ACT_RELU),
     (7, 48, 8, 4, 1, 6, W.ACT_GELU_ERF), (640, 136, 392, 8, 2, 12, W.ACT_GELU_ERF), (641, 136, 392, 8, 2, 12, W.ACT_GELU_ERF),
+    (896, 128, 8192, 2, 2, 3, W.ACT_GELU_ERF), (897, 128, 8192, 2, 2, 3, W.ACT_GELU_ERF), (7500, 136, 1032, 4, 2, 6, W.ACT_GELU_TANH),
     (130, 512, 2048, 8, 2, 9, W.ACT_RELU), (900, 128, 256, 256, 4, 512, W.ACT_GELU_ERF)])
 def test_rows_products_with_few_rows_per_expert(api, N, d, f, E, k, V, act):  # noqa: F811
     stagewise(api, W.scaled(W.CONFIGS["gpt_m"], N=N, d=d, f=f, E=E, k=k, V=V, act=act, max_rep=3))
@@ -127,7 +129,7 @@ def test_bias_and_gate_gradients(api, dtype, N, d, f, E, k, V):  # noqa: F811
             if got is not None:
                 check(got, ref, size, A)
                 got.fill_(7.0)
-    dl, dwg = torch.zeros(N, k, device="cuda"), torch.full((d, E), 7.0, dtype=tdt, device="cuda")
+    dl, dwg = torch.zeros((N, k), dtype=torch.float32, device="cuda"), torch.full((d, E), 7.0, dtype=tdt, device="cuda")
     B.flexmoe_gate_bwd(dev["wg"], L.topk_idx, L.topk_w, dev["dy"], L.yp, L.xp, L.dest, L.src, L.vexpert_off, L.vexpert_owner,
                        dl, L.dx, dwg, L.ws)
     g, yk = L.topk_w.double(), L.yp.double()[L.dest.long()].view(N, k, d)
