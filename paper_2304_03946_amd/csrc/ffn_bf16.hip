@@ -124,11 +124,18 @@ static int small_rows(int A, int d, int f, int E) {
   if (A <= kSmall32Rows * E) return 32;
   return A <= kSmall64Rows * E || (long long)A * std::max(d, f) <= kSmallOutputs ? 64 : 0;
 }
+// Partial tiles that a product with contraction K and NC columns can leave at most (see small_segments): none for short
+// contractions.
+static long long small_slots(int A, int E, int bm, int K, int NC) {
+  const int most = small_segments(1, (K + SK - 1) / SK);
+  return most == 1 ? 0 : std::min<long long>(kSmallSlots, (long long)(A / bm + E) * ((NC + SN - 1) / SN) * most);
+}
 static size_t small_ws_bytes(int A, int d, int f, int E) {
   const int bm = small_rows(A, d, f, E);
   if (!bm) return 0;
   return align_up((size_t)(A / bm + E + 1) * sizeof(i32x4), 256) + align_up((size_t)A * sizeof(int32_t), 256) +
-         align_up(kSmallSlots * sizeof(int), 256) + (size_t)kSmallSlots * bm * SN * sizeof(float);
+         align_up(kSmallSlots * sizeof(int), 256) +
+         (size_t)std::max(small_slots(A, E, bm, d, f), small_slots(A, E, bm, f, d)) * bm * SN * sizeof(float);
 }
 
 size_t ffn_ws_bytes(int A, int d, int f, int E, int V, int dtype) {
