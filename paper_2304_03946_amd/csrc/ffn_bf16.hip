@@ -64,15 +64,20 @@ namespace flexmoe {
 // =============================================================================================
 // Weight gradient: how many 32-token K tiles one workgroup contracts before the expert's sum is
 // cut into a further segment: a compute unit's even share of all (output tile, K tile) pairs
-// (shorter segments measured slower: more fp32 partial tiles), so that the hottest expert's contraction is no longer one serial K loop.  0 = no cutting:
+// but at least 32 (shorter segments measured slower: more fp32 partial tiles), so that the hottest expert's contraction is
+// no longer one serial K loop; at least 16 where the gradient of an expert is at most four output tiles and even those
+// leave most of the chip idle (a share of at most 8 K tiles).  Whole training steps, f = 4 d, k 2, in us, 32 and 16: d 128,
+// 4800 rows of 12 experts 166, 148; d 192, 9600 of 12 223, 208; d 256, 16000 of 40 (share 7.8) 262, 250; past the line,
+// d 256, 32000 of 40 (share 15.6) 337, 353; d 512 (16 output tiles), 4000 of 40 228, 256.  0 = no cutting:
 // when a segment would hold more than a quarter of all tokens (many output tiles per expert: the
 // grid is busy anyway, and the fp32 partial tiles would be large).
 constexpr int kComputeUnits = 256;
 static int wgrad_seg_tiles(int A, int d, int f) {
   const long long out_tiles = (long long)((d + BM - 1) / BM) * ((f + BN - 1) / BN);
   const long long k_tiles = A / DK;
-  long long seg = k_tiles * out_tiles / kComputeUnits;
-  if (seg < 32) seg = 32;
+  const long long share = k_tiles * out_tiles / kComputeUnits;
+  const long long least = share <= 8 && out_tiles <= 4 ? 16 : 32;
+  const long long seg = std::max(share, least);
   return 4 * seg <= k_tiles ? (int)seg : 0;
 }
 // Upper bounds over all load distributions: extra segments (beyond one per expert), and partial

@@ -16,8 +16,10 @@ def stagewise(api, cfg, seed=3):  # noqa: F811
 
 
 # one job per 1/8 and 1/4 of a patch: the work lists are dealt out over 64 and 32 bins (several lanes rows of the
-# minimum); two patches per job: 4 bins; 70 jobs: the second pass of 64
-@pytest.mark.parametrize("N,d,f,E,V", [(2100, 256, 1024, 12, 17), (1300, 256, 2048, 6, 9), (4200, 512, 1024, 5, 8), (3000, 256, 512, 70, 80)])
+# minimum); two patches per job: 4 bins; 70 jobs: the second pass of 64; segments of
+# 16 K tiles: the first size that is cut and the last that is not, and 32 K tiles from a share of 8 on
+@pytest.mark.parametrize("N,d,f,E,V", [(2100, 256, 1024, 12, 17), (1300, 256, 2048, 6, 9), (4200, 512, 1024, 5, 8), (3000, 256, 512, 70, 80),
+                                       (1024, 136, 264, 3, 5), (1023, 136, 264, 3, 5), (16500, 136, 264, 3, 5)])
 def test_weight_gradient_work_lists(api, N, d, f, E, V):  # noqa: F811
     stagewise(api, W.scaled(W.CONFIGS["gpt_m"], N=N, d=d, f=f, E=E, V=V, max_rep=3))
 
