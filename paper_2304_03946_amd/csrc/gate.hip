@@ -11,8 +11,12 @@
 // W_g^T travel global -> LDS with direct loads that fetch whole 128-byte lines of a row (eight
 // rows per instruction), several 64-wide K tiles in flight per workgroup, and the MFMA fragments
 // are read from LDS.  Otherwise (gate_bf16_kernel): one workgroup per 32 tokens, operands read
-// straight into the MFMA register layout, the contraction split over the waves and the
+// straight into the MFMA register layout, the contraction split over four waves (or four pairs) and the
 // partial logits summed in a fixed order through LDS.
+// The order of a logit's sum is part of the result: logits that differ by fp32 rounding alone decide a near tie, and with
+// it a token's experts.  Below 32768 tokens, and with more than 64 experts, every kernel adds in quarters: quarter q holds
+// the 64-wide K chunks q, q + 4, .., summed in ascending order, and the logit is q0 + (q1 + (q2 + q3)).  From 32768
+// tokens with up to 64 experts: one sum over all chunks, from a first chunk that depends on the token's workgroup.
 //
 // fp32 path: a group of lanes per token, sequential fp32 FMA per logit out of LDS, butterfly arg-max per pick.
 #include <algorithm>
@@ -113,38 +117,40 @@ __device__ __forceinline__ void gate_select_store(f32x16 (&acc)[NT], int t, int 
   }
 }
 
-// One workgroup = 32 tokens.  The contraction is split over its WAVES wavefronts (wave w takes the 64-wide K chunks w,
-// w + WAVES, ...), then every partial logit is summed in wave order through LDS, so results do not depend on timing, and
-// wave 0 selects.  What bounds it is the latency of the chunks' round trips, one after another in a wave: the fewer the
-// workgroups, the more waves share the chunks (launch_gate).
+// One workgroup = 32 tokens.  The contraction is split over four wavefronts (wave w % 4 takes the 64-wide K chunks of
+// quarter w % 4); with G > 1 there are G waves per quarter, each with NT / G of the expert tiles.  Then every partial logit
+// is summed over the quarters through LDS, the pieces dealt to all waves, and wave 0 selects.  What bounds it is the latency
+// of the chunks' round trips, one after another in a wave: where the fragments of W_g are many, a second wave per quarter
+// has half of them to fetch and room for more chunks in flight (launch_gate).
 // DIRECT: `wgt` is W_g itself, [d, E]: a lane gathers the eight values of a fragment with 2-byte
 // loads (stride E) instead of reading a transposed copy -- 32 NT small loads per chunk from a
 // matrix that sits in L2, which saves the launch that writes the copy.  Lanes of experts >= E
 // re-read expert E-1 (their logits are discarded) and rows past d re-read row d-1 (x is zero there).
-template <int NT, int WAVES, bool DIRECT>   // NT tiles of 32 experts
-__global__ __launch_bounds__(WAVES * kWave) void gate_bf16_kernel(const bf16_t* __restrict__ x,
+template <int NT, int G, bool DIRECT>   // NT tiles of 32 experts, G waves per quarter
+__global__ __launch_bounds__(4 * G * kWave) void gate_bf16_kernel(const bf16_t* __restrict__ x,
                                                                  const bf16_t* __restrict__ wgt, int N, int d,
                                                                  int E, int k, int32_t* __restrict__ topk_idx,
                                                                  float* __restrict__ topk_w) {
+  constexpr int W = 4, NTW = NT / G;                    // quarters; expert tiles of a wave
   constexpr int kPieces = NT * 4;                       // float4 pieces of a lane's logits
-  __shared__ float4 partial[WAVES][kPieces][kWave];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  __shared__ float4 partial[W][kPieces][kWave];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, quarter = wave % W, r0 = wave / W * NTW;
   const int j = lane & 31, h = lane >> 5;
   const int t0 = blockIdx.x * 32;
 
-  f32x16 acc[NT];
+  f32x16 acc[NTW];
 #pragma unroll
-  for (int r = 0; r < NT; ++r)
+  for (int r = 0; r < NTW; ++r)
 #pragma unroll
     for (int n = 0; n < 16; ++n) acc[r][n] = 0.f;
 
   const bf16_t* xrow = x + (size_t)min(t0 + j, N - 1) * d + 32 * h;   // clamp the ragged last tile
-  const bf16_t* wrow = wgt + (size_t)j * d + 32 * h;
+  const bf16_t* wrow = wgt + (size_t)(r0 * 32 + j) * d + 32 * h;
   const int nchunks = (d + 63) / 64;
   // DIRECT: column of W_g for the lane's expert in tile r, at row 32 h
-  const bf16_t* wcol[NT];
+  const bf16_t* wcol[NTW];
 #pragma unroll
-  for (int r = 0; r < NT; ++r) wcol[r] = wgt + (size_t)(32 * h) * E + min(r * 32 + j, E - 1);
+  for (int r = 0; r < NTW; ++r) wcol[r] = wgt + (size_t)(32 * h) * E + min((r0 + r) * 32 + j, E - 1);
   auto gather_w = [&](int r, int k0, bool full) -> uint4 {        // W_g[k0 + 32 h + 0..7, expert]
     Frag f;
 #pragma unroll
@@ -156,12 +162,12 @@ __global__ __launch_bounds__(WAVES * kWave) void gate_bf16_kernel(const bf16_t* 
   };
 
   // lane reads k = 64c + 32h + 8s .. +8 of its row for s = 0..3 (64 contiguous bytes); pieces past d are zero
-  auto load_chunk = [&](int c, Frag (&xb)[4], Frag (&wa)[NT][4]) {
+  auto load_chunk = [&](int c, Frag (&xb)[4], Frag (&wa)[NTW][4]) {
     if (c * 64 + 64 <= d) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) xb[s].u = *(const uint4*)(xrow + c * 64 + s * 8);
 #pragma unroll
-      for (int r = 0; r < NT; ++r)
+      for (int r = 0; r < NTW; ++r)
 #pragma unroll
         for (int s = 0; s < 4; ++s)
           wa[r][s].u = DIRECT ? gather_w(r, c * 64 + s * 8, true) : *(const uint4*)(wrow + (size_t)r * 32 * d + c * 64 + s * 8);
@@ -171,62 +177,63 @@ __global__ __launch_bounds__(WAVES * kWave) void gate_bf16_kernel(const bf16_t* 
         const bool ok = c * 64 + 32 * h + s * 8 < d;
         xb[s].u = ok ? *(const uint4*)(xrow + c * 64 + s * 8) : make_uint4(0, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < NT; ++r) {
+        for (int r = 0; r < NTW; ++r) {
           if (DIRECT) wa[r][s].u = gather_w(r, c * 64 + s * 8, false);
           else wa[r][s].u = ok ? *(const uint4*)(wrow + (size_t)r * 32 * d + c * 64 + s * 8) : make_uint4(0, 0, 0, 0);
         }
       }
     }
   };
-  auto mma_chunk = [&](const Frag (&xb)[4], const Frag (&wa)[NT][4]) {
+  auto mma_chunk = [&](const Frag (&xb)[4], const Frag (&wa)[NTW][4]) {
 #pragma unroll
-    for (int r = 0; r < NT; ++r)
+    for (int r = 0; r < NTW; ++r)
 #pragma unroll
       for (int s = 0; s < 4; ++s) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[r][s].v, xb[s].v, acc[r], 0, 0, 0);
   };
 
-  // chunks of loads in flight per wave (register sets used in rotation), as many as the registers of WAVES waves hold
-  constexpr int kSets = NT == 8 ? 1 : NT == 4 || WAVES == 8 ? 2 : 3;
-  Frag xb[kSets][4], wa[kSets][NT][4];
-  int c = wave;
+  // chunks of loads in flight per wave (register sets used in rotation), as many as the registers hold
+  constexpr int kSets = NTW == 8 ? 1 : NTW == 4 ? 2 : 3;
+  Frag xb[kSets][4], wa[kSets][NTW][4];
+  int c = quarter;
 #pragma unroll
   for (int q = 0; q < kSets; ++q)
-    if (c + WAVES * q < nchunks) load_chunk(c + WAVES * q, xb[q], wa[q]);
-  for (; c < nchunks; c += WAVES * kSets) {
+    if (c + W * q < nchunks) load_chunk(c + W * q, xb[q], wa[q]);
+  for (; c < nchunks; c += W * kSets) {
 #pragma unroll
     for (int q = 0; q < kSets; ++q)
-      if (c + WAVES * q < nchunks) {
+      if (c + W * q < nchunks) {
         mma_chunk(xb[q], wa[q]);
-        if (c + WAVES * (q + kSets) < nchunks) load_chunk(c + WAVES * (q + kSets), xb[q], wa[q]);
+        if (c + W * (q + kSets) < nchunks) load_chunk(c + W * (q + kSets), xb[q], wa[q]);
       }
   }
 
-  // every piece of the logits is summed over the waves in ascending order, the pieces dealt to the waves
+  // quarter 0 + (1 + (2 + 3)), the pieces dealt to the waves
 #pragma unroll
-  for (int r = 0; r < NT; ++r)
+  for (int r = 0; r < NTW; ++r)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      partial[wave][r * 4 + q][lane] = make_float4(acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]);
+      partial[quarter][(r0 + r) * 4 + q][lane] = make_float4(acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]);
   __syncthreads();
-  for (int i = wave; i < kPieces; i += WAVES) {
-    float4 v = partial[0][i][lane];
+  for (int i = wave; i < kPieces; i += W * G) {
+    float4 v = partial[W - 1][i][lane];
 #pragma unroll
-    for (int ww = 1; ww < WAVES; ++ww) {
-      const float4 o = partial[ww][i][lane];
-      v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+    for (int q = W - 2; q >= 0; --q) {
+      const float4 o = partial[q][i][lane];
+      v.x = o.x + v.x; v.y = o.y + v.y; v.z = o.z + v.z; v.w = o.w + v.w;
     }
     partial[0][i][lane] = v;
   }
   __syncthreads();
   if (wave != 0) return;
+  f32x16 l[NT];
 #pragma unroll
   for (int r = 0; r < NT; ++r)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const float4 o = partial[0][r * 4 + q][lane];
-      acc[r][4 * q] = o.x; acc[r][4 * q + 1] = o.y; acc[r][4 * q + 2] = o.z; acc[r][4 * q + 3] = o.w;
+      l[r][4 * q] = o.x; l[r][4 * q + 1] = o.y; l[r][4 * q + 2] = o.z; l[r][4 * q + 3] = o.w;
     }
-  gate_select_store<NT>(acc, t0 + j, N, E, k, topk_idx, topk_w);
+  gate_select_store<NT>(l, t0 + j, N, E, k, topk_idx, topk_w);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -236,6 +243,8 @@ __global__ __launch_bounds__(WAVES * kWave) void gate_bf16_kernel(const bf16_t* 
 // i's 16 bytes at M0 + 16*i, i.e. eight lanes fill one row, so the swizzle is applied by choosing
 // which chunk of the row a lane fetches.  Chunks past d come from a row of zeros (x) or from the
 // zero padding of the transposed weights; token rows past N are clamped (their results are dropped).
+// QUARTERS: one accumulator per quarter of the chunks and gate_bf16_kernel's fragments, so that a token's logits are the
+// same bits in either kernel.
 // ---------------------------------------------------------------------------------------------
 __device__ const uint4 kGateZeroRow[8] = {};
 typedef __attribute__((address_space(3))) unsigned char gate_lds_t;
@@ -257,7 +266,7 @@ __device__ __forceinline__ void gate_wait_tiles(int tiles) {   // callers keep L
   }
 }
 
-template <int NT, int WAVES, int S>
+template <int NT, int WAVES, int S, bool QUARTERS>
 __global__ __launch_bounds__(WAVES * kWave) void gate_dma_kernel(const bf16_t* __restrict__ x,
                                                                  const bf16_t* __restrict__ wgt, int N, int d,
                                                                  int dpad, int E, int k,
@@ -293,7 +302,7 @@ __global__ __launch_bounds__(WAVES * kWave) void gate_dma_kernel(const bf16_t* _
   // Workgroups start their contraction at different K tiles and wrap around, so that the requests in flight on the
   // chip are not all at the same column offset of their rows (measured: -7 % on 65536 tokens x 2048 features).
   // The order of a token's sum then depends on its workgroup, i.e. on the token's index only: still reproducible.
-  const int kshift = (int)((blockIdx.x * 5u) % (unsigned)KT);
+  const int kshift = QUARTERS ? 0 : (int)((blockIdx.x * 5u) % (unsigned)KT);
   auto issue = [&](int kt) {
     const unsigned st = lds_base + (kt % S) * kStage;
     const int ktr = kt + kshift < KT ? kt + kshift : kt + kshift - KT;
@@ -312,38 +321,52 @@ __global__ __launch_bounds__(WAVES * kWave) void gate_dma_kernel(const bf16_t* _
     }
   };
 
-  f32x16 acc[NT];
+  constexpr int Q = QUARTERS ? 4 : 1;
+  f32x16 acc[Q][NT];
 #pragma unroll
-  for (int r = 0; r < NT; ++r)
+  for (int q = 0; q < Q; ++q)
 #pragma unroll
-    for (int n = 0; n < 16; ++n) acc[r][n] = 0.f;
+    for (int r = 0; r < NT; ++r)
+#pragma unroll
+      for (int n = 0; n < 16; ++n) acc[q][r][n] = 0.f;
 
 #pragma unroll
   for (int p = 0; p < S - 1; ++p)
     if (p < KT) issue(p);
-  for (int kt = 0; kt < KT; ++kt) {
-    // tile kt has landed once at most the younger tiles are still in flight
-    gate_wait_tiles<L>(min(S - 2, KT - 1 - kt));
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    if (kt + S - 1 < KT) issue(kt + S - 1);                   // into the stage every wave has just left
-    const gate_lds_t* xs = (const gate_lds_t*)smem + (kt % S) * kStage + wave * 32 * 128;
-    const gate_lds_t* wsm = (const gate_lds_t*)smem + (kt % S) * kStage + kXBytes;
+  for (int kt0 = 0; kt0 < KT; kt0 += Q) {
 #pragma unroll
-    for (int ks = 0; ks < kGateDK / 16; ++ks) {
-      const int chunk = ((2 * ks + h) ^ (j & 7)) << 4;
-      Frag xb;
-      xb.v = *(const __attribute__((address_space(3))) bf16x8*)(xs + j * 128 + chunk);
+    for (int q = 0; q < Q; ++q) {
+      const int kt = kt0 + q;
+      if (kt >= KT) break;
+      // tile kt has landed once at most the younger tiles are still in flight
+      gate_wait_tiles<L>(min(S - 2, KT - 1 - kt));
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+      if (kt + S - 1 < KT) issue(kt + S - 1);                   // into the stage every wave has just left
+      const gate_lds_t* xs = (const gate_lds_t*)smem + (kt % S) * kStage + wave * 32 * 128;
+      const gate_lds_t* wsm = (const gate_lds_t*)smem + (kt % S) * kStage + kXBytes;
 #pragma unroll
-      for (int r = 0; r < NT; ++r) {
-        Frag wa;
-        wa.v = *(const __attribute__((address_space(3))) bf16x8*)(wsm + (r * 32 + j) * 128 + chunk);
-        acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa.v, xb.v, acc[r], 0, 0, 0);
+      for (int ks = 0; ks < kGateDK / 16; ++ks) {
+        const int chunk = ((QUARTERS ? ks + 4 * h : 2 * ks + h) ^ (j & 7)) << 4;
+        Frag xb;
+        xb.v = *(const __attribute__((address_space(3))) bf16x8*)(xs + j * 128 + chunk);
+#pragma unroll
+        for (int r = 0; r < NT; ++r) {
+          Frag wa;
+          wa.v = *(const __attribute__((address_space(3))) bf16x8*)(wsm + (r * 32 + j) * 128 + chunk);
+          acc[q][r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa.v, xb.v, acc[q][r], 0, 0, 0);
+        }
       }
     }
   }
-  if (t0 < N) gate_select_store<NT>(acc, t0 + j, N, E, k, topk_idx, topk_w);
+  f32x16 l[NT];
+#pragma unroll
+  for (int r = 0; r < NT; ++r)
+#pragma unroll
+    for (int n = 0; n < 16; ++n)
+      l[r][n] = QUARTERS ? acc[0][r][n] + (acc[1 % Q][r][n] + (acc[2 % Q][r][n] + acc[3 % Q][r][n])) : acc[0][r][n];
+  if (t0 < N) gate_select_store<NT>(l, t0 + j, N, E, k, topk_idx, topk_w);
 }
 
 // fp32: LPT lanes per token, lane l of a token's group owns experts l, l + LPT, ... (LPT = the experts rounded up to a
@@ -441,10 +464,9 @@ __global__ __launch_bounds__(kGateThreads) void gate_f32_kernel(const float* __r
   }
 }
 
-// Tokens that the split-K kernel takes in one round: 256 workgroups of eight waves with 33 to 64 experts, 512 of four
-// below.  Past that the streaming kernel is ahead, in us (split-K, streaming; tokens x features): 64 experts 8000 x 2048
-// 17.5, 21.3; 12000 x 2048 31.1, 21.9; 16000 x 512 12.2, 10.3; 30000 x 1536 49.8, 32.4; 32 experts 16384 x 1024 10.7, 11.8;
-// 30000 x 2048 32.1, 23.5; 30000 x 256 8.2, 7.2.
+// Tokens that the split-K kernel takes in one round: 256 workgroups with 33 to 64 experts, 512 below.  Past that the
+// streaming kernel is ahead, in us (split-K, streaming; tokens x features): 64 experts 9000 x 2048 30.8, 22.5; 12000 x 2048
+// 32.9, 23.4; 17000 x 1024 26.6, 25.1; 32000 x 64 14.1, 10.3; 32 experts 25000 x 1024 16.7, 13.4; 32000 x 256 7.8, 7.2.
 static bool gate_streams(int N, int nt) { return nt <= 2 && N > (nt == 2 ? 8192 : 16384); }
 
 hipError_t launch_gate(const void* x, const void* wg, int N, int d, int E, int k, int dtype, int32_t* idx, float* w,
@@ -472,38 +494,40 @@ hipError_t launch_gate(const void* x, const void* wg, int N, int d, int E, int k
     const int dpad = gate_dpad(d);
     hipLaunchKernelGGL(gate_transpose_wg_kernel, dim3((dpad + 255) / 256, epad), dim3(256), 0, s, (const bf16_t*)wg, d,
                        E, epad, dpad, wgt);
-#define FLEXMOE_GATE_LAUNCH(NT_, WAVES_, S_)                                                                       \
-  hipLaunchKernelGGL((gate_dma_kernel<NT_, WAVES_, S_>), dim3((N + 32 * WAVES_ - 1) / (32 * WAVES_)),                \
+#define FLEXMOE_GATE_LAUNCH(NT_, WAVES_, S_, Q_)                                                                   \
+  hipLaunchKernelGGL((gate_dma_kernel<NT_, WAVES_, S_, Q_>), dim3((N + 32 * WAVES_ - 1) / (32 * WAVES_)),            \
                      dim3(WAVES_* kWave), 0, s, xb, wgt, N, d, dpad, E, k, idx, w)
     if (N >= 65536) {
-      if (nt == 1) FLEXMOE_GATE_LAUNCH(1, 4, 6);
-      else FLEXMOE_GATE_LAUNCH(2, 4, 6);
+      if (nt == 1) FLEXMOE_GATE_LAUNCH(1, 4, 6, false);
+      else FLEXMOE_GATE_LAUNCH(2, 4, 6, false);
+    } else if (N >= 32768) {
+      if (nt == 1) FLEXMOE_GATE_LAUNCH(1, 2, 6, false);
+      else FLEXMOE_GATE_LAUNCH(2, 2, 6, false);
     } else {
-      if (nt == 1) FLEXMOE_GATE_LAUNCH(1, 2, 6);
-      else FLEXMOE_GATE_LAUNCH(2, 2, 6);
+      if (nt == 1) FLEXMOE_GATE_LAUNCH(1, 2, 6, true);
+      else FLEXMOE_GATE_LAUNCH(2, 2, 6, true);
     }
 #undef FLEXMOE_GATE_LAUNCH
     return hipGetLastError();
   }
   // small batches (a few waves per compute unit at most) and more than 64 experts: split-K kernel.
-  // Eight waves per workgroup where the fragments of W_g are many and a wave had several rounds of chunks, four otherwise.
-  // Four -> eight, in us (tokens x features, experts): 256 x 2048, 64: 20.4 -> 13.6; 12000 x 2048, 64: 54.0 -> 32.4;
-  // 30000 x 1536, 64: 65.9 -> 48.6; 4096 x 512, 128: 15.7 -> 14.6; but 16384 x 1024, 32: 10.7 -> 11.7.
+  // Two waves per quarter with 33 to 64 experts and several rounds of chunks (one, two; us; 64 experts): 256 x 2048 20.6,
+  // 15.6; 12000 x 2048 49.8, 32.9; 32000 x 1024 42.5, 36.2; but 16000 x 512 13.2, 13.4.  With more experts two waves lose what the
+  // smaller fragments win: 4096 x 1024, 128 experts 19.6, 20.7; 2000 x 2048, 100 experts 26.3, 29.2.
   const dim3 grid((N + 31) / 32);
-  const int waves = d >= 512 && (nt == 2 || nt == 4) ? 8 : 4;
+  const int g = d >= 512 && nt == 2 ? 2 : 1;
   const bool direct = nt <= 2;      // the fragments of W_g are gathered from the matrix as stored (one launch)
   if (!direct)
     hipLaunchKernelGGL(gate_transpose_wg_kernel, dim3((d + 255) / 256, epad), dim3(256), 0, s, (const bf16_t*)wg, d, E, epad, d, wgt);
   const bf16_t* wgb = direct ? (const bf16_t*)wg : wgt;
-#define FLEXMOE_GATE_LAUNCH(NT_, WAVES_, DIRECT_) \
-  hipLaunchKernelGGL((gate_bf16_kernel<NT_, WAVES_, DIRECT_>), grid, dim3(WAVES_* kWave), 0, s, xb, wgb, N, d, E, k, idx, w)
-  switch (nt * 100 + waves) {
-    case 104: FLEXMOE_GATE_LAUNCH(1, 4, true); break;
-    case 204: FLEXMOE_GATE_LAUNCH(2, 4, true); break;
-    case 208: FLEXMOE_GATE_LAUNCH(2, 8, true); break;
-    case 404: FLEXMOE_GATE_LAUNCH(4, 4, false); break;
-    case 408: FLEXMOE_GATE_LAUNCH(4, 8, false); break;
-    default: FLEXMOE_GATE_LAUNCH(8, 4, false); break;
+#define FLEXMOE_GATE_LAUNCH(NT_, G_, DIRECT_) \
+  hipLaunchKernelGGL((gate_bf16_kernel<NT_, G_, DIRECT_>), grid, dim3(4 * G_ * kWave), 0, s, xb, wgb, N, d, E, k, idx, w)
+  switch (nt * 10 + g) {
+    case 11: FLEXMOE_GATE_LAUNCH(1, 1, true); break;
+    case 21: FLEXMOE_GATE_LAUNCH(2, 1, true); break;
+    case 22: FLEXMOE_GATE_LAUNCH(2, 2, true); break;
+    case 41: FLEXMOE_GATE_LAUNCH(4, 1, false); break;
+    default: FLEXMOE_GATE_LAUNCH(8, 1, false); break;
   }
 #undef FLEXMOE_GATE_LAUNCH
   return hipGetLastError();

@@ -142,3 +142,37 @@ def test_bias_and_gate_gradients(api, dtype, N, d, f, E, k, V):  # noqa: F811
     check(L.dx, dx0.double() + step.sum(1), dx0.double().abs() + step.abs().sum(1), k + 1)
     rows = dl.double().flatten()[L.src.long()][:, None] * L.xp.double()
     check(dwg, expert_sums(rows).t(), expert_sums(rows.abs()).t(), A)
+
+
+# the same kernels: logits that differ in the order of their fp32 sums alone.  One feature per 64-wide chunk is non-zero; an
+# expert's products are one 2^24 and small whole numbers, so that each addition rounds and the order decides ties
+@pytest.mark.parametrize("N,d,E,k", [(257, 256, 20, 2), (33, 1024, 32, 1), (300, 448, 64, 3), (257, 1024, 64, 2), (100, 712, 40, 8), (300, 576, 128, 2),
+                                     (200, 320, 100, 2), (200, 1024, 200, 2), (8192, 1024, 48, 2), (8193, 1024, 48, 2), (16384, 520, 32, 2),
+                                     (16385, 520, 32, 2), (24577, 520, 32, 2), (16385, 2048, 32, 2), (32767, 1032, 64, 2)])
+def test_order_of_the_gate_sums(api, N, d, E, k):  # noqa: F811
+    """Fewer than 32768 tokens or more than 64 experts: chunks c, c + 4, .. in ascending order, then 0 + (1 + (2 + 3))."""
+    binding, layer_mod = api
+    rng = np.random.default_rng(N + d + E)
+    chunks, patterns = (d + 63) // 64, d % 64 or 64
+    small = rng.choice([-1.0, 0.0, 1.0, 1.0, 2.0], size=(chunks, patterns, E)).astype(np.float32)
+    big = rng.integers(chunks, size=(patterns, E))
+    small[big, np.arange(patterns)[:, None], np.arange(E)] = 2.0 ** 24
+    wg, x = np.zeros((chunks, 64, E), dtype=np.float32), np.zeros((N, chunks, 64), dtype=np.float32)
+    wg[:, :patterns] = small
+    of = rng.integers(patterns, size=N)                  # a token's pattern: its feature within every chunk
+    x[np.arange(N), :, of] = 1.0
+    wg, x = wg.reshape(-1, E)[:d], x.reshape(N, -1)[:, :d]
+    quarter = [np.zeros((patterns, E), dtype=np.float32) for _ in range(4)]
+    for c in range(chunks):
+        quarter[c % 4] = quarter[c % 4] + small[c]
+    logits = quarter[0] + (quarter[1] + (quarter[2] + quarter[3]))
+    assert logits.dtype == np.float32 and (logits != small.astype(np.float64).sum(0)).mean() > 0.1, "the order must matter"
+    want = np.argsort(-logits, axis=1, kind="stable")[:, :k]
+    idx = torch.full((N, k), -1, dtype=torch.int32, device="cuda")
+    w = torch.zeros((N, k), dtype=torch.float32, device="cuda")
+    ws = torch.empty(4 << 20, dtype=torch.uint8, device="cuda")
+    up = lambda a: layer_mod.to_device(W.Bf16Tensor.from_f32(np.ascontiguousarray(a)))
+    binding.flexmoe_gate_topk(up(x), up(wg), k, idx, w, ws)
+    assert np.array_equal(idx.cpu().numpy(), want[of])
+    ex = np.exp(np.take_along_axis(logits, want, 1).astype(np.float64) - logits.max(1, keepdims=True))
+    np.testing.assert_allclose(w.cpu().numpy(), (ex / ex.sum(1, keepdims=True))[of], rtol=1e-5, atol=1e-7)
