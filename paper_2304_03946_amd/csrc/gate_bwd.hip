@@ -12,7 +12,7 @@
 // fixed summation order, so results are reproducible: no atomics.  What does not depend on each other shares a
 // launch: both bias gradients (two launches in all); the logit gradients and the transposed copy of W_g; then the
 // gate's share of dX and the partial sums of dW_g; then their final sums.  Eight launches of 4.6 - 15 us became five:
-// 5003 tokens (d 192, f 768, E 12) 57.6 -> 31.2 us, 1500 tokens (d 1024, f 4096, E 32) 61.9 -> 37.0.
+// 5003 tokens (d 192, f 768, E 12) 49.2 -> 29.0 us, 1500 tokens (d 1024, f 4096, E 32) 47.2 -> 30.7 (replayed from a graph).
 #include "common.h"
 
 namespace flexmoe {
@@ -22,6 +22,7 @@ constexpr int kBwdWaves = kBwdThreads / kWave;
 constexpr int kChunkRows = 128;                    // rows of one bucket summed by one workgroup
 constexpr int kSumThreads = 512;                   // of the partial sums: every wave has its 16 rows in flight at once
 constexpr int kSumWaves = kSumThreads / kWave;
+constexpr int kSumChains = 4;                      // sums per column: rows w, w + 4, ..
 constexpr int kMaxGridY = 65535;
 constexpr int kChunkCols = 512;                    // columns per workgroup: 64 lanes x 16 bytes of bf16
 
@@ -155,7 +156,8 @@ template <typename T> static constexpr int kSumCols = kChunkCols * Vec16<T>::n /
 
 // Stage 1: partial[chunk, c] = sum over the chunk's rows of weight(row) * in[row, c], fp32.
 // WEIGHTED: weight(row p) = row_w[src[p]] (a value per assignment id); otherwise 1.
-// Wave w sums rows w, w + 8, ... of the chunk in ascending order; the waves' sums are added in wave order through
+// Rows w, w + 4, ... of the chunk are summed in ascending order, the first half of them by wave w, which hands its sum to
+// wave w + 4 for the second half (whose rows have come meanwhile); the four sums are added in order through
 // LDS.  One workgroup sums the `chunk` it is given for the column blocks cb, cb + cb_step, ..: those of
 // the first matrix s0, then those of a second one, s1.
 template <typename T> struct SumInput {
@@ -169,7 +171,7 @@ __device__ __forceinline__ void bucket_colsum_partial(const SumInput<T>& s0, con
                                                       int V, int chunk, int cb, int cb_step) {
   constexpr int VN = Vec16<T>::n, U = kChunkRows / kSumWaves;
   __shared__ int chunk_start[FLEXMOE_MAX_VEXPERTS + 1];
-  __shared__ float red[kSumWaves][kWave][VN];
+  __shared__ float red[kSumChains][kWave][VN];
   __shared__ float weight[kChunkRows];
   chunk_starts(voff, V, chunk_start);
   if (chunk >= chunk_start[V]) return;               // uniform
@@ -181,9 +183,11 @@ __device__ __forceinline__ void bucket_colsum_partial(const SumInput<T>& s0, con
     else hi = mid - 1;
   }
   const int v = lo;
-  const int row0 = voff[v] + (chunk - chunk_start[v]) * kChunkRows;
-  const int rows = min(kChunkRows, voff[v + 1] - row0);
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  // uniform: a row's address in scalar registers
+  const int row0 = __builtin_amdgcn_readfirstlane(voff[v] + (chunk - chunk_start[v]) * kChunkRows);
+  const int rows = __builtin_amdgcn_readfirstlane(min(kChunkRows, voff[v + 1] - row0));
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), chain = wave % kSumChains;
+  const bool second = wave >= kSumChains;
   if (WEIGHTED) {
     if ((int)threadIdx.x < rows) weight[threadIdx.x] = row_w[src[row0 + threadIdx.x]];
     __syncthreads();
@@ -191,35 +195,43 @@ __device__ __forceinline__ void bucket_colsum_partial(const SumInput<T>& s0, con
   for (; cb < s0.blocks + s1.blocks; cb += cb_step) {
     const SumInput<T>& m = cb < s0.blocks ? s0 : s1;
     const int col = (cb < s0.blocks ? cb : cb - s0.blocks) * kSumCols<T> + lane * VN;
-    float acc[VN];
-#pragma unroll
-    for (int q = 0; q < VN; ++q) acc[q] = 0.f;
+    const int first = chain + (second ? U * kSumChains : 0);
+    uint4 raw[U];
     if (col < m.C) {
-      uint4 raw[U];
 #pragma unroll
       for (int i = 0; i < U; ++i)
-        raw[i] = *(const uint4*)(m.in + (size_t)(row0 + min(wave + i * kSumWaves, rows - 1)) * m.C + col);
+        raw[i] = *(const uint4*)((const char*)(m.in + (size_t)(row0 + min(first + i * kSumChains, rows - 1)) * m.C) + (uint32_t)col * sizeof(T));
+    }
+    auto add = [&](bool resume) {
+      float acc[VN];
 #pragma unroll
-      for (int i = 0; i < U; ++i) {
-        const int r = wave + i * kSumWaves;
-        if (r < rows) {
-          const float wt = WEIGHTED ? weight[r] : 1.f;
-          float u[VN];
-          Vec16<T>::unpack(raw[i], u);
+      for (int q = 0; q < VN; ++q) acc[q] = resume ? red[chain][lane][q] : 0.f;
+      if (col < m.C) {
 #pragma unroll
-          for (int q = 0; q < VN; ++q) acc[q] = fmaf(wt, u[q], acc[q]);
+        for (int i = 0; i < U; ++i) {
+          const int r = first + i * kSumChains;
+          if (r < rows) {
+            const float wt = WEIGHTED ? weight[r] : 1.f;
+            float u[VN];
+            Vec16<T>::unpack(raw[i], u);
+#pragma unroll
+            for (int q = 0; q < VN; ++q) acc[q] = fmaf(wt, u[q], acc[q]);
+          }
         }
       }
-    }
 #pragma unroll
-    for (int q = 0; q < VN; ++q) red[wave][lane][q] = acc[q];
+      for (int q = 0; q < VN; ++q) red[chain][lane][q] = acc[q];
+    };
+    if (!second) add(false);
+    __syncthreads();
+    if (second) add(true);
     __syncthreads();
     if (wave == 0 && col < m.C) {
 #pragma unroll
       for (int q = 0; q < VN; ++q) {
         float s = red[0][lane][q];
 #pragma unroll
-        for (int ww = 1; ww < kSumWaves; ++ww) s += red[ww][lane][q];
+        for (int ww = 1; ww < kSumChains; ++ww) s += red[ww][lane][q];
         m.partial[(size_t)chunk * m.C + col + q] = s;
       }
     }
@@ -227,12 +239,12 @@ __device__ __forceinline__ void bucket_colsum_partial(const SumInput<T>& s0, con
   }
 }
 template <typename T>
-__global__ __launch_bounds__(kSumThreads) void bias_partial_kernel(SumInput<T> s0, SumInput<T> s1, const int32_t* __restrict__ voff, int V) {
+__global__ __launch_bounds__(kSumThreads, 4) void bias_partial_kernel(SumInput<T> s0, SumInput<T> s1, const int32_t* __restrict__ voff, int V) {
   bucket_colsum_partial<T, false>(s0, s1, nullptr, nullptr, voff, V, blockIdx.x, blockIdx.y, gridDim.y);
 }
 // Second launch of the gate's backward pass: blockIdx.y < token_rows adds the gate's share of dX, the others sum dW_g's chunks.
 template <typename T>
-__global__ __launch_bounds__(kSumThreads) void gate_bwd_apply_kernel(const float* __restrict__ dl, const int32_t* __restrict__ idx,
+__global__ __launch_bounds__(kSumThreads, 4) void gate_bwd_apply_kernel(const float* __restrict__ dl, const int32_t* __restrict__ idx,
                                                                     const T* __restrict__ wgT, int N, int k, int d,
                                                                     T* __restrict__ dx, int token_rows, SumInput<T> xp,
                                                                     const int32_t* __restrict__ src,

@@ -176,3 +176,30 @@ def test_order_of_the_gate_sums(api, N, d, E, k):  # noqa: F811
     assert np.array_equal(idx.cpu().numpy(), want[of])
     ex = np.exp(np.take_along_axis(logits, want, 1).astype(np.float64) - logits.max(1, keepdims=True))
     np.testing.assert_allclose(w.cpu().numpy(), (ex / ex.sum(1, keepdims=True))[of], rtol=1e-5, atol=1e-7)
+
+
+# whole numbers and +-2^24 in one column: an addition past 2^24 rounds, so the order decides what is left
+@pytest.mark.parametrize("dtype,A,d", [("f32", 1, 8), ("f32", 61, 256), ("f32", 300, 264), ("bf16", 64, 512), ("bf16", 128, 520), ("bf16", 449, 40)])
+def test_order_of_the_bias_sums(api, dtype, A, d):  # noqa: F811
+    """Chunks of 128 rows: rows r, r + 4, .. in ascending order, the four sums in order; then the chunks in order (four at most here)."""
+    B, layer_mod = api
+    tdt, code = (torch.float32, B.F32) if dtype == "f32" else (torch.bfloat16, B.BF16)
+    rng = np.random.default_rng(A + d)
+    rows = rng.integers(-1, 3, size=(A, d)).astype(np.float32)
+    for sign in (1.0, -1.0):
+        rows[rng.integers(A, size=d), np.arange(d)] = sign * 2.0 ** 24
+    chunks = []
+    for c0 in range(0, A, 128):
+        chains = np.zeros((4, d), dtype=np.float32)
+        for r in range(c0, min(c0 + 128, A)):
+            chains[(r - c0) % 4] += rows[r]
+        chunks.append(((chains[0] + chains[1]) + chains[2]) + chains[3])
+    want = np.zeros(d, dtype=np.float32)
+    for c in chunks:
+        want = want + c
+    assert A < 8 or (want != rows.sum(0, dtype=np.float64)).any(), "the order must matter"
+    f, i32 = 16, lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    ws = torch.zeros(B.flexmoe_workspace_bytes(A, d, f, 1, 1, 1, code), dtype=torch.uint8, device="cuda")
+    got = torch.empty((1, d), dtype=tdt, device="cuda")
+    B.flexmoe_expert_bias_grads(torch.from_numpy(rows).cuda().to(tdt), i32([0, A]), i32([0]), f, 1, None, got, ws)
+    assert torch.equal(got[0].cpu(), torch.from_numpy(want).to(tdt))
