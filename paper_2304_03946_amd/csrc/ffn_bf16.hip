@@ -197,9 +197,11 @@ static hipError_t launch_small(const FfnArgs& a, const void* in, const void* w, 
                                int gk, const int32_t* scatter_rows) {
   float* partial;
   const SmallPlan pl = small_plan_ws(a, ws, &partial);
-  const int lut = EPI == EPI_PLAIN || a.act == FLEXMOE_RELU ? -1 : a.act == FLEXMOE_GELU_ERF ? 0 : 1;
+  // The table as in the 256 x 256 kernels: where the contraction is whole 128-wide rounds.  Otherwise the activation is
+  // evaluated: the table has 2^-24 for every smaller magnitude, zero included, and a negative NaN is lost in it.
+  const int lut = EPI == EPI_PLAIN || a.act == FLEXMOE_RELU || K % 128 ? -1 : a.act == FLEXMOE_GELU_ERF ? 0 : 1;
   const SmallArgs p{(const bf16_t*)in, (const bf16_t*)w, (const bf16_t*)bias, pl.tab, pl.rowmap, K, NC, (NC + SN - 1) / SN,
-                    (const bf16_t*)hpre_in, (bf16_t*)out0, (bf16_t*)out1, gsrc, gk, scatter_rows, lut, partial, pl.counters};
+                    (const bf16_t*)hpre_in, (bf16_t*)out0, (bf16_t*)out1, gsrc, gk, scatter_rows, a.act, lut, partial, pl.counters};
   // two workgroups per compute unit walk the tiles
   const long long most = (long long)(a.A / pl.bm + a.E) * p.col_tiles;
   const unsigned grid = (unsigned)std::min<long long>(kSmallSplitTarget, std::max<long long>(most * kSmallSplitMax, 1));

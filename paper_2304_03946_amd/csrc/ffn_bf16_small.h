@@ -53,7 +53,7 @@ struct SmallArgs {
   const int32_t* gsrc;           // gathered rows of `in`: row gsrc[bucket row] / gk; or null
   int gk;
   const int32_t* scatter_rows;   // bucket row p is stored as row scatter_rows[p] of out0; or null
-  int lut;                       // which of g_act_lut's tables, -1: ReLU
+  int act, lut;                  // activation; which of g_act_lut's tables it is read from, -1: none (evaluated)
   float* partial;                // kSmallSlots partial tiles
   int* counters;                 // one per tile that is cut into segments, zeroed by the plan
 };
@@ -161,6 +161,12 @@ __device__ __forceinline__ void small_load(const bf16_t* base, uint32_t off, uns
 }
 __device__ __forceinline__ void small_load_at(const bf16_t* p, unsigned lds) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p), "s"(lds) : "memory");
+}
+// Activation and derivative without a table.
+__device__ __forceinline__ void small_act(int act, float z, float* a, float* da) {
+  if (act == FLEXMOE_RELU) act_both<FLEXMOE_RELU>(z, a, da);
+  else if (act == FLEXMOE_GELU_ERF) act_both<FLEXMOE_GELU_ERF>(z, a, da);
+  else act_both<FLEXMOE_GELU_TANH>(z, a, da);
 }
 template <int L> __device__ __forceinline__ void small_wait(int tiles) {
   switch (tiles) {
@@ -393,7 +399,9 @@ __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const S
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
                 const uint32_t zu = __float_as_uint(z[q]);
-                a[q] = use_lut ? lut_act(sm, zu) : act_fast<FLEXMOE_RELU>(z[q]);
+                float da;
+                if (use_lut) a[q] = lut_act(sm, zu);
+                else small_act(p.act, z[q], &a[q], &da);
               }
               if (p.out0) *(uint2*)(p.out0 + o) = pre;
               *(uint2*)(p.out1 + o) = pack4(a[0], a[1], a[2], a[3]);
@@ -406,7 +414,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const S
                 if (use_lut) {
                   lut_act_both(sm, zu, &a[q], &dv[q]);
                 } else {
-                  act_both<FLEXMOE_RELU>(z[q], &a[q], &dv[q]);
+                  small_act(p.act, z[q], &a[q], &dv[q]);
                 }
               }
               *(uint2*)(p.out0 + o) = pack4(c[0] * dv[0], c[1] * dv[1], c[2] * dv[2], c[3] * dv[3]);

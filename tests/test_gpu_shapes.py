@@ -203,3 +203,23 @@ def test_order_of_the_bias_sums(api, dtype, A, d):  # noqa: F811
     got = torch.empty((1, d), dtype=tdt, device="cuda")
     B.flexmoe_expert_bias_grads(torch.from_numpy(rows).cuda().to(tdt), i32([0, A]), i32([0]), f, 1, None, got, ws)
     assert torch.equal(got[0].cpu(), torch.from_numpy(want).to(tdt))
+
+
+# contractions that are no whole 128-wide rounds evaluate the activation instead of reading it from a table, in the kernels for
+# few rows and in the 256 x 256 ones past their line
+@pytest.mark.parametrize("act", [W.ACT_GELU_ERF, W.ACT_GELU_TANH, W.ACT_RELU])
+@pytest.mark.parametrize("A,d,f", [(3, 136, 264), (200, 40, 264), (15000, 136, 1032)])
+def test_activation_of_zero_and_nan(api, act, A, d, f):  # noqa: F811
+    B, layer_mod = api
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    w1, w2, x = torch.ones((1, d, f), **bf), torch.ones((1, f, d), **bf), torch.zeros((A, d), **bf)
+    hpre, h, yp = torch.empty((A, f), **bf), torch.empty((A, f), **bf), torch.empty((A, d), **bf)
+    ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, 1, 1, 1, B.BF16), dtype=torch.uint8, device="cuda")
+    B.flexmoe_expert_ffn_fwd(x, i32([0, A]), i32([0]), w1, None, w2, None, act, hpre, yp, ws, h=h)
+    assert not hpre.any() and not h.any() and not yp.any(), "act(0) is 0"
+    if act != W.ACT_RELU:
+        b1 = torch.zeros((1, f), **bf)
+        b1.view(torch.int16)[0, 5] = -64                  # 0xffc0: a NaN with its sign set
+        B.flexmoe_expert_ffn_fwd(x, i32([0, A]), i32([0]), w1, b1, w2, None, act, hpre, yp, ws, h=h)
+        assert hpre.isnan().sum() == A and torch.equal(h.isnan(), hpre.isnan()) and bool(yp.isnan().all())
