@@ -58,7 +58,8 @@ enum flexmoe_act { FLEXMOE_RELU = 0, FLEXMOE_GELU_ERF = 1, FLEXMOE_GELU_TANH = 2
 /* Human-readable name of a status code (static storage). */
 const char* flexmoe_status_str(int status);
 
-/* Bytes of scratch that any entry point may need for the given problem (max over all). */
+/* Bytes of scratch that any entry point may need for the given problem (max over all).  Never falls where N alone grows: a
+   workspace for the largest batch serves every smaller one of the same layer. */
 size_t flexmoe_workspace_bytes(int N, int d, int f, int E, int k, int V, int dtype);
 
 /*

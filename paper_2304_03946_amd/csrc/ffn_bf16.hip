@@ -99,11 +99,29 @@ static size_t rows_split_bytes(int A, int V, int K, int NC) {
   return (size_t)kSplitMaxSlots * BM * BN * sizeof(float);
 }
 
-// Job table + fp32 partial tiles of one segmented weight-gradient product (0 when not segmented).
+// The workspace must not shrink where the number of rows grows (a caller sizes it for the largest batch and passes it to
+// every smaller one), but the slots do: longer segments leave fewer.  So what is reserved for A rows is the most that any
+// number of rows up to A takes, from the last number of K tiles k of each rule: segments of 16 (share <= 8, at most four
+// output tiles), of 32 (share <= 32), and of a share s > 32, where (k + V) / s < (34 c + V) / 33, c = 256 / output tiles,
+// because k < (s + 1) c.  More than 65 output tiles are never cut.
+static int wgrad_slots_reserved(int A, int d, int f, int V) {
+  const long long out_tiles = (long long)((d + BM - 1) / BM) * ((f + BN - 1) / BN);
+  const int k_tiles = A / DK;
+  if (out_tiles > kComputeUnits / 4 + 1) return 0;
+  const int out = (int)out_tiles, k16 = (9 * kComputeUnits - 1) / out, k32 = (33 * kComputeUnits - 1) / out;
+  int extra = -1;                                         // segments beyond one per expert; slots = 2 extra + 1
+  if (out <= 4 && k_tiles >= 4 * 16) extra = (std::min(k_tiles, k16) + V) / 16;
+  if (std::min(k_tiles, k32) >= 4 * 32) extra = std::max(extra, (std::min(k_tiles, k32) + V) / 32);
+  if (k_tiles > k32) extra = std::max(extra, (34 * kComputeUnits + V * out - 1) / (33 * out));
+  return 2 * extra + (extra >= 0 ? 1 : 2);
+}
+// fp32 partial tiles of one weight-gradient product.
 static size_t wgrad_tail_bytes(int A, int d, int f, int V) {
-  const int seg_tiles = wgrad_seg_tiles(A, d, f);
-  if (!seg_tiles) return 0;
-  return align_up((size_t)wgrad_partial_slots(A, V, seg_tiles) * d * f * sizeof(float), 256);
+  return align_up((size_t)wgrad_slots_reserved(A, d, f, V) * d * f * sizeof(float), 256);
+}
+// Work list of both.
+static size_t wgrad_plan_reserved(int A, int d, int f, int E, int V) {
+  return align_up(wgrad_plan_bytes(E + wgrad_slots_reserved(A, d, f, V) / 2, E, V), 256);
 }
 
 // Which rows kernels a call of these sizes takes: 32 or 64 = rows_gemm_small_bf16 with row tiles of that many rows,
@@ -124,10 +142,13 @@ static size_t wgrad_tail_bytes(int A, int d, int f, int V) {
 //   d 1024: 2400 of 12 389, 339; 3200 of 4 384, 327;                  past: 4800 of 12 536, 550; 6400 of 4 554, 604
 constexpr int kSmall32Rows = 4, kSmall64Rows = 160;
 constexpr long long kSmallOutputs = 224ll * BM * BN;
+// The largest number of rows that takes them (every smaller one does, too):
+static int small_rows_most(int d, int f, int E) {
+  const long long wide = std::max(d, f);
+  return (int)std::min(std::max((long long)kSmall64Rows * E, kSmallOutputs / wide), ((1ll << 30) - 1) / wide);      // 32-bit byte offsets of the row loads
+}
 static int small_rows(int A, int d, int f, int E) {
-  if ((long long)A * std::max(d, f) >= 1ll << 30) return 0;      // 32-bit byte offsets of the row loads
-  if (A <= kSmall32Rows * E) return 32;
-  return A <= kSmall64Rows * E || (long long)A * std::max(d, f) <= kSmallOutputs ? 64 : 0;
+  return A > small_rows_most(d, f, E) ? 0 : A <= kSmall32Rows * E ? 32 : 64;
 }
 // Partial tiles that a product with contraction K and NC columns can leave at most (see small_segments): none for short
 // contractions.
@@ -135,39 +156,46 @@ static long long small_slots(int A, int E, int bm, int K, int NC) {
   const int most = small_segments(1, (K + SK - 1) / SK);
   return most == 1 ? 0 : std::min<long long>(kSmallSlots, (long long)(A / bm + E) * ((NC + SN - 1) / SN) * most);
 }
+// Their workspace: row tiles (room for tiles of 32 rows, so that the size does not fall at the line to 64), row list,
+// counters, partial tiles.
+static size_t small_tab_bytes(int A, int E) { return align_up((size_t)(A / 32 + E + 1) * sizeof(i32x4), 256); }
 static size_t small_ws_bytes(int A, int d, int f, int E) {
   const int bm = small_rows(A, d, f, E);
   if (!bm) return 0;
-  return align_up((size_t)(A / bm + E + 1) * sizeof(i32x4), 256) + align_up((size_t)A * sizeof(int32_t), 256) +
-         align_up(kSmallSlots * sizeof(int), 256) +
+  return small_tab_bytes(A, E) + align_up((size_t)A * sizeof(int32_t), 256) + align_up(kSmallSlots * sizeof(int), 256) +
          (size_t)std::max(small_slots(A, E, bm, d, f), small_slots(A, E, bm, f, d)) * bm * SN * sizeof(float);
 }
+// What the rows products of a call take: either the partial tiles of a split last round and the table of 256-row tiles, or the
+// above.  Past the small kernels' line still what they take at the line: the size never falls where A grows.
+static size_t rows_ws_bytes(int A, int d, int f, int E, int V) {
+  const size_t small = small_ws_bytes(std::min(A, small_rows_most(d, f, E)), d, f, E);
+  if (small_rows(A, d, f, E)) return small;
+  return std::max(small, rows_split_bytes(A, V, f, d) + align_up(rows_tab_bytes(max_row_tiles(A, V)), 256));      // (GEMM2 and dXp are split)
+}
 
+// The workspace, in this order: dHpre (or H in a forward pass); H; the partial tiles of dW2, then of dW1; the weight
+// gradients' work lists; what the rows products take.
 size_t ffn_ws_bytes(int A, int d, int f, int E, int V, int dtype) {
   const size_t s = dtype == FLEXMOE_BF16 ? 2 : 4;
-  size_t need = align_up((size_t)A * f * s, 256) * 2;      // dHpre (or H in forward) + H
-  if (dtype == FLEXMOE_BF16) {
-    need += 2 * wgrad_tail_bytes(A, d, f, V);      // one region per weight gradient
-    need += rows_split_bytes(A, V, f, d);          // GEMM2 / dXp: partial tiles of the split last round
-    need += align_up(wgrad_plan_bytes(wgrad_seg_rows_max(A, d, f, E, V), E, V), 256);   // work list of the weight gradients
-    need += align_up(rows_tab_bytes(max_row_tiles(A, V)), 256);                         // row tiles of the bucket list
-    need += small_ws_bytes(A, d, f, E);            // plan and partial tiles of the small rows kernels
-  }
+  size_t need = align_up((size_t)A * f * s, 256) * 2;
+  if (dtype == FLEXMOE_BF16)
+    need += 2 * wgrad_tail_bytes(A, d, f, V) + wgrad_plan_reserved(A, d, f, E, V) + rows_ws_bytes(A, d, f, E, V);
   return need;
 }
-static i32x4* rows_tab_ws(const FfnArgs& a, void* ws) {
-  return (i32x4*)((char*)ws + 2 * align_up((size_t)a.A * a.f * sizeof(bf16_t), 256) + 2 * wgrad_tail_bytes(a.A, a.d, a.f, a.V) +
-                  rows_split_bytes(a.A, a.V, a.f, a.d) +
-                  align_up(wgrad_plan_bytes(wgrad_seg_rows_max(a.A, a.d, a.f, a.E, a.V), a.E, a.V), 256));
+static void* wgrad_plan_ws(const FfnArgs& a, void* ws) {
+  return (char*)ws + 2 * align_up((size_t)a.A * a.f * sizeof(bf16_t), 256) + 2 * wgrad_tail_bytes(a.A, a.d, a.f, a.V);
 }
-// The small rows kernels' share of the workspace, behind the row-tile table.
+static void* rows_ws(const FfnArgs& a, void* ws) { return (char*)wgrad_plan_ws(a, ws) + wgrad_plan_reserved(a.A, a.d, a.f, a.E, a.V); }
+// of the 256 x 256 kernels: partial tiles of the split last round, row-tile table
+static void* rows_split_ws(const FfnArgs& a, void* ws) { return rows_ws(a, ws); }
+static i32x4* rows_tab_ws(const FfnArgs& a, void* ws) { return (i32x4*)((char*)rows_ws(a, ws) + rows_split_bytes(a.A, a.V, a.f, a.d)); }
+// of the small ones
 static SmallPlan small_plan_ws(const FfnArgs& a, void* ws, float** partial = nullptr) {
   SmallPlan pl;
-  pl.A = a.A;
   pl.bm = small_rows(a.A, a.d, a.f, a.E);
-  char* at = (char*)rows_tab_ws(a, ws) + align_up(rows_tab_bytes(max_row_tiles(a.A, a.V)), 256);
+  char* at = (char*)rows_ws(a, ws);
   pl.tab = (i32x4*)at;
-  if (pl.bm) at += align_up((size_t)(a.A / pl.bm + a.E + 1) * sizeof(i32x4), 256);
+  at += small_tab_bytes(a.A, a.E);
   pl.rowmap = (int32_t*)at;
   at += align_up((size_t)a.A * sizeof(int32_t), 256);
   pl.counters = (int*)at;
@@ -208,14 +236,6 @@ static hipError_t launch_small(const FfnArgs& a, const void* in, const void* w, 
   if (pl.bm == 32) launch_small_t<32, WT, EPI>(p, grid, s);
   else launch_small_t<64, WT, EPI>(p, grid, s);
   return hipGetLastError();
-}
-
-static void* wgrad_plan_ws(const FfnArgs& a, void* ws) {
-  return (char*)ws + 2 * align_up((size_t)a.A * a.f * sizeof(bf16_t), 256) + 2 * wgrad_tail_bytes(a.A, a.d, a.f, a.V) +
-         rows_split_bytes(a.A, a.V, a.f, a.d);
-}
-static void* rows_split_ws(const FfnArgs& a, void* ws) {
-  return (char*)ws + 2 * align_up((size_t)a.A * a.f * sizeof(bf16_t), 256) + 2 * wgrad_tail_bytes(a.A, a.d, a.f, a.V);
 }
 
 static RowsDmaArgs rows_dma_args(const FfnArgs& a, const void* in, const void* w, const void* bias, int K, int NC,

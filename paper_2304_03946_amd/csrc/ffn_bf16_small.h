@@ -72,7 +72,7 @@ struct SmallPlan {
   i32x4* tab;
   int32_t* rowmap;
   int* counters;
-  int A, bm;                     // bm = 0: the product does not use these kernels
+  int bm;                        // 0: the product does not use these kernels
 };
 __device__ __forceinline__ void small_plan_block(const int32_t* __restrict__ voff, const int32_t* __restrict__ owner, int E, int V,
                                                  const SmallPlan& plan, int block, int nblocks) {

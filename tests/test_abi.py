@@ -56,6 +56,25 @@ def test_status_strings_and_workspace_size():
     assert binding.flexmoe_workspace_bytes(16, 64, 64, 4, 5, 4, binding.BF16) == 0      # k > E
 
 
+def test_workspace_size_never_falls_with_the_number_of_tokens():
+    """A workspace sized for the largest batch serves every smaller one.  Layers on both sides of every line that the kernels'
+    dispatch draws: 1 to 70 weight-gradient tiles per expert, contractions split or not, one expert and the most."""
+    import random
+    binding, lib = _lib()
+    rng = random.Random(5)
+    layers = [(192, 768, 12, 2, 15), (256, 1024, 40, 2, 48), (768, 3072, 16, 2, 18), (2048, 8192, 64, 2, 96), (1024, 4096, 32, 2, 48),
+              (512, 2048, 32, 1, 40), (512, 1024, 128, 4, 160), (8, 8, 1, 1, 1), (128, 256, 256, 8, 512), (2048, 2048, 4, 1, 6),
+              (2056, 2048, 4, 1, 6), (1280, 3328, 2, 2, 300)]
+    for d, f, E, k, V in layers:
+        for dtype in (binding.BF16, binding.F32):
+            sizes = sorted(set(range(1, 9000)) | set(range(9000, 80000, 7)) | {rng.randrange(80000, (1 << 30) // k) for _ in range(2000)})
+            last = 0
+            for N in sizes:
+                size = lib.flexmoe_workspace_bytes(N, d, f, E, k, V, dtype)
+                assert size >= last, (N, d, f, E, k, V, dtype, last - size)
+                last = size
+
+
 def test_product_path_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2304_03946_amd")
     for fn in os.listdir(pkg):
