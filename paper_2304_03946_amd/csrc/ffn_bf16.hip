@@ -145,6 +145,7 @@ constexpr long long kSmallOutputs = 224ll * BM * BN;
 // The largest number of rows that takes them (every smaller one does, too):
 static int small_rows_most(int d, int f, int E) {
   const long long wide = std::max(d, f);
+  if (wide >= 1 << 24) return 0;                          // 32-bit byte offsets of the weight loads: 128 rows of that many columns
   return (int)std::min(std::max((long long)kSmall64Rows * E, kSmallOutputs / wide), ((1ll << 30) - 1) / wide);      // 32-bit byte offsets of the row loads
 }
 static int small_rows(int A, int d, int f, int E) {

@@ -223,3 +223,20 @@ def test_activation_of_zero_and_nan(api, act, A, d, f):  # noqa: F811
         b1.view(torch.int16)[0, 5] = -64                  # 0xffc0: a NaN with its sign set
         B.flexmoe_expert_ffn_fwd(x, i32([0, A]), i32([0]), w1, b1, w2, None, act, hpre, yp, ws, h=h)
         assert hpre.isnan().sum() == A and torch.equal(h.isnan(), hpre.isnan()) and bool(yp.isnan().all())
+
+
+def test_offsets_of_a_very_wide_layer(api):  # noqa: F811
+    """64 contraction rows of 34 million columns: beyond the 32-bit offsets of the few-rows kernels, although the rows are few."""
+    B, layer_mod = api
+    A, d, f = 2, 64, 34_089_000
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.empty((A, d), **bf).random_(-1, 2, generator=g)
+    w1, w2 = torch.empty((1, d, f), **bf).random_(-2, 3, generator=g), torch.zeros((1, f, d), **bf)
+    hpre, yp = torch.empty((A, f), **bf), torch.empty((A, d), **bf)
+    ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, 1, 1, 1, B.BF16), dtype=torch.uint8, device="cuda")
+    B.flexmoe_expert_ffn_fwd(x, i32([0, A]), i32([0]), w1, None, w2, None, B.RELU, hpre, yp, ws)
+    for c in range(0, f, 1 << 22):
+        assert torch.equal(hpre[:, c:c + (1 << 22)].float(), x.float() @ w1[0, :, c:c + (1 << 22)].float()), c
+    assert not yp.any()
