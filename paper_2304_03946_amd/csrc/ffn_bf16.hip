@@ -191,9 +191,11 @@ static void* rows_ws(const FfnArgs& a, void* ws) { return (char*)wgrad_plan_ws(a
 static void* rows_split_ws(const FfnArgs& a, void* ws) { return rows_ws(a, ws); }
 static i32x4* rows_tab_ws(const FfnArgs& a, void* ws) { return (i32x4*)((char*)rows_ws(a, ws) + rows_split_bytes(a.A, a.V, a.f, a.d)); }
 // of the small ones
+static int small_plan_parts(const FfnArgs& a) { return std::max(1, std::min(a.A / (a.V * 512), 2048 / a.V)); }      // waves per bucket, up to 512 workgroups
 static SmallPlan small_plan_ws(const FfnArgs& a, void* ws, float** partial = nullptr) {
   SmallPlan pl;
   pl.bm = small_rows(a.A, a.d, a.f, a.E);
+  pl.parts = small_plan_parts(a);
   char* at = (char*)rows_ws(a, ws);
   pl.tab = (i32x4*)at;
   at += small_tab_bytes(a.A, a.E);
@@ -205,7 +207,7 @@ static SmallPlan small_plan_ws(const FfnArgs& a, void* ws, float** partial = nul
   return pl;
 }
 static int plan_blocks(const FfnArgs& a) {
-  if (small_rows(a.A, a.d, a.f, a.E)) return 1 + (a.V + 3) / 4;      // the first: row tiles; the others: a wave per bucket
+  if (small_rows(a.A, a.d, a.f, a.E)) return 1 + (a.V * small_plan_parts(a) + 3) / 4;      // the first: row tiles; the others: the row list
   return std::max(1, std::min(64, (max_row_tiles(a.A, a.V) + kGemmThreads - 1) / kGemmThreads));
 }
 // What the rows kernels of one forward call look up: the row-tile table of the persistent kernels, or the small kernels'

@@ -66,18 +66,22 @@ __host__ __device__ inline int small_segments(int tiles, int k_tiles) {
 }
 
 // ---- plan: expert-major row list and row tiles ----------------------------------------------
-// Every workgroup derives the prefixes; the first writes the row tiles, the others the row list, bucket by bucket (an
-// expert's buckets in ascending vExpert id).
+// Every workgroup derives the prefixes.  The first writes the experts' first row tiles, a thread per expert, and all of them
+// together the further ones; the others write the row list, bucket by bucket (an expert's buckets in ascending vExpert id),
+// plan.parts waves to a bucket.  (With one wave per bucket and one thread per expert the plan was the longest launch where
+// few experts have many rows: whole forward passes, d = f = 8, 1.6 million rows of 4 experts 485 -> 319 us; d 64, f 128, 112000 rows
+// 121 -> 101; d 128, f 512, 22400 rows 64 -> 61.)
 struct SmallPlan {
   i32x4* tab;
   int32_t* rowmap;
   int* counters;
   int bm;                        // 0: the product does not use these kernels
+  int parts;                     // waves that write a bucket's rows
 };
 __device__ __forceinline__ void small_plan_block(const int32_t* __restrict__ voff, const int32_t* __restrict__ owner, int E, int V,
                                                  const SmallPlan& plan, int block, int nblocks) {
   const int bm = plan.bm;
-  __shared__ int rows_e[FLEXMOE_MAX_EXPERTS], start_e[FLEXMOE_MAX_EXPERTS], wsum[2][kGemmThreads / kWave];
+  __shared__ int rows_e[FLEXMOE_MAX_EXPERTS], start_e[FLEXMOE_MAX_EXPERTS], tile_e[FLEXMOE_MAX_EXPERTS], wsum[2][kGemmThreads / kWave];
   __shared__ int2 bucket[FLEXMOE_MAX_VEXPERTS];          // {expert, rows}
   __shared__ int pos0[FLEXMOE_MAX_VEXPERTS], off[FLEXMOE_MAX_VEXPERTS];
   static_assert(kGemmThreads == FLEXMOE_MAX_EXPERTS && 2 * kGemmThreads == FLEXMOE_MAX_VEXPERTS, "a thread per expert, two buckets per thread");
@@ -122,14 +126,26 @@ __device__ __forceinline__ void small_plan_block(const int32_t* __restrict__ vof
     row0 += wsum[0][w];
     tile0 += wsum[1][w];
   }
+  constexpr int kFirst = 4;                              // row tiles of an expert that its thread writes
   if (block == 0) {
-    for (int i = 0; i < n; ++i) plan.tab[1 + tile0 + i] = i32x4{row0 + i * bm, min(bm, r - i * bm), t, 0};
+    for (int i = 0; i < min(n, kFirst); ++i) plan.tab[1 + tile0 + i] = i32x4{row0 + i * bm, min(bm, r - i * bm), t, 0};
     if (t == kGemmThreads - 1) plan.tab[0] = i32x4{tile0 + n, 0, 0, 0};
     for (int i = t; i < kSmallSlots; i += kGemmThreads) plan.counters[i] = 0;
-    return;
   }
   start_e[t] = row0;
-  __syncthreads();
+  tile_e[t] = tile0;
+  if (__syncthreads_or(n > kFirst)) {
+    const int total = tile_e[kGemmThreads - 1] + (rows_e[kGemmThreads - 1] + bm - 1) / bm;
+    for (int rt = block * kGemmThreads + t; rt < total; rt += nblocks * kGemmThreads) {
+      int e = 0;                                         // the last expert with tile_e <= rt (one without tiles shares its successor's value)
+#pragma unroll
+      for (int step = kGemmThreads / 2; step; step >>= 1)
+        if (tile_e[e + step] <= rt) e += step;
+      const int i = rt - tile_e[e];
+      if (i >= kFirst) plan.tab[1 + rt] = i32x4{start_e[e] + i * bm, min(bm, rows_e[e] - i * bm), e, 0};
+    }
+  }
+  if (block == 0) return;
   {
     int before[2] = {0, 0};      // rows of the same expert in earlier buckets
 #pragma unroll 8
@@ -144,10 +160,10 @@ __device__ __forceinline__ void small_plan_block(const int32_t* __restrict__ vof
       if (own[h] >= 0) pos0[t + h * kGemmThreads] = start_e[own[h]] + before[h];
   }
   __syncthreads();
-  constexpr int kWaves = kGemmThreads / kWave;           // a wave per bucket
-  for (int v = (block - 1) * kWaves + wave; v < V; v += (nblocks - 1) * kWaves) {
-    const int lo = off[v], len = bucket[v].y, to = pos0[v];
-    for (int i = lane; i < len; i += kWave) plan.rowmap[to + i] = lo + i;
+  constexpr int kWaves = kGemmThreads / kWave;
+  for (int w = (block - 1) * kWaves + wave; w < V * plan.parts; w += (nblocks - 1) * kWaves) {
+    const int v = w / plan.parts, lo = off[v], len = bucket[v].y, to = pos0[v];
+    for (int i = w % plan.parts * kWave + lane; i < len; i += plan.parts * kWave) plan.rowmap[to + i] = lo + i;
   }
 }
 __global__ __launch_bounds__(kGemmThreads) void small_plan_kernel(const int32_t* __restrict__ voff,
