@@ -124,32 +124,50 @@ static size_t wgrad_plan_reserved(int A, int d, int f, int E, int V) {
   return align_up(wgrad_plan_bytes(E + wgrad_slots_reserved(A, d, f, V) / 2, E, V), 256);
 }
 
-// Which rows kernels a call of these sizes takes: 32 or 64 = rows_gemm_small_bf16 with row tiles of that many rows,
-// 0 = the 256 x 256 kernels.  First by the mean rows per expert, since the loads are not known here (skewed: a few experts have
-// ten times the mean, most have less).  Measured, both products of a forward pass in us:
-//   1 row per expert  (16 tokens, d 1024, f 4096, E 32, k 2):     32-row tiles 59, 64-row 69, 256-row 162
-//   8 rows            (256 tokens, d 2048, f 8192, E 64, k 2):    610, 562, 1135
-//   62 rows           (2000 tokens, the same layer):              1381, 1078, 1412
-//   94 rows           (1500 tokens, d 1024, f 4096, E 32, k 2):   226, 179, 208
-//   128 rows          (4096 tokens, d 512, f 1024, E 128, k 4):   149, 115, 143
+// Which rows kernels a call of these sizes takes: 32 or 64 = rows_gemm_small_bf16 with row tiles of that many rows, 0 = the
+// 256 x 256 kernels.  The loads are not known here (skewed: a few experts have ten times the mean, most have less).
+//
+// Either pass reads an expert's weights once per row tile: the small one for about A / 64 + E / 2 tiles (half an empty one per
+// expert), the other for at least one per vExpert.  How many times as many tiles the small one can afford falls with the size
+// of a weight matrix, as re-reading it counts more than the matrix cores: 1.4 from 2^23 elements, 1.7 from 2^20, 2.4 below.
+// Forward passes, f = 4 d unless given, in us, 256-row and 64-row tiles by mean rows per expert (loads between even and Zipf 1.5):
+//   d 2048, E 64, V 64: 60 1134, 1123;             past the line: 70 1138, 1239; 100 1280, 1411
+//   d 2048, E 64, V 96: 100 1511, 1425;                           130 1538, 1650
+//   d 2048, E 32, V 40:                                           100 648, 656; 130 647, 786
+//   d 1024, E 64, V 64: 70 355, 324;                              85 345, 338; 100 352, 375
+//   d 1024, E 32, V 48: 100 237, 226; 130 243, 237;               160 247, 250; 200 280, 296
+//   d 1024, E 16, V 64: 380 271, 263
+//   d 1024, E 128, V 160: 100 698, 701;                           130 714, 832
+//   d 512, E 128, V 160: 100 258, 244;                            130 264, 281
+//   d 512, f 1024, E 128, V 128: 120 164, 156;                    140 176, 175
+//   d 512, f 1024, E 128, V 160: 160 195, 181;                    220 216, 223
+//   d 256, E 128, V 128: 120 114, 112;                            150 119, 123
+// Training steps cross a little later (d 2048, E 64, V 96: 100 4314, 3931; 130 4402, 4449; 160 4900, 4941).
+//
 // And 64-row tiles for any number of rows per expert while the wider product does not fill 224 of the 256 x 256 tiles (a
-// tile per compute unit: most of the chip waits for a few long tiles, and for half-empty ones).  Whole training steps,
-// f = 4 d, k 2, in us, 256-row and 64-row tiles:
-//   d 128:  4800 rows of 12 experts 166, 148; 16000 of 40 190, 184;   past the line: 32000 of 40 229, 237
-//   d 192:  9600 of 12 (no whole 128-wide rounds) 223, 175
-//   d 256:  9600 of 12 217, 200; 8000 of 40 225, 207;                 past: 16000 of 40 262, 269; 19200 of 12 262, 275
-//   d 512:  4800 of 12 275, 240; 6400 of 4 289, 266;                  past: 9600 of 12 337, 343; 8000 of 40 379, 391
-//   d 1024: 2400 of 12 389, 339; 3200 of 4 384, 327;                  past: 4800 of 12 536, 550; 6400 of 4 554, 604
-constexpr int kSmall32Rows = 4, kSmall64Rows = 160;
-constexpr long long kSmallOutputs = 224ll * BM * BN;
+// tile per compute unit: most of the chip waits for a few long tiles, and for half-empty ones); fewer where the shorter contraction is
+// below 432, because a small tile's epilogue and first loads weigh more.  4 experts, f = 4 d unless given, forward and training:
+//   d 2048: 1800 rows 323, 252 and 819, 647;             past the line: 2400 328, 342 and 860, 848
+//   d 1024: 3600 177, 139 and 459, 379;                                 4400 183, 176 and 522, 515; 5600 187, 201 and 549, 586
+//   d 512:  7200 98, 94 and 297, 286;                                   8800 113, 117 and 337, 345
+//   d 256:                                                              11200 72, 69 and 206, 197; 16800 83, 87 and 253, 258
+//   d 128:  11200 54, 55 and 161, 158;                                  22400 58, 61 and 177, 178; 28800 59, 66 and 187, 199
+//   d 64, f 256: 24000 62, 57 and 173, 158 (94 tiles);                  44000 68, 72 and 193, 203
+//
+// 32-row tiles up to four rows per expert: both products, 32- and 64-row tiles, 1 row (16 tokens, d 1024, E 32, k 2) 59, 69;
+// 8 rows (256 tokens, d 2048, E 64, k 2) 610, 562.
+constexpr int kSmall32Rows = 4;
 // The largest number of rows that takes them (every smaller one does, too):
-static int small_rows_most(int d, int f, int E) {
-  const long long wide = std::max(d, f);
+static int small_rows_most(int d, int f, int E, int V) {
+  const long long wide = std::max(d, f), few = std::min(d, f);
   if (wide >= 1 << 24) return 0;                          // 32-bit byte offsets of the weight loads: 128 rows of that many columns
-  return (int)std::min(std::max((long long)kSmall64Rows * E, kSmallOutputs / wide), ((1ll << 30) - 1) / wide);      // 32-bit byte offsets of the row loads
+  const long long matrix = (long long)d * f, tenths = matrix >= 1 << 23 ? 14 : matrix >= 1 << 20 ? 17 : 24;
+  const long long by_tiles = tenths * V * 64 / 10 - 32ll * E;
+  const long long by_outputs = std::min(224ll, 64 + 3 * few / 8) * BM * BN / wide;
+  return (int)std::min(std::max(by_tiles, by_outputs), ((1ll << 30) - 1) / wide);      // 32-bit byte offsets of the row loads
 }
-static int small_rows(int A, int d, int f, int E) {
-  return A > small_rows_most(d, f, E) ? 0 : A <= kSmall32Rows * E ? 32 : 64;
+static int small_rows(int A, int d, int f, int E, int V) {
+  return A > small_rows_most(d, f, E, V) ? 0 : A <= kSmall32Rows * E ? 32 : 64;
 }
 // Partial tiles that a product with contraction K and NC columns can leave at most (see small_segments): none for short
 // contractions.
@@ -160,8 +178,8 @@ static long long small_slots(int A, int E, int bm, int K, int NC) {
 // Their workspace: row tiles (room for tiles of 32 rows, so that the size does not fall at the line to 64), row list,
 // counters, partial tiles.
 static size_t small_tab_bytes(int A, int E) { return align_up((size_t)(A / 32 + E + 1) * sizeof(i32x4), 256); }
-static size_t small_ws_bytes(int A, int d, int f, int E) {
-  const int bm = small_rows(A, d, f, E);
+static size_t small_ws_bytes(int A, int d, int f, int E, int V) {
+  const int bm = small_rows(A, d, f, E, V);
   if (!bm) return 0;
   return small_tab_bytes(A, E) + align_up((size_t)A * sizeof(int32_t), 256) + align_up(kSmallSlots * sizeof(int), 256) +
          (size_t)std::max(small_slots(A, E, bm, d, f), small_slots(A, E, bm, f, d)) * bm * SN * sizeof(float);
@@ -169,8 +187,8 @@ static size_t small_ws_bytes(int A, int d, int f, int E) {
 // What the rows products of a call take: either the partial tiles of a split last round and the table of 256-row tiles, or the
 // above.  Past the small kernels' line still what they take at the line: the size never falls where A grows.
 static size_t rows_ws_bytes(int A, int d, int f, int E, int V) {
-  const size_t small = small_ws_bytes(std::min(A, small_rows_most(d, f, E)), d, f, E);
-  if (small_rows(A, d, f, E)) return small;
+  const size_t small = small_ws_bytes(std::min(A, small_rows_most(d, f, E, V)), d, f, E, V);
+  if (small_rows(A, d, f, E, V)) return small;
   return std::max(small, rows_split_bytes(A, V, f, d) + align_up(rows_tab_bytes(max_row_tiles(A, V)), 256));      // (GEMM2 and dXp are split)
 }
 
@@ -194,7 +212,7 @@ static i32x4* rows_tab_ws(const FfnArgs& a, void* ws) { return (i32x4*)((char*)r
 static int small_plan_parts(const FfnArgs& a) { return std::max(1, std::min(a.A / (a.V * 512), 2048 / a.V)); }      // waves per bucket, up to 512 workgroups
 static SmallPlan small_plan_ws(const FfnArgs& a, void* ws, float** partial = nullptr) {
   SmallPlan pl;
-  pl.bm = small_rows(a.A, a.d, a.f, a.E);
+  pl.bm = small_rows(a.A, a.d, a.f, a.E, a.V);
   pl.parts = small_plan_parts(a);
   char* at = (char*)rows_ws(a, ws);
   pl.tab = (i32x4*)at;
@@ -207,7 +225,7 @@ static SmallPlan small_plan_ws(const FfnArgs& a, void* ws, float** partial = nul
   return pl;
 }
 static int plan_blocks(const FfnArgs& a) {
-  if (small_rows(a.A, a.d, a.f, a.E)) return 1 + (a.V * small_plan_parts(a) + 3) / 4;      // the first: row tiles; the others: the row list
+  if (small_rows(a.A, a.d, a.f, a.E, a.V)) return 1 + (a.V * small_plan_parts(a) + 3) / 4;      // the first: row tiles; the others: the row list
   return std::max(1, std::min(64, (max_row_tiles(a.A, a.V) + kGemmThreads - 1) / kGemmThreads));
 }
 // What the rows kernels of one forward call look up: the row-tile table of the persistent kernels, or the small kernels'
@@ -289,7 +307,7 @@ static hipError_t launch_rows(const FfnArgs& a, const void* in, const void* w, c
                               const void* hpre_in, void* out0, void* out1, void* ws, hipStream_t s,
                               const int32_t* gsrc = nullptr, int gk = 1, void* split_ws = nullptr,
                               const int32_t* scatter_rows = nullptr) {
-  if (small_rows(a.A, a.d, a.f, a.E)) return launch_small<WT, EPI>(a, in, w, bias, K, NC, hpre_in, out0, out1, ws, s, gsrc, gk, scatter_rows);
+  if (small_rows(a.A, a.d, a.f, a.E, a.V)) return launch_small<WT, EPI>(a, in, w, bias, K, NC, hpre_in, out0, out1, ws, s, gsrc, gk, scatter_rows);
   const i32x4* tab = rows_tab_ws(a, ws);
   if (EPI == EPI_PLAIN)
     return launch_rows_t<WT, EPI, FLEXMOE_RELU>(a, in, w, bias, K, NC, hpre_in, out0, out1, s, gsrc, gk, split_ws,

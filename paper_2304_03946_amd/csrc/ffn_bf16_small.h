@@ -126,7 +126,7 @@ __device__ __forceinline__ void small_plan_block(const int32_t* __restrict__ vof
     row0 += wsum[0][w];
     tile0 += wsum[1][w];
   }
-  constexpr int kFirst = 4;                              // row tiles of an expert that its thread writes
+  constexpr int kFirst = 16;                             // row tiles of an expert that its thread writes
   if (block == 0) {
     for (int i = 0; i < min(n, kFirst); ++i) plan.tab[1 + tile0 + i] = i32x4{row0 + i * bm, min(bm, r - i * bm), t, 0};
     if (t == kGemmThreads - 1) plan.tab[0] = i32x4{tile0 + n, 0, 0, 0};

@@ -37,6 +37,15 @@ def test_rows_products_with_few_rows_per_expert(api, N, d, f, E, k, V, act):  # 
     stagewise(api, W.scaled(W.CONFIGS["gpt_m"], N=N, d=d, f=f, E=E, k=k, V=V, act=act, max_rep=3))
 
 
+# the last size of these kernels and the first of the 256 x 256 ones: by the outputs (register-staged and persistent), by the row
+# tiles per vExpert
+@pytest.mark.parametrize("N,d,f,E,k,V,act", [
+    (9613, 136, 392, 8, 2, 12, W.ACT_RELU), (9614, 136, 392, 8, 2, 12, W.ACT_GELU_ERF), (3584, 512, 2048, 8, 2, 9, W.ACT_GELU_TANH),
+    (3585, 512, 2048, 8, 2, 9, W.ACT_RELU), (17612, 128, 256, 256, 4, 512, W.ACT_GELU_ERF), (17613, 128, 256, 256, 4, 512, W.ACT_GELU_ERF)])
+def test_rows_products_at_the_line(api, N, d, f, E, k, V, act):  # noqa: F811
+    stagewise(api, W.scaled(W.CONFIGS["gpt_m"], N=N, d=d, f=f, E=E, k=k, V=V, act=act, max_rep=3))
+
+
 @pytest.mark.parametrize("N,d,f,E,V,k", [(3, 256, 1024, 16, 20, 1), (100, 384, 640, 8, 13, 1), (300, 128, 1024, 64, 96, 2)])
 def test_forward_variants_with_few_rows_per_expert(api, N, d, f, E, V, k):  # noqa: F811
     """Gathered loads, the scattered store of the top-1 call and the replayed contraction segments: the staged forward's bits."""
