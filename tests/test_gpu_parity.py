@@ -244,6 +244,20 @@ SMALL = {
     # (every one a ragged tile, many experts with a handful of tokens, the bucket lookups at their widest)
     "max_experts": W.scaled(W.CONFIGS["gpt_xl"], N=2500, d=128, f=256, E=256, V=512, k=8, max_rep=8, skew_s=1.0),
 }
+# The layers above have few rows for their experts or little output, so their rows products take the kernels for that (all but
+# split_tail); the same kinds of layers with enough rows for the 256 x 256 kernels: register-staged (contractions that
+# are no multiple of 128), persistent, both in one layer, top-1, ragged strips, balanced work lists, the library's limits
+MANY = {
+    "bert_many": W.scaled(SMALL["bert_small"], N=8100),
+    "gpt_many": W.scaled(SMALL["gpt_small"], N=10400),
+    "mixed_many": W.scaled(SMALL["gpt_small"], N=10700, d=264, f=512),
+    "swin_many": W.scaled(SMALL["swin_small"], N=20700),
+    "dma_many": W.scaled(SMALL["gpt_dma"], N=10800),
+    "strip_many": W.scaled(SMALL["strip_patches"], N=4900),
+    "balance_many": W.scaled(SMALL["wgrad_balance"], N=7300),
+    "experts_many": W.scaled(SMALL["max_experts"], N=9000),
+}
+SMALL.update(MANY)
 
 
 @pytest.mark.parametrize("name", list(SMALL))
@@ -273,6 +287,16 @@ def test_other_activations(api, act):
     cfg = W.scaled(SMALL["gpt_small"], N=900, act=act)
     inp = W.make_layer_inputs(cfg, seed=9)
     run_stagewise(api, cfg, inp, *W.placement_from_loads(W.prior_loads(cfg), cfg.V, 4))
+
+
+@pytest.mark.parametrize("act", [W.ACT_RELU, W.ACT_GELU_ERF, W.ACT_GELU_TANH])
+@pytest.mark.parametrize("name", ["gpt_many", "dma_many"])
+def test_bias_and_activation_with_many_rows(api, name, act):
+    cfg = W.scaled(SMALL[name], act=act, backward=False)
+    inp = W.make_layer_inputs(cfg, seed=9)
+    rng = np.random.default_rng(1)
+    b1, b2 = (W.Bf16Tensor.from_f32((rng.standard_normal((cfg.E, n)) * 0.3).astype(np.float32)) for n in (cfg.f, cfg.d))
+    run_stagewise(api, cfg, inp, *W.placement_from_loads(W.prior_loads(cfg), cfg.V, 4), b1=b1, b2=b2)
 
 
 def run_full_backward(api, cfg, inp, rep_off, rep_ids, b1=None, b2=None):
@@ -350,7 +374,7 @@ def test_full_backward_fp32(api):
     run_full_backward(api, cfg, inp, *W.placement_from_loads([5, 4, 3, 2, 1], cfg.V, 3, shuffle_seed=3), b1=b1, b2=b2)
 
 
-@pytest.mark.parametrize("name", ["gpt_small", "swin_small", "xl_small", "gpt_dma", "gpt_dma_seg", "strip_patches", "wgrad_balance"])
+@pytest.mark.parametrize("name", ["gpt_small", "swin_small", "xl_small", "gpt_dma", "gpt_dma_seg", "strip_patches", "wgrad_balance", "gpt_many", "dma_many"])
 def test_full_backward_reduced_configs(api, name):
     cfg = SMALL[name]
     inp = W.make_layer_inputs(cfg)
@@ -373,7 +397,7 @@ def test_full_backward_is_reproducible(api):
         assert np.array_equal(runs[0][n], runs[1][n]), n
 
 
-@pytest.mark.parametrize("name,bias", [("gpt_dma", False), ("gpt_dma", True)])
+@pytest.mark.parametrize("name,bias", [("gpt_dma", False), ("gpt_dma", True), ("dma_many", True)])
 def test_gathered_forward_equals_permute_then_ffn(api, name, bias):
     """flexmoe_expert_ffn_fwd_gather must reproduce flexmoe_permute + flexmoe_expert_ffn_fwd bit for
     bit (same tiles, same arithmetic, only the row addresses differ)."""
@@ -399,7 +423,7 @@ def test_gathered_forward_equals_permute_then_ffn(api, name, bias):
     assert not host(L.xp).any(), "the fused path must not touch xp"
 
 
-@pytest.mark.parametrize("name", ["tiny_f32", "bert_small", "gpt_dma"])
+@pytest.mark.parametrize("name", ["tiny_f32", "bert_small", "gpt_dma", "bert_many", "dma_many"])
 def test_forward_without_stored_preactivations(api, name):
     """hpre = NULL (inference): yp and y are the same bits, the hpre buffer is not touched.
     Covers the fp32 kernels, the register-staged bf16 kernels and the direct-to-LDS ones (both entry points)."""
@@ -488,7 +512,7 @@ def test_forward_variants_agree_bit_for_bit(api, N, d, f, E, V, k, bias):
             assert torch.equal(getattr(L, n), want[n]), f"{tag}: {n}"
 
 
-@pytest.mark.parametrize("name", ["swin_small", "many_rounds"])
+@pytest.mark.parametrize("name", ["swin_small", "many_rounds", "swin_many"])
 def test_top1_backward_equals_the_staged_backward(api, name):
     """flexmoe_expert_ffn_bwd_top1 stores dXp's rows through src: the same dX as the staged backward's
     combine, and the same weight gradients, bit for bit (shared launch and, at the larger size, the
@@ -515,7 +539,7 @@ def test_top1_backward_equals_the_staged_backward(api, name):
     assert not bool(L.dxp.any()), "the fused backward must not touch dxp"
 
 
-@pytest.mark.parametrize("name", ["gpt_small", "gpt_dma", "gpt_dma_seg", "swin_small", "tiny_f32", "gelu_tanh"])
+@pytest.mark.parametrize("name", ["gpt_small", "gpt_dma", "gpt_dma_seg", "swin_small", "tiny_f32", "gelu_tanh", "gpt_many", "dma_many", "mixed_many", "swin_many"])
 def test_backward_with_kept_activations_equals_the_recomputing_backward(api, name):
     """The forward pass may leave act(Hpre) in a buffer of the caller's, and the backward pass then skips
     computing and storing it: the kept tensor is what the recomputing backward derives from hpre, and dX, dW1,
@@ -606,6 +630,47 @@ def test_activation_on_every_bf16_value(api, act):
         worst = int(np.argmax(err / allowed))
         assert (err <= allowed).all(), (z.flat[worst], got.flat[worst], ref.flat[worst])
         assert (err <= 0.5 * _bf16_ulp(ref) + 2.0 ** -24).mean() > 0.999        # correctly rounded almost everywhere
+
+
+@pytest.mark.parametrize("act", [W.ACT_GELU_ERF, W.ACT_GELU_TANH])
+@pytest.mark.parametrize("d,copies", [(128, 128), (136, 1), (136, 116)])
+def test_activation_on_every_bf16_value_in_the_other_kernels(api, act, d, copies):
+    """As above where the table is read by the 256 x 256 kernel (d = 128, enough copies of the rows), and where the activation
+    is evaluated (d = 136, few rows and many).  Evaluated, Phi is good to 1.5e-7 (Abramowitz & Stegun 7.1.26) and tanh to
+    2^-22, plus a few roundings of 2^-24 of intermediates up to 1 + |z| (z stops where act' is 0 or 1)."""
+    B, layer = api
+    bits = np.arange(65536, dtype=np.uint32).astype(np.uint16)
+    bits[(bits & 0x7F80) == 0x7F80] = 0
+    bits[(bits & 0x7F80) == 0] &= 0x8000
+    rows = -(-65536 // d)
+    bits = np.tile(np.concatenate([bits, np.zeros(rows * d - 65536, dtype=np.uint16)]).reshape(rows, d), (copies, 1))
+    if d == 136:                                             # 4 z^3 of the tanh form overflows fp32 past 2^42: act is z or 0 there anyway
+        big = (bits & 0x7FFF) > (127 + 40 << 7)
+        bits[big] = 0
+    A = rows * copies
+    xp = W.Bf16Tensor(bits)
+    z = W.decode(W.Bf16Tensor(bits[:rows])).astype(np.float64)
+    up = layer.to_device
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device="cuda")
+    eye, ones = up(W.Bf16Tensor.from_f32(np.eye(d, dtype=np.float32)[None])), torch.ones((A, d), dtype=torch.bfloat16, device="cuda")
+    hpre = torch.empty(A, d, dtype=torch.bfloat16, device="cuda")
+    yp, dxp = torch.empty_like(hpre), torch.empty_like(hpre)
+    dw1, dw2 = torch.empty_like(eye), torch.empty_like(eye)
+    ws = torch.empty(B.flexmoe_workspace_bytes(A, d, d, 1, 1, 1, W.DT_BF16), dtype=torch.uint8, device="cuda")
+    xp_d = up(xp)
+    B.flexmoe_expert_ffn_fwd(xp_d, i32([0, A]), i32([0]), eye, None, eye, None, act, hpre, yp, ws)
+    B.flexmoe_expert_ffn_bwd(ones, xp_d, hpre, eye, eye, i32([0, A]), i32([0]), act, dxp, dw1, dw2, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(hpre.view(torch.int16), xp_d.view(torch.int16)) or torch.equal(hpre, xp_d)
+    for got, ref in ((yp, O.act_fn(z, act)), (dxp, O.act_grad(z, act))):
+        same = got.view(torch.int16).view(copies, rows, d)
+        assert torch.equal(same, same[:1].expand_as(same)), "every copy the same bits"
+        err = np.abs(host(got[:rows]).astype(np.float64) - ref)
+        allowed = np.maximum(_bf16_ulp(ref), 2.0 ** -24)
+        if d == 136:
+            allowed = 0.5 * _bf16_ulp(ref) + 2.0 ** -24 + (2.0 ** -21) * np.minimum(1 + np.abs(z), 16) * (np.abs(z) < 16)
+        worst = int(np.argmax(err / allowed))
+        assert (err <= allowed).all(), (z.flat[worst], host(got[:rows]).flat[worst], ref.flat[worst])
 
 
 @pytest.mark.parametrize("N,d,E,k", [(333, 136, 5, 1), (333, 136, 33, 2), (1000, 72, 64, 8), (97, 520, 100, 3),
