@@ -59,11 +59,14 @@ def test_forward_variants_with_few_rows_per_expert(api, N, d, f, E, V, k):  # no
     b1, b2 = (layer_mod.to_device(W.Bf16Tensor.from_f32((rng.standard_normal((E, n)) * 0.3).astype(np.float32))) for n in (f, d))
     rep = W.placement_from_loads(W.prior_loads(cfg), cfg.V, cfg.max_rep, shuffle_seed=11)
     L = layer_mod.MoELayer.for_config(cfg)
+    L.yp.fill_(float("nan"))
     L.forward(dev["x"], dev["wg"], dev["w1"], dev["w2"], *rep, b1, b2)
     want = L.y.clone()
+    assert not want.isnan().any()
     for fwd in [L.forward, L.forward_fused] + ([L.forward_top1] if k == 1 else []):
         for _ in range(3):      # the segment counters are left as they were found
-            L.y.zero_()
+            L.y.fill_(float("nan"))
+            L.yp.fill_(float("nan"))
             fwd(dev["x"], dev["wg"], dev["w1"], dev["w2"], *rep, b1, b2, keep_hpre=False)
             assert torch.equal(L.y, want)
 
@@ -95,7 +98,7 @@ def test_fp32_gate(api, N, d, E, k):  # noqa: F811
 # a partial last chunk, padded expert tiles, W_g as stored and transposed.  (check_gate wants at most 5 % of the tokens within
 # its error bound of a tie; the bound grows as d^1.5, 5e-4 at d = 520, against gaps of about 0.2 between k + 1 neighbouring
 # logits: about 1 % per pick at d = 520 but 3 % at d = 1032, so the larger d come with k = 1.)
-@pytest.mark.parametrize("N,d,E,k", [(8192, 520, 64, 2), (8193, 520, 64, 2), (16384, 72, 20, 1), (16385, 72, 20, 1), (33, 512, 33, 2),
+@pytest.mark.parametrize("N,d,E,k", [(8192, 520, 64, 2), (8193, 520, 64, 2), (16384, 72, 20, 1), (16385, 72, 20, 1), (24577, 248, 20, 1), (24577, 256, 20, 1), (33, 512, 33, 2),
                                      (400, 1032, 100, 1), (400, 520, 128, 2), (1, 8, 48, 8), (165, 504, 64, 3), (500, 776, 256, 1)])
 def test_bf16_gate(api, N, d, E, k):  # noqa: F811
     binding, layer_mod = api
