@@ -464,10 +464,17 @@ __global__ __launch_bounds__(kGateThreads) void gate_f32_kernel(const float* __r
   }
 }
 
-// Tokens that the split-K kernel takes in one round: 256 workgroups with 33 to 64 experts, 512 below.  Past that the
-// streaming kernel is ahead, in us (split-K, streaming; tokens x features): 64 experts 9000 x 2048 30.8, 22.5; 12000 x 2048
-// 32.9, 23.4; 17000 x 1024 26.6, 25.1; 32000 x 64 14.1, 10.3; 32 experts 25000 x 1024 16.7, 13.4; 32000 x 256 7.8, 7.2.
-static bool gate_streams(int N, int nt) { return nt <= 2 && N > (nt == 2 ? 8192 : 16384); }
+// From which size the streaming kernel is ahead: where the split-K kernel needs another round.  Its registers leave a compute
+// unit one workgroup with 33 to 64 experts (8192 tokens a round), three below (24576; the second workgroup of a compute unit
+// already costs as much as streaming from 2048 features on).  Below 256 features the launch that transposes W_g eats it up.  In us,
+// split-K and streaming, tokens x features:
+//   64 experts: 9000 x 64 7.6, 6.8; 9000 x 2048 30.8, 22.5; 17000 x 1024 26.6, 25.1; 32000 x 64 14.1, 10.3; but 17000 x 512 17.3, 17.2
+//   32 experts: 25000 x 256 7.4, 7.1; 25000 x 1024 17.1, 13.4; 32000 x 512 11.5, 9.5; 17000 x 2048 22.2, 20.2;
+//               past the line: 25000 x 128 6.1, 6.2; 32000 x 64 5.7, 5.9; 17000 x 1024 12.7, 12.9; 20000 x 512 7.8, 10.1; 17000 x 64 4.3, 5.7
+static bool gate_streams(int N, int d, int nt) {
+  if (nt > 2) return false;
+  return N >= 32768 || (nt == 2 ? N > 8192 : d >= 2048 ? N > 16384 : d >= 256 && N > 24576);
+}
 
 hipError_t launch_gate(const void* x, const void* wg, int N, int d, int E, int k, int dtype, int32_t* idx, float* w,
                        void* ws, hipStream_t s) {
@@ -489,7 +496,7 @@ hipError_t launch_gate(const void* x, const void* wg, int N, int d, int E, int k
   const int epad = nt * 32;
   bf16_t* wgt = (bf16_t*)ws;
   const bf16_t* xb = (const bf16_t*)x;
-  if (gate_streams(N, nt)) {
+  if (gate_streams(N, d, nt)) {
     // large batches: direct-to-LDS streaming, four waves (two below 65536 tokens) share a weight tile
     const int dpad = gate_dpad(d);
     hipLaunchKernelGGL(gate_transpose_wg_kernel, dim3((dpad + 255) / 256, epad), dim3(256), 0, s, (const bf16_t*)wg, d,
