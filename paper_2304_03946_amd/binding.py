@@ -132,7 +132,7 @@ def dtype_code(t: torch.Tensor) -> int:
 
 def _host_i32(a):
     """`a` as a contiguous int32 array, and its address (the array has to outlive the call the address goes to)."""
-    if type(a) is not np.ndarray or a.dtype != np.int32 or not a.flags.c_contiguous:
+    if type(a) is not np.ndarray or a.dtype != np.int32 or not a.flags.c_contiguous or not a.ndim:
         a = np.ascontiguousarray(np.asarray(a, dtype=np.int32))
     return a, a.__array_interface__["data"][0]
 

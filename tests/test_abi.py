@@ -75,6 +75,21 @@ def test_workspace_size_never_falls_with_the_number_of_tokens():
                 last = size
 
 
+def test_host_tables_in_every_form():
+    """Placement tables reach the library as contiguous int32 arrays of at least one dimension, whatever they come as."""
+    import numpy as np
+    from paper_2304_03946_amd import binding
+    base = np.arange(12, dtype=np.int32)
+    frozen = base.copy()
+    frozen.flags.writeable = False
+    for a in (base, frozen, base[::2], base[::-1], base.astype(np.int64), base.astype(">i4"), base.tolist(), base.view(np.matrix)[0], np.int32(3),
+              np.array(3, dtype=np.int32), np.array(3), 3, np.empty(0, dtype=np.int32)):
+        got, at = binding._host_i32(a)
+        assert got.dtype == np.int32 and got.flags.c_contiguous and got.ndim >= 1 and at == got.ctypes.data
+        assert np.array_equal(got.ravel(), np.asarray(a).ravel())
+    assert binding._host_i32(base)[0] is base
+
+
 def test_product_path_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2304_03946_amd")
     for fn in os.listdir(pkg):
