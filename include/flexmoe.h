@@ -116,6 +116,7 @@ int flexmoe_permute(const void* x, const int32_t* src, const float* row_scale,
  *   that pass computing and storing it again (the backward's first kernel then writes one [A,f] tensor
  *   instead of two); the price is A*f more elements of saved activations per layer.  Same bits either way.
  * The activation is applied to hpre as stored (i.e. after rounding to dtype).
+ * Equal calls give equal bits.  The fp32 sums' order may depend on the bucket sizes, and the last bits of a row with it.
  */
 int flexmoe_expert_ffn_fwd(const void* xp, const int32_t* vexpert_off, const int32_t* vexpert_owner,
                            const void* w1, const void* b1, const void* w2, const void* b2,

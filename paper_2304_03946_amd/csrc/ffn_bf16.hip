@@ -1,10 +1,12 @@
 // bf16 expert FFN (paper Eq. 2) per vExpert bucket, forward and backward, as grouped GEMMs on
 // the CDNA4 matrix cores (fp32 accumulation).
 //
-// All kernels share one 256x256 workgroup tile, one workgroup per compute unit: eight wavefronts with
+// Layers with enough rows for their experts share one 256x256 workgroup tile, one workgroup per compute unit: eight wavefronts with
 // 128x64 accumulator blocks (32 tiles of v_mfma_f32_16x16x32_bf16) in the direct-to-LDS kernels that
 // serve contractions of whole 128-wide rounds, four wavefronts with 128x128 blocks (16 tiles of
-// v_mfma_f32_32x32x16_bf16) in the register-staged kernel that serves the rest.
+// v_mfma_f32_32x32x16_bf16) in the register-staged kernel that serves the rest.  Rows products with few rows per expert or
+// little output have kernels of their own, with 32- or 64-row tiles and contraction segments (ffn_bf16_small.h; small_rows below
+// draws the line).
 //
 //  * rows GEMMs: C[rows of bucket v, :] = In[rows of v, :] . W_owner(v)    (fwd GEMM1/GEMM2,
 //    bwd dH and dXp).  The row dimension is cut per bucket: a device-side lookup maps the flat
@@ -19,15 +21,15 @@
 //    (the result does not depend on scheduling).
 //
 // Two operand pipelines:
-//  * direct-to-LDS (rows_gemm_persist_bf16, wgrad_gemm_persist_bf16, wgrad_gemm_dma_bf16; used whenever K is a
-//    multiple of 128, i.e. for every benchmark shape): global_load_lds_dwordx4 copies 32-wide K tiles
+//  * direct-to-LDS (rows_gemm_persist_bf16 where K is a multiple of 128, i.e. for every benchmark shape;
+//    wgrad_gemm_persist_bf16, wgrad_gemm_dma_bf16; rows_gemm_small_bf16 has its own): global_load_lds_dwordx4 copies 32-wide K tiles
 //    straight into one of four LDS stages (no register staging, no LDS store instructions); an
 //    operand whose contraction index is strided in memory is copied as stored and transposed on
 //    the way out of LDS by ds_read_tr16_b64.  The loads of the tile three steps ahead are
 //    spread between the MFMAs of the current one, and one LDS-only barrier per K tile orders
 //    stage reuse.  What bounds the K loop is the energy of bringing the operands into LDS (the stripped loop
 //    without its direct loads runs 27-41 % faster on random operands, 9-18 % on constant ones: csrc/probe).
-//  * register-staged (rows_gemm_bf16; any K that is a multiple of 8): 64-wide K
+//  * register-staged (rows_gemm_bf16; rows products with any other K that is a multiple of 8): 64-wide K
 //    tiles through registers into two LDS stages, strided operands transposed 8x8 in registers.
 //
 // LDS tiles are XOR-swizzled at 16-byte chunk granularity so that fragment reads and tile
@@ -35,7 +37,7 @@
 // The MFMA is issued as (weights-fragment, activations-fragment) so that a lane ends up with 4
 // consecutive output columns of one output row; the epilogue passes the accumulators through a
 // wave-private LDS patch so that global stores fill whole 128-byte lines.
-// GELU and its derivative act on bf16-rounded arguments, so both are read from a table indexed
+// GELU and its derivative act on bf16-rounded arguments, so where K is a multiple of 128 both are read from a table indexed
 // by the argument's bits (constant data in the code object, computed from the fp64 formulas when the
 // library is built; outside the table's range GELU equals ReLU to below bf16 resolution).
 //
@@ -46,8 +48,8 @@
 //
 // Layout of the sources: ffn_bf16_tile.h (tile mapping, fragments, activation tables, epilogues, the
 // register-staged kernel), ffn_bf16_dma.h (direct-to-LDS pipeline, one rows tile on it),
-// ffn_bf16_persist.h (persistent rows kernels and their row-tile table), ffn_bf16_wgrad.h
-// (weight-gradient plan and kernels); this file holds the host side.
+// ffn_bf16_persist.h (persistent rows kernels and their row-tile table), ffn_bf16_small.h (rows kernels for few rows
+// and their plan), ffn_bf16_wgrad.h (weight-gradient plan and kernels); this file holds the host side.
 #include <algorithm>
 
 #include "common.h"
@@ -67,8 +69,8 @@ namespace flexmoe {
 // but at least 32 (shorter segments measured slower: more fp32 partial tiles), so that the hottest expert's contraction is
 // no longer one serial K loop; at least 16 where the gradient of an expert is at most four output tiles and even those
 // leave most of the chip idle (a share of at most 8 K tiles).  Whole training steps, f = 4 d, k 2, in us, 32 and 16: d 128,
-// 4800 rows of 12 experts 166, 148; d 192, 9600 of 12 223, 208; d 256, 16000 of 40 (share 7.8) 262, 250; past the line,
-// d 256, 32000 of 40 (share 15.6) 337, 353; d 512 (16 output tiles), 4000 of 40 228, 256.  0 = no cutting:
+// 4800 rows of 12 experts 150, 133; d 192, 9600 of 12 182, 169; d 256, 9600 of 12 201, 190, 16000 of 40 (share 7.8) 269, 260; past the
+// line, 18400 of 40 (share 9) 274, 271, 32000 of 40 (share 15.6) 350, 365; d 512 (16 output tiles), 4000 of 40 233, 265.  0 = no cutting:
 // when a segment would hold more than a quarter of all tokens (many output tiles per expert: the
 // grid is busy anyway, and the fp32 partial tiles would be large).
 constexpr int kComputeUnits = 256;

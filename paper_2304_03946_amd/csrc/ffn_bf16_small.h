@@ -14,10 +14,11 @@ namespace flexmoe {
 //    fetch whole 128-byte lines of either operand (a K-strided operand: 256-byte pieces of 64 rows), S stages of
 //    them, two workgroups per compute unit (measured for the loads alone: 5.6 - 6.2 TB/s of 8);
 //  * where there are fewer tiles than workgroups the contraction is cut into segments; the last workgroup
-//    to finish a tile adds the fp32 partial tiles in segment order (a fixed order: reproducible) and runs the
-//    epilogue, so there is no second launch;
-//  * products are summed by the same instruction in the same order as in the 256 x 256 kernels, so without
-//    segments a row's result does not depend on which of the two ran.
+//    to finish a tile adds the fp32 partial tiles in segment order (a fixed order: the same call gives the same bits) and
+//    runs the epilogue, so there is no second launch.  How many segments there are follows from the row tiles in use
+//    (small_segments), so the last bits of a row can depend on how many experts the other rows of the batch went to;
+//  * where K is a multiple of 128, products are summed by the same instruction in the same order as in the 256 x 256
+//    kernels: a row without segments here and outside a split last round there has the same bits in either.
 // K and NC are any multiples of 8: the last, partial K tile reads zeros past K.
 // =============================================================================================
 constexpr int SN = 128, SK = 64;                         // columns of a tile, contraction indices of a stage

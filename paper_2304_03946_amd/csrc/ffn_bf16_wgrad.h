@@ -109,7 +109,8 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
 // The deal is a serial chain over the jobs (each goes to the bin that the earlier ones left least loaded), so it is the
 // length of one link that counts: lane q keeps bin q's load and count in registers and the least loaded bin comes from
 // a DPP minimum over (load, bin).  With one thread walking the bins in LDS the plan took 82 us of the Swin-like layer's
-// backward pass and 27 us of the GPT-medium-like one; like this the two layers' steps are 61 and 17 us shorter.
+// backward pass and 30 us of the GPT-medium-like one, now 17 and 14; the first layer's step is 59 us shorter, the second's gain
+// is within the differences between its runs.
 __device__ inline int balance_jobs(const WgradPlanShared& sh, WgradBalance geo, int seg_tiles, int positions,
                                    int4* __restrict__ dst) {
   const int lane = threadIdx.x & (kWave - 1);

@@ -25,9 +25,8 @@ def test_weight_gradient_work_lists(api, N, d, f, E, V):  # noqa: F811
 
 
 # rows kernels for few rows per expert or little output: 32-row tiles (at most 4 rows per expert on average; N = 1: two
-# experts with a single row, the contraction cut into its most segments), 64-row tiles up to 160 rows or 224 256 x 256
-# tiles of outputs, and the first size past either line (K whole and not whole 128-wide rounds); K with a partial last
-# tile (d, f multiples of 8 only), K below one tile, ragged column tiles, 512 buckets
+# experts with a single row, the contraction cut into its most segments) and the first size of 64-row tiles, K with a partial last
+# tile (d, f multiples of 8 only), K below one tile, ragged column tiles, 512 buckets; (7500, 136, 1032) is past their line
 @pytest.mark.parametrize("N,d,f,E,k,V,act", [
     (1, 1024, 4096, 32, 2, 48, W.ACT_GELU_ERF), (31, 264, 520, 16, 2, 21, W.ACT_GELU_TANH), (33, 264, 520, 16, 2, 21, W.ACT_RELU),
     (7, 48, 8, 4, 1, 6, W.ACT_GELU_ERF), (640, 136, 392, 8, 2, 12, W.ACT_GELU_ERF), (641, 136, 392, 8, 2, 12, W.ACT_GELU_ERF),
