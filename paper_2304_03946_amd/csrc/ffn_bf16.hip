@@ -238,9 +238,10 @@ static void launch_rows_plan(const FfnArgs& a, void* ws, hipStream_t s) {
   else hipLaunchKernelGGL(rows_plan_kernel, dim3(plan_blocks(a)), dim3(kGemmThreads), 0, s, a.voff, a.owner, a.V, rows_tab_ws(a, ws));
 }
 
-template <int BM, bool WT, int EPI>
-static void launch_small_t(const SmallArgs& p, unsigned grid, hipStream_t s) {
-  hipLaunchKernelGGL((rows_gemm_small_bf16<BM, WT, EPI>), dim3(grid), dim3(kSmallThreads), 0, s, p);
+template <bool WT, int EPI, bool EVAL>
+static void launch_small_t(int bm, const SmallArgs& p, unsigned grid, hipStream_t s) {
+  if (bm == 32) hipLaunchKernelGGL((rows_gemm_small_bf16<32, WT, EPI, EVAL>), dim3(grid), dim3(kSmallThreads), 0, s, p);
+  else hipLaunchKernelGGL((rows_gemm_small_bf16<64, WT, EPI, EVAL>), dim3(grid), dim3(kSmallThreads), 0, s, p);
 }
 template <bool WT, int EPI>
 static hipError_t launch_small(const FfnArgs& a, const void* in, const void* w, const void* bias, int K, int NC,
@@ -250,14 +251,20 @@ static hipError_t launch_small(const FfnArgs& a, const void* in, const void* w, 
   const SmallPlan pl = small_plan_ws(a, ws, &partial);
   // The table as in the 256 x 256 kernels: where the contraction is whole 128-wide rounds.  Otherwise the activation is
   // evaluated: the table has 2^-24 for every smaller magnitude, zero included, and a negative NaN is lost in it.
-  const int lut = EPI == EPI_PLAIN || a.act == FLEXMOE_RELU || K % 128 ? -1 : a.act == FLEXMOE_GELU_ERF ? 0 : 1;
+  const bool gelu = EPI != EPI_PLAIN && a.act != FLEXMOE_RELU;
+  const int lut = !gelu || K % 128 ? -1 : a.act == FLEXMOE_GELU_ERF ? 0 : 1;
   const SmallArgs p{(const bf16_t*)in, (const bf16_t*)w, (const bf16_t*)bias, pl.tab, pl.rowmap, K, NC, (NC + SN - 1) / SN,
                     (const bf16_t*)hpre_in, (bf16_t*)out0, (bf16_t*)out1, gsrc, gk, scatter_rows, a.act, lut, partial, pl.counters};
   // two workgroups per compute unit walk the tiles
   const long long most = (long long)(a.A / pl.bm + a.E) * p.col_tiles;
   const unsigned grid = (unsigned)std::min<long long>(kSmallSplitTarget, std::max<long long>(most * kSmallSplitMax, 1));
-  if (pl.bm == 32) launch_small_t<32, WT, EPI>(p, grid, s);
-  else launch_small_t<64, WT, EPI>(p, grid, s);
+  if constexpr (EPI != EPI_PLAIN) {
+    if (gelu && lut < 0) {
+      launch_small_t<WT, EPI, true>(pl.bm, p, grid, s);
+      return hipGetLastError();
+    }
+  }
+  launch_small_t<WT, EPI, false>(pl.bm, p, grid, s);
   return hipGetLastError();
 }
 

@@ -54,7 +54,7 @@ struct SmallArgs {
   const int32_t* gsrc;           // gathered rows of `in`: row gsrc[bucket row] / gk; or null
   int gk;
   const int32_t* scatter_rows;   // bucket row p is stored as row scatter_rows[p] of out0; or null
-  int act, lut;                  // activation; which of g_act_lut's tables it is read from, -1: none (evaluated)
+  int act, lut;                  // activation (EVAL); which of g_act_lut's tables it is read from, -1: ReLU
   float* partial;                // kSmallSlots partial tiles
   int* counters;                 // one per tile that is cut into segments, zeroed by the plan
 };
@@ -180,8 +180,8 @@ __device__ __forceinline__ void small_load_at(const bf16_t* p, unsigned lds) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p), "s"(lds) : "memory");
 }
 // Activation and derivative without a table.
-__device__ __forceinline__ void small_act(int act, float z, float* a, float* da) {
-  if (act == FLEXMOE_RELU) act_both<FLEXMOE_RELU>(z, a, da);
+template <bool EVAL> __device__ __forceinline__ void small_act(int act, float z, float* a, float* da) {
+  if (!EVAL) act_both<FLEXMOE_RELU>(z, a, da);
   else if (act == FLEXMOE_GELU_ERF) act_both<FLEXMOE_GELU_ERF>(z, a, da);
   else act_both<FLEXMOE_GELU_TANH>(z, a, da);
 }
@@ -193,8 +193,9 @@ template <int L> __device__ __forceinline__ void small_wait(int tiles) {
   }
 }
 
-// EPI as in rows_epilogue_t.  WT: W_e is [NC, K] (else [K, NC]).
-template <int BM, bool WT, int EPI>
+// EPI as in rows_epilogue_t.  WT: W_e is [NC, K] (else [K, NC]).  EVAL: GELU is evaluated, not read from a table (kernels of their
+// own: with both in one, the 1500-token step of d 1024 took 658 us instead of 650).
+template <int BM, bool WT, int EPI, bool EVAL>
 __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const SmallArgs p) {
   typedef SmallCfg<BM> C;
   constexpr int S = C::S, RB = BM / 16, NB2 = SN / kSmallWaves / 16;      // 16-row and 16-column blocks of a wave
@@ -382,7 +383,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const S
       __syncthreads();                                   // the flag has been read
     }
 
-    const bool use_lut = EPI != EPI_PLAIN && p.lut >= 0;
+    const bool use_lut = EPI != EPI_PLAIN && !EVAL && p.lut >= 0;
     if (use_lut) {
       // the stages are free: the activation table (28 KB, from L2) goes there
 #pragma unroll
@@ -422,7 +423,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const S
                 const uint32_t zu = __float_as_uint(z[q]);
                 float da;
                 if (use_lut) a[q] = lut_act(sm, zu);
-                else small_act(p.act, z[q], &a[q], &da);
+                else small_act<EVAL>(p.act, z[q], &a[q], &da);
               }
               if (p.out0) *(uint2*)(p.out0 + o) = pre;
               *(uint2*)(p.out1 + o) = pack4(a[0], a[1], a[2], a[3]);
@@ -435,7 +436,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const S
                 if (use_lut) {
                   lut_act_both(sm, zu, &a[q], &dv[q]);
                 } else {
-                  small_act(p.act, z[q], &a[q], &dv[q]);
+                  small_act<EVAL>(p.act, z[q], &a[q], &dv[q]);
                 }
               }
               *(uint2*)(p.out0 + o) = pack4(c[0] * dv[0], c[1] * dv[1], c[2] * dv[2], c[3] * dv[3]);
