@@ -41,7 +41,7 @@ __device__ __forceinline__ int lds_off(int row, int chunk) { return row * BK + (
 // ---- workgroup id -> tile, XCD aware ---------------------------------------------------------
 // Workgroups are dealt round-robin to the 8 XCDs (id % 8), each with its own L2, and an XCD runs
 // its workgroups in ascending id.  The rows x cols tile grid is cut into column strips pw tiles wide
-// (pw divides cols whenever a divisor in 5..8 exists) and every strip, walked row by row, into patches
+// (pw divides cols; up to 8 columns are one strip) and every strip, walked row by row, into patches
 // of 32 consecutive tiles (one per CU of an XCD: 32 / pw rows of the strip; where pw does not divide 32
 // a patch starts and ends inside a row); the j-th workgroup of XCD x gets tile j % 32 of patch
 // (j / 32) * 8 + x, patches numbered strip by strip within a row of patches.  The workgroups that run
@@ -54,21 +54,37 @@ __host__ __device__ inline int patch_width(int cols) {
     if (cols % pw == 0) return pw;
   return 8;
 }
+// Column counts that no such strip divides (9, 11, 13, 17, 19, .. tiles): strips would leave positions without a tile, always the
+// same workgroups' (a workgroup keeps its place in a patch from round to round), so the walk goes through bands of four rows instead,
+// column by column: 32 neighbouring tiles are four rows of eight columns, and there are no holes.
+// Strips and bands: d 1152, f 4352 (17 tiles), 16384 rows, GEMM1 267 and 197 us, dH 263 and 208; d 1408,
+// f 2816 (11), 32768 rows, GEMM1 347 and 269, dH 369 and 276, dW1 445 and 372; few rows: d 1152, f 4224 (9 and 33 of 128 columns), 3000
+// rows of 32 experts 143 and 105, 109 and 103; d 640, f 1152 (9), 16384 rows of 128 experts 132 and 85.
+__host__ __device__ inline bool patch_bands(int cols) { return cols % patch_width(cols) != 0; }
+constexpr int kBand = 4;
 __host__ __device__ inline unsigned patched_grid(int rows, int cols) {
   const int pw = patch_width(cols);
-  const int np = ((rows * pw + kPatch - 1) / kPatch) * ((cols + pw - 1) / pw);
+  const int np = patch_bands(cols) ? (rows * cols + kPatch - 1) / kPatch : ((rows * pw + kPatch - 1) / kPatch) * (cols / pw);
   return (unsigned)((np + kXcds - 1) / kXcds * kXcds) * kPatch;
 }
 // returns false when the workgroup falls into the padding of the patch grid
 __device__ __forceinline__ bool patched_tile(unsigned b, int rows, int cols, int* r, int* c) {
   const int pw = patch_width(cols);
-  const int npc = (cols + pw - 1) / pw;
   const unsigned x = b % kXcds, j = b / kXcds;
   const unsigned P = (j / kPatch) * kXcds + x, q = j % kPatch;
+  if (patch_bands(cols)) {
+    const unsigned t = P * kPatch + q, band = t / (unsigned)(kBand * cols), u = t - band * (kBand * cols);
+    const int h = min(kBand, rows - (int)band * kBand);
+    if (h <= 0) return false;
+    *r = (int)band * kBand + (int)(u % (unsigned)h);
+    *c = (int)(u / (unsigned)h);
+    return *c < cols;
+  }
+  const int npc = cols / pw;
   const unsigned t = (P / npc) * kPatch + q;      // position in the strip's row-by-row walk
   *r = (int)(t / pw);
   *c = (int)(P % npc) * pw + (int)(t % pw);
-  return *r < rows && *c < cols;
+  return *r < rows;
 }
 
 // ---- global -> registers -> LDS -------------------------------------------------------------

@@ -72,8 +72,8 @@ struct WgradBalance {
   int groups, per_slot;
 };
 __host__ __device__ inline WgradBalance wgrad_balance_geometry(int m_tiles, int n_tiles) {
-  const int pw = patch_width(n_tiles), ph = kPatch / pw, npc = (n_tiles + pw - 1) / pw;
-  if (pw * ph != kPatch) return WgradBalance{1, 1};
+  const int pw = patch_width(n_tiles), ph = kPatch / pw, npc = n_tiles / pw;
+  if (pw * ph != kPatch || patch_bands(n_tiles)) return WgradBalance{1, 1};
   if (m_tiles % ph == 0) {
     const int pj = (m_tiles / ph) * npc;                 // patches per job
     if (pj < kXcds && kXcds % pj == 0) return WgradBalance{kXcds / pj, 1};
