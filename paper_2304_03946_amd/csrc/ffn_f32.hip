@@ -1,27 +1,26 @@
 // fp32 expert FFN (paper Eq. 2) forward and backward per vExpert bucket, on the fp32 matrix instruction
-// v_mfma_f32_32x32x2_f32 (fp32 operands, products and sums).
+// v_mfma_f32_16x16x4_f32 (fp32 operands, products and sums).
 //
-// One workgroup of four waves per 64 x 64 outputs, a wave per 32 x 32.  32-wide K tiles travel global -> LDS with direct
-// loads through four stages (64 KB: two workgroups per compute unit); three tiles are in flight while one is multiplied.
-// The contraction index inside a K tile is dealt to the instruction's two halves four at a time, so that a
-// K-contiguous operand is read from LDS as 16-byte vectors.  Every sum runs over its K tiles in ascending order in one
-// accumulator: results are reproducible.
+// One workgroup of four waves per tile of outputs.  64 x 64: a wave per 32 x 32 (four independent accumulators).  32 x 64, where 64 x 64
+// tiles would leave most of the chip without work: two waves per 32 x 32, one for the even 32-wide K tiles and one for the odd, whose
+// sums are added at the end.  K tiles travel global -> LDS with direct loads through four (three) stages; two workgroups per compute
+// unit.  Within sixteen k an instruction's lane groups hold four consecutive ones each, so that a K-contiguous operand is read
+// from LDS as 16-byte vectors.  The order of a sum depends on the sizes only: results are reproducible.
 //
-// What bounds it: a workgroup's K tile is 1024 cycles of matrix instructions per wave against 16 KB of operands; with
-// 100 - 600 workgroups (the sizes fp32 layers are used at) the K tiles' latency.  One thread per output, reading its
-// operands with scalar loads, took 255 us for [2000, 256] x [256, 1024] and 1680 us where the weights are read along their
-// rows (dH, dXp: every lane in a cache line of its own); these take 31 us each (34 TFLOP/s of 157), the weight gradients
-// of that layer 26 us instead of 317, and the whole fp32 training step 237 us instead of 4920.
+// What bounds it: 1024 cycles of matrix instructions per K tile and wave where the chip is full (4352 tiles: 207 us for [8192, 512] x
+// [512, 2048], 83 TFLOP/s of 157), else what a workgroup does before its first K tile, the K tiles' latency, and workgroups that do not
+// come out even over the compute units.  With 64 x 64 tiles alone, loads behind a branch each and two trips to memory before the first
+// one: fp32 training step of 1000 tokens (d 256, f 1024, 8 experts) 30, 29, 31, 27 us for its rows products and 28, 28 for its weight
+// gradients, now 25, 25, 26, 24 and 22, 22; 4096 tokens (d 512, f 2048) 221, 228, 233, 229, 203, 201 -> 207, 198, 219, 195, 187, 185; 100
+// tokens of that layer 26, 52, 27, 49, 20, 20 -> 16, 27, 17, 26, 23, 22; weight gradients of a hot expert (d 128, f 512, 8192 rows) 84 -> 46.
+#include <type_traits>
+
 #include "common.h"
 
 namespace flexmoe {
 
 constexpr int kF32Threads = 256;
-constexpr int FM = 64, FN = 64, FK = 32;             // tile of outputs, K tile
-constexpr int kF32Stages = 4;
-constexpr int kF32OpBytes = 64 * FK * 4;             // one operand's K tile: 8 KB
-constexpr int kF32StageBytes = 2 * kF32OpBytes;
-constexpr int kF32Loads = 4;                         // direct loads per wave and K tile: two per operand
+constexpr int FN = 64, FK = 32;                      // columns of a tile, contraction indices of a K tile
 
 enum { EPI_FWD1 = 0, EPI_PLAIN = 1, EPI_DH = 2 };
 
@@ -32,162 +31,249 @@ __device__ __forceinline__ void f32_load(const float* p, unsigned lds) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p), "s"(lds) : "memory");
 }
 template <int N> __device__ __forceinline__ void f32_wait_vmcnt() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14)); }
-__device__ __forceinline__ void f32_wait_tiles(int tiles) {      // at most `tiles` younger K tiles in flight
-  switch (tiles) {
-    case 0: f32_wait_vmcnt<0>(); break;
-    case 1: f32_wait_vmcnt<kF32Loads>(); break;
-    default: f32_wait_vmcnt<2 * kF32Loads>(); break;
+
+// One operand's K tile in LDS, W outputs wide.  KC (K-contiguous): [W][32 k], rows of eight 16-byte chunks, chunk index XOR row & 7.
+// K-strided: [32 k][W]; an instruction's four lane groups read rows four apart, 16 outputs (64 bytes) each, which must lie in different
+// banks: 64 wide, chunk index XOR 4 ((k / 4) % 4); 32 wide (half the banks), chunk index XOR 4 ((k / 4) % 2), neighbouring rows swapped
+// where k & 8.
+template <bool KC, int W> struct F32Op {
+  static constexpr int kBytes = W * FK * 4;
+  static constexpr int kPieces = kBytes / 1024;      // direct loads
+  // output (row or column) and k that the lane fetches in piece i, four of the contiguous ones from there
+  static __device__ __forceinline__ int out(int i, int lane) {
+    if (KC) return i * 8 + (lane >> 3);
+    if (W == 64) return ((lane & 15) ^ (((k(i, lane) >> 2) & 3) << 2)) * 4;
+    return ((lane & 7) ^ (((k(i, lane) >> 2) & 1) << 2)) * 4;
   }
-}
-
-// LDS tile of a K-contiguous operand: [64][32 k], rows of eight 16-byte chunks, chunk index XOR row & 7 (conflict-free
-// 16-byte reads of 32 rows).  Direct load q of wave w fills rows 8 (2 w + q) ..: the lane's row and first k:
-__device__ __forceinline__ int kc_row(int wave, int q, int lane) { return (wave * 2 + q) * 8 + (lane >> 3); }
-__device__ __forceinline__ int kc_k(int lane) { return ((lane & 7) ^ (lane >> 3)) * 4; }
-// LDS tile of a K-strided operand: [32 k][64], rows of sixteen chunks, chunk index XOR 8 where k & 4 (the
-// instruction's halves read rows four apart: 32 banks apart).  The lane's k row and first column:
-__device__ __forceinline__ int ks_k(int wave, int q, int lane) { return (wave * 2 + q) * 4 + (lane >> 4); }
-__device__ __forceinline__ int ks_col(int k, int lane) { return ((lane & 15) ^ ((k & 4) << 1)) * 4; }
-
-// Four k of one operand's 32 outputs (lane % 32 + base): k = 8 kk + 4 (lane / 32) ..
-template <bool KC> __device__ __forceinline__ void f32_frag(float (&f)[4], const lds_t* tile, int base, int kk, int lane) {
-  const int r = base + (lane & 31), h = lane >> 5;
-  if (KC) {
-    const f32x4 v = *(const __attribute__((address_space(3))) f32x4*)(tile + r * 128 + (((2 * kk + h) ^ (r & 7)) << 4));
+  static __device__ __forceinline__ int k(int i, int lane) {
+    if (KC) return ((lane & 7) ^ (lane >> 3)) * 4;
+    if (W == 64) return i * 4 + (lane >> 4);
+    const int p = i * 8 + (lane >> 3);
+    return p ^ ((p >> 3) & 1);
+  }
+  // four k of output base + lane % 16: k = 16 kk + 4 (lane / 16) ..
+  static __device__ __forceinline__ void frag(float (&f)[4], const lds_t* tile, int base, int kk, int lane) {
+    const int r = base + (lane & 15), g = lane >> 4;
+    if (KC) {
+      const f32x4 v = *(const __attribute__((address_space(3))) f32x4*)(tile + r * 128 + (((4 * kk + g) ^ (r & 7)) << 4));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) f[j] = v[j];
-  } else {
+      for (int j = 0; j < 4; ++j) f[j] = v[j];
+    } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = 8 * kk + 4 * h + j;
-      f[j] = *(const __attribute__((address_space(3))) float*)(tile + k * 256 + (((r >> 2) ^ (h << 3)) << 4) + (r & 3) * 4);
+      for (int j = 0; j < 4; ++j) {
+        const int kr = 16 * kk + 4 * g + j;
+        const lds_t* at = W == 64 ? tile + kr * 256 + (((r >> 2) ^ (g << 2)) << 4) + (r & 3) * 4
+                                  : tile + (kr ^ (g >> 1)) * 128 + (((r >> 2) ^ ((g & 1) << 2)) << 4) + (r & 3) * 4;
+        f[j] = *(const __attribute__((address_space(3))) float*)at;
+      }
     }
   }
-}
+};
 
-// KT K tiles through the stages; issue(kt, lds address of the stage) starts the wave's kF32Loads loads of one.
-// First operand = output rows, second = columns; acc[q]: row lane % 32, column 8 (q / 4) + 4 (lane / 32) + q % 4 of the wave's block.
-template <bool KC0, bool KC1, typename Issue>
-__device__ __forceinline__ void f32_mainloop(lds_t* sm, f32x16& acc, int KT, Issue issue) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)sm);
+typedef f32x4 F32Acc[2][2];                          // a wave's 32 x 32 outputs: 16-row and 16-column blocks
+
+// A workgroup's K loop: MT 32-row blocks x 64 columns.  MT == 2: a wave per 32 x 32 outputs.  MT == 1: two waves per 32 x 32 outputs,
+// one for the even K tiles, one for the odd ones.  A stage holds 3 - MT K tiles.
+template <int MT, bool KC0, bool KC1> struct F32Loop {
+  typedef F32Op<KC0, MT * 32> Op0;
+  typedef F32Op<KC1, FN> Op1;
+  static constexpr int kSub = 3 - MT;                // K tiles of a stage
+  static constexpr int kSubBytes = Op0::kBytes + Op1::kBytes;
+  static constexpr int kStageBytes = kSub * kSubBytes;
+  static constexpr int S = MT == 2 ? 4 : 3;
+  static constexpr int kL0 = kSub * Op0::kPieces / 4, kL1 = kSub * Op1::kPieces / 4, kLoads = kL0 + kL1;      // direct loads per wave and stage
+  static constexpr int kLds = S * kStageBytes;
+  // the wave's q-th load of either operand: K tile of the stage, piece
+  static __device__ __forceinline__ int sub0(int wave, int q) { return (wave * kL0 + q) / Op0::kPieces; }
+  static __device__ __forceinline__ int piece0(int wave, int q) { return (wave * kL0 + q) % Op0::kPieces; }
+  static __device__ __forceinline__ int sub1(int wave, int q) { return (wave * kL1 + q) / Op1::kPieces; }
+  static __device__ __forceinline__ int piece1(int wave, int q) { return (wave * kL1 + q) % Op1::kPieces; }
+  static __device__ __forceinline__ unsigned dst0(int wave, int q) { return sub0(wave, q) * kSubBytes + piece0(wave, q) * 1024; }
+  static __device__ __forceinline__ unsigned dst1(int wave, int q) { return sub1(wave, q) * kSubBytes + Op0::kBytes + piece1(wave, q) * 1024; }
+
+  // KT stages; issue(s, lds address) starts the wave's loads of one.
+  // acc[i][j]: row 16 i + lane % 16, columns 16 j + 4 (lane / 16) .. of the wave's block.  MT == 1: on return the wave with the even K tiles
+  // has the sums of the block's first 16 columns, the other one of the rest.
+  template <typename Issue>
+  static __device__ __forceinline__ void run(lds_t* sm, F32Acc& acc, int KT, Issue issue) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)sm);
 #pragma unroll
-  for (int s = 0; s < kF32Stages - 1; ++s)
-    if (s < KT) issue(s, lds0 + s * kF32StageBytes);
-  for (int kt = 0; kt < KT; ++kt) {
-    f32_wait_tiles(min(kF32Stages - 2, KT - 1 - kt));
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    if (kt + kF32Stages - 1 < KT) issue(kt + kF32Stages - 1, lds0 + (kt + kF32Stages - 1) % kF32Stages * kF32StageBytes);
-    const lds_t* st = sm + kt % kF32Stages * kF32StageBytes;
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int kk = 0; kk < FK / 8; ++kk) {
-      float a[4], b[4];
-      f32_frag<KC0>(a, st, (wave >> 1) * 32, kk, lane);
-      f32_frag<KC1>(b, st + kF32OpBytes, (wave & 1) * 32, kk, lane);
+      for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j], a[j], acc, 0, 0, 0);
+    for (int s = 0; s < S - 1; ++s)
+      if (s < KT) issue(s, lds0 + s * kStageBytes);
+    for (int kt = 0; kt < KT; ++kt) {
+      switch (min(S - 2, KT - 1 - kt)) {             // younger stages in flight
+        case 0: f32_wait_vmcnt<0>(); break;
+        case 1: f32_wait_vmcnt<kLoads>(); break;
+        default: f32_wait_vmcnt<2 * kLoads>(); break;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+      if (kt + S - 1 < KT) issue(kt + S - 1, lds0 + (kt + S - 1) % S * kStageBytes);
+      const lds_t* st = sm + kt % S * kStageBytes + (MT == 1 ? (wave >> 1) * kSubBytes : 0);
+#pragma unroll
+      for (int kk = 0; kk < FK / 16; ++kk) {
+        float a[2][4], b[2][4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) Op0::frag(a[i], st, (MT == 2 ? (wave >> 1) * 32 : 0) + i * 16, kk, lane);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) Op1::frag(b[j], st + Op0::kBytes, (wave & 1) * 32 + j * 16, kk, lane);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][q], a[i][q], acc[i][j], 0, 0, 0);
+      }
+    }
+    if (MT == 1) {
+      // the two waves of a block trade the halves they do not keep (even K tiles + odd K tiles, in either)
+      __syncthreads();
+      typedef __attribute__((address_space(3))) f32x4* Ptr;
+      const int keep = wave >> 1;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const f32x4 first = acc[i][0], second = acc[i][1];
+        *(Ptr)(sm + ((wave * 2 + i) * kWave + lane) * 16) = keep ? first : second;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const f32x4 v = *(Ptr)(sm + (((wave ^ 2) * 2 + i) * kWave + lane) * 16);      // (even K tiles + odd ones, in either wave)
+        acc[i][0] += v;
+        acc[i][1] += v;
+      }
     }
   }
-}
+};
 
-// flat row-tile index -> {first row, rows, expert} of a 64-row tile of the bucket list; one wave scans the buckets'
-// tile counts.  False (for the whole workgroup): beyond the last tile.
-__device__ __forceinline__ bool f32_row_tile(const int32_t* __restrict__ voff, const int32_t* __restrict__ owner, int V, int rt,
-                                             int* s_tile, int* row0, int* rows, int* e) {
+// Workgroup -> {first row, rows, expert} of an FM-row tile of the bucket list, and column tile; one wave scans the buckets'
+// tile counts (all that it needs of them in one trip to memory).  False (for the whole workgroup): beyond the last tile.
+// Workgroups are dealt round-robin to the XCDs; XCD x takes the x-th eighth of the tiles, row tile by row tile, so that rows and
+// weights come into one L2 or two and not into all eight.
+constexpr unsigned kF32Xcds = 8;
+template <int FM>
+__device__ __forceinline__ bool f32_tile(const int32_t* __restrict__ voff, const int32_t* __restrict__ owner, int V, int col_tiles,
+                                         int* s_tile, int* row0, int* rows, int* e, int* ct) {
   if (threadIdx.x < kWave) {
     const int lane = threadIdx.x;
     if (lane == 0) s_tile[0] = -1;
-    const int per = (V + kWave - 1) / kWave;
-    int sum = 0;
-    for (int q = 0; q < per; ++q) {
-      const int v = lane * per + q;
-      if (v < V) sum += (voff[v + 1] - voff[v] + FM - 1) / FM;
-    }
-    int incl = sum;
+    const unsigned x = blockIdx.x % kF32Xcds;
+    auto scan = [&](auto per_lane) {                 // buckets per lane
+      constexpr int kPer = decltype(per_lane)::value;
+      int lo[kPer], hi[kPer], own[kPer], sum = 0;
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int up = __shfl_up(incl, o);
-      if (lane >= o) incl += up;
-    }
-    int start = incl - sum;
-    if (rt >= start && rt < incl)
-      for (int q = 0; q < per; ++q) {
-        const int v = lane * per + q;
-        if (v >= V) break;
-        const int lo = voff[v], n = (voff[v + 1] - lo + FM - 1) / FM;
-        if (rt < start + n) {
-          s_tile[0] = lo + (rt - start) * FM;
-          s_tile[1] = min(FM, voff[v + 1] - s_tile[0]);
-          s_tile[2] = owner[v];
-          break;
+      for (int q = 0; q < kPer; ++q) {
+        const int v = lane * kPer + q;
+        lo[q] = voff[min(v, V)];
+        hi[q] = voff[min(v + 1, V)];
+        own[q] = owner[min(v, V - 1)];
+      }
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) sum += (hi[q] - lo[q] + FM - 1) / FM;
+      int incl = sum;
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int up = __shfl_up(incl, o);
+        if (lane >= o) incl += up;
+      }
+      const unsigned long long tiles = (unsigned long long)(unsigned)__builtin_amdgcn_readlane(incl, kWave - 1) * (unsigned)col_tiles;
+      const unsigned t = (unsigned)(tiles * x / kF32Xcds) + blockIdx.x / kF32Xcds;
+      const int rt = t < (unsigned)(tiles * (x + 1) / kF32Xcds) ? (int)(t / (unsigned)col_tiles) : -1;
+      if (lane == 0) s_tile[3] = (int)(t % (unsigned)col_tiles);
+      int start = incl - sum;
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        const int n = (hi[q] - lo[q] + FM - 1) / FM;
+        if (rt >= start && rt < start + n) {
+          s_tile[0] = lo[q] + (rt - start) * FM;
+          s_tile[1] = min(FM, hi[q] - s_tile[0]);
+          s_tile[2] = own[q];
         }
         start += n;
       }
+    };
+    if (V <= kWave) scan(std::integral_constant<int, 1>{});
+    else scan(std::integral_constant<int, FLEXMOE_MAX_VEXPERTS / kWave>{});
   }
   __syncthreads();
   *row0 = __builtin_amdgcn_readfirstlane(s_tile[0]);
   *rows = __builtin_amdgcn_readfirstlane(s_tile[1]);
   *e = __builtin_amdgcn_readfirstlane(s_tile[2]);
+  *ct = __builtin_amdgcn_readfirstlane(s_tile[3]);
   return *row0 >= 0;
 }
 
 // C[p, n] = sum_k In[p, k] * W_e[k, n]   (WT == false, W_e is [K, NC])
 //         = sum_k In[p, k] * W_e[n, k]   (WT == true,  W_e is [NC, K])
-template <bool WT, int EPI>
+template <int MT, bool WT, int EPI>
 __global__ __launch_bounds__(kF32Threads, 2) void rows_gemm_f32(const float* __restrict__ in, const float* __restrict__ w,
                                                                 const float* __restrict__ bias,
                                                                 const int32_t* __restrict__ voff,
                                                                 const int32_t* __restrict__ owner, int V, int K, int NC,
                                                                 int act, const float* __restrict__ hpre_in,
                                                                 float* __restrict__ out0, float* __restrict__ out1) {
-  __shared__ __align__(1024) unsigned char smem[kF32Stages * kF32StageBytes];
-  __shared__ int s_tile[3];
-  int row0, rows, e;
-  if (!f32_row_tile(voff, owner, V, blockIdx.x, s_tile, &row0, &rows, &e)) return;
-  const int n0 = blockIdx.y * FN, cols = min(FN, NC - n0);
+  typedef F32Loop<MT, true, WT> Loop;
+  __shared__ __align__(1024) unsigned char smem[Loop::kLds];
+  __shared__ int s_tile[4];
+  int row0, rows, e, ct;
+  if (!f32_tile<MT * 32>(voff, owner, V, (NC + FN - 1) / FN, s_tile, &row0, &rows, &e, &ct)) return;
+  const int n0 = ct * FN, cols = min(FN, NC - n0);
   const float* we = w + (size_t)e * K * NC;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 
-  const float* ap[2];
-  const float* wp[2];
-  int wk[2];
+  // the lane's loads, from the tile's first row and column on
+  const float* const a_base = in + (size_t)row0 * K;
+  const float* const w_base = we + (WT ? (size_t)n0 * K : (size_t)n0);
+  size_t aoff[Loop::kL0], woff[Loop::kL1];
+  int ak[Loop::kL0], wk[Loop::kL1];                  // k (in the stage) of the lane's first element
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    ap[q] = in + (size_t)(row0 + min(kc_row(wave, q, lane), rows - 1)) * K + kc_k(lane);
-    if (WT) {
-      wk[q] = kc_k(lane);
-      wp[q] = we + (size_t)(n0 + min(kc_row(wave, q, lane), cols - 1)) * K + wk[q];
-    } else {
-      wk[q] = ks_k(wave, q, lane);
-      wp[q] = we + (size_t)wk[q] * NC + n0 + min(ks_col(wk[q], lane), cols - 4);
-    }
+  for (int q = 0; q < Loop::kL0; ++q) {
+    const int i = Loop::piece0(wave, q);
+    ak[q] = Loop::sub0(wave, q) * FK + Loop::Op0::k(i, lane);
+    aoff[q] = (uint64_t)(uint32_t)min(Loop::Op0::out(i, lane), rows - 1) * (uint32_t)K + ak[q];
   }
-  auto issue = [&](int kt, unsigned lds) {
-    const int k0 = kt * FK;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) f32_load(k0 + kc_k(lane) < K ? ap[q] + k0 : (const float*)&kF32Zero, lds + (wave * 2 + q) * 1024);
+  for (int q = 0; q < Loop::kL1; ++q) {
+    const int i = Loop::piece1(wave, q);
+    wk[q] = Loop::sub1(wave, q) * FK + Loop::Op1::k(i, lane);
+    woff[q] = WT ? (uint64_t)(uint32_t)min(Loop::Op1::out(i, lane), cols - 1) * (uint32_t)K + wk[q]
+                 : (uint64_t)(uint32_t)wk[q] * (uint32_t)NC + min(Loop::Op1::out(i, lane), cols - 4);
+  }
+  constexpr int kStep = Loop::kSub * FK;
+  auto issue = [&](int s, unsigned lds) {
+    const int k0 = s * kStep;
+    const float *ab = a_base + k0, *wb = w_base + (WT ? (size_t)k0 : (size_t)k0 * NC);
+    if (k0 + kStep <= K) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-      f32_load(k0 + wk[q] < K ? wp[q] + (WT ? (size_t)k0 : (size_t)k0 * NC) : (const float*)&kF32Zero,
-               lds + kF32OpBytes + (wave * 2 + q) * 1024);
+      for (int q = 0; q < Loop::kL0; ++q) f32_load(ab + aoff[q], lds + Loop::dst0(wave, q));
+#pragma unroll
+      for (int q = 0; q < Loop::kL1; ++q) f32_load(wb + woff[q], lds + Loop::dst1(wave, q));
+    } else {                                         // past K: zeros
+#pragma unroll
+      for (int q = 0; q < Loop::kL0; ++q) f32_load(k0 + ak[q] < K ? ab + aoff[q] : (const float*)&kF32Zero, lds + Loop::dst0(wave, q));
+#pragma unroll
+      for (int q = 0; q < Loop::kL1; ++q) f32_load(k0 + wk[q] < K ? wb + woff[q] : (const float*)&kF32Zero, lds + Loop::dst1(wave, q));
+    }
   };
-  f32x16 acc;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) acc[q] = 0.f;
-  f32_mainloop<true, WT>((lds_t*)smem, acc, (K + FK - 1) / FK, issue);
+  F32Acc acc;
+  Loop::run((lds_t*)smem, acc, (K + kStep - 1) / kStep, issue);
 
-  const int row = (wave >> 1) * 32 + (lane & 31);
-  if (row >= rows) return;
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const int col = n0 + (wave & 1) * 32 + 8 * g + 4 * (lane >> 5);
-    if (col >= NC) continue;
+  for (int x = 0; x < 4; ++x) {
+    const int i = x >> 1, j = x & 1;
+    const int row = (MT == 2 ? (wave >> 1) * 32 : 0) + i * 16 + (lane & 15);
+    const int col = n0 + (wave & 1) * 32 + j * 16 + 4 * (lane >> 4);
+    if (row >= rows || col >= NC || (MT == 1 && j != (wave >> 1))) continue;
     const size_t o = (size_t)(row0 + row) * NC + col;
     float c[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) c[q] = acc[4 * g + q];
+    for (int q = 0; q < 4; ++q) c[q] = acc[i][j][q];
     if (bias) {
       const float4 b = *(const float4*)(bias + (size_t)e * NC + col);
       c[0] += b.x; c[1] += b.y; c[2] += b.z; c[3] += b.w;
@@ -208,15 +294,21 @@ __global__ __launch_bounds__(kF32Threads, 2) void rows_gemm_f32(const float* __r
 
 // dW_e[m, n] = sum over the vExperts v of e (ascending v), rows p of v: L[p, m] * R[p, n].  The rows of all of the
 // expert's buckets are one contraction: K tile kt holds rows 32 kt .. of the buckets laid behind each other.
+template <int MT>
 __global__ __launch_bounds__(kF32Threads, 2) void wgrad_f32(const float* __restrict__ L, const float* __restrict__ R,
                                                             const int32_t* __restrict__ voff,
                                                             const int32_t* __restrict__ owner, int V, int M, int NC,
                                                             float* __restrict__ dw) {
-  __shared__ __align__(1024) unsigned char smem[kF32Stages * kF32StageBytes];
+  typedef F32Loop<MT, false, false> Loop;
+  __shared__ __align__(1024) unsigned char smem[Loop::kLds];
   __shared__ int s_first[FLEXMOE_MAX_VEXPERTS], s_end[FLEXMOE_MAX_VEXPERTS];      // first row - rows before it, rows up to its end
   __shared__ int s_n;
-  const int e = blockIdx.z;
-  const int m0 = blockIdx.y * FM, n0 = blockIdx.x * FN;
+  // XCD x takes the x-th eighth of every expert's output tiles, cut along the longer side: each half of the operands comes into one L2,
+  // the other into all
+  const int mt = (M + MT * 32 - 1) / (MT * 32), nt = (NC + FN - 1) / FN;
+  const int e = blockIdx.y, t = (int)(blockIdx.x % kF32Xcds * (gridDim.x / kF32Xcds) + blockIdx.x / kF32Xcds);
+  if (t >= mt * nt) return;
+  const int m0 = (mt >= nt ? t / nt : t % mt) * (MT * 32), n0 = (mt >= nt ? t % nt : t / mt) * FN;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (wave == 0) {                  // the expert's non-empty buckets, ascending
     int n = 0, total = 0;
@@ -244,47 +336,121 @@ __global__ __launch_bounds__(kF32Threads, 2) void wgrad_f32(const float* __restr
   __syncthreads();
   const int nb = s_n, T = nb ? s_end[nb - 1] : 0;
 
-  // the wave's loads of a K tile: k rows ks_k(wave, 0) and ks_k(wave, 1); a lane's k rows only grow, so its bucket does too
-  int b[2] = {0, 0};
-  auto issue = [&](int kt, unsigned lds) {
+  constexpr int kStep = Loop::kSub * FK;
+  size_t loff[Loop::kL0], roff[Loop::kL1];           // the lane's loads, from a stage's first row
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int k = ks_k(wave, q, lane), p = kt * FK + k;
+  for (int q = 0; q < Loop::kL0; ++q) {
+    const int i = Loop::piece0(wave, q), k = Loop::sub0(wave, q) * FK + Loop::Op0::k(i, lane);
+    loff[q] = (uint64_t)(uint32_t)k * (uint32_t)M + min(m0 + Loop::Op0::out(i, lane), M - 4);
+  }
+#pragma unroll
+  for (int q = 0; q < Loop::kL1; ++q) {
+    const int i = Loop::piece1(wave, q), k = Loop::sub1(wave, q) * FK + Loop::Op1::k(i, lane);
+    roff[q] = (uint64_t)(uint32_t)k * (uint32_t)NC + min(n0 + Loop::Op1::out(i, lane), NC - 4);
+  }
+  int bu = 0, bu_end = 0, bu_first = 0;              // bucket of a stage's first row
+  if (nb) {
+    bu_end = __builtin_amdgcn_readfirstlane(s_end[0]);
+    bu_first = __builtin_amdgcn_readfirstlane(s_first[0]);
+  }
+  auto issue = [&](int s, unsigned lds) {
+    const int p0 = s * kStep;
+    while (p0 >= bu_end) {
+      ++bu;
+      bu_end = __builtin_amdgcn_readfirstlane(s_end[bu]);
+      bu_first = __builtin_amdgcn_readfirstlane(s_first[bu]);
+    }
+    if (p0 + kStep <= bu_end) {                      // all rows of the stage in one bucket
+      const float *lb = L + (size_t)(bu_first + p0) * M, *rb = R + (size_t)(bu_first + p0) * NC;
+#pragma unroll
+      for (int q = 0; q < Loop::kL0; ++q) f32_load(lb + loff[q], lds + Loop::dst0(wave, q));
+#pragma unroll
+      for (int q = 0; q < Loop::kL1; ++q) f32_load(rb + roff[q], lds + Loop::dst1(wave, q));
+      return;
+    }
+    if (bu == nb - 1) {                              // .. and the end of the last one: zeros
+      const float *lb = L + (size_t)(bu_first + p0) * M, *rb = R + (size_t)(bu_first + p0) * NC;
+      const int left = T - p0;
+#pragma unroll
+      for (int q = 0; q < Loop::kL0; ++q)
+        f32_load(Loop::sub0(wave, q) * FK + Loop::Op0::k(Loop::piece0(wave, q), lane) < left ? lb + loff[q] : (const float*)&kF32Zero,
+                 lds + Loop::dst0(wave, q));
+#pragma unroll
+      for (int q = 0; q < Loop::kL1; ++q)
+        f32_load(Loop::sub1(wave, q) * FK + Loop::Op1::k(Loop::piece1(wave, q), lane) < left ? rb + roff[q] : (const float*)&kF32Zero,
+                 lds + Loop::dst1(wave, q));
+      return;
+    }
+#pragma unroll
+    for (int q = 0; q < Loop::kL0; ++q) {
+      const int i = Loop::piece0(wave, q), p = p0 + Loop::sub0(wave, q) * FK + Loop::Op0::k(i, lane);
       const float* l = (const float*)&kF32Zero;
-      const float* r = l;
       if (p < T) {
-        while (p >= s_end[b[q]]) ++b[q];
-        const size_t row = (size_t)(s_first[b[q]] + p);
-        l = L + row * M + min(m0 + ks_col(k, lane), M - 4);
-        r = R + row * NC + min(n0 + ks_col(k, lane), NC - 4);
+        int b = bu;
+        while (p >= s_end[b]) ++b;
+        l = L + (size_t)(s_first[b] + p) * M + min(m0 + Loop::Op0::out(i, lane), M - 4);
       }
-      f32_load(l, lds + (wave * 2 + q) * 1024);
-      f32_load(r, lds + kF32OpBytes + (wave * 2 + q) * 1024);
+      f32_load(l, lds + Loop::dst0(wave, q));
+    }
+#pragma unroll
+    for (int q = 0; q < Loop::kL1; ++q) {
+      const int i = Loop::piece1(wave, q), p = p0 + Loop::sub1(wave, q) * FK + Loop::Op1::k(i, lane);
+      const float* r = (const float*)&kF32Zero;
+      if (p < T) {
+        int b = bu;
+        while (p >= s_end[b]) ++b;
+        r = R + (size_t)(s_first[b] + p) * NC + min(n0 + Loop::Op1::out(i, lane), NC - 4);
+      }
+      f32_load(r, lds + Loop::dst1(wave, q));
     }
   };
-  f32x16 acc;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) acc[q] = 0.f;
-  f32_mainloop<false, false>((lds_t*)smem, acc, (T + FK - 1) / FK, issue);
+  F32Acc acc;
+  Loop::run((lds_t*)smem, acc, (T + kStep - 1) / kStep, issue);
 
-  const int m = m0 + (wave >> 1) * 32 + (lane & 31);
-  if (m >= M) return;
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const int col = n0 + (wave & 1) * 32 + 8 * g + 4 * (lane >> 5);
-    if (col < NC)
-      *(float4*)(dw + (size_t)e * M * NC + (size_t)m * NC + col) = make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+  for (int x = 0; x < 4; ++x) {
+    const int i = x >> 1, j = x & 1;
+    const int m = m0 + (MT == 2 ? (wave >> 1) * 32 : 0) + i * 16 + (lane & 15);
+    const int col = n0 + (wave & 1) * 32 + j * 16 + 4 * (lane >> 4);
+    if (m < M && col < NC && (MT == 2 || j == (wave >> 1)))
+      *(float4*)(dw + (size_t)e * M * NC + (size_t)m * NC + col) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
   }
 }
 
 static unsigned tiles_of(int n, int t) { return (unsigned)((n + t - 1) / t); }
 
+// 32-row blocks of a workgroup's tile: two (64 x 64 tiles) where there are enough tiles for the chip, else one, with the contraction
+// over two waves.  In us, one and two blocks, by 64 x 64 tiles:
+//   rows products  144 (K 1024) 24.7, 27.9; 576 (K 256) 25.0, 28.1; 672 (K 512) 37, 48; 1088 (K 2048) 198, 217; 1600 (K 512) 89, 89;
+//                  past the line: 2176 (K 256) 72, 66; 4352 (K 512) 221, 208; but 1088 (K 128) 27.9, 26.5
+//   weight gradients, 250 rows per expert and more  128 46, 78; 512 22.4, 26.8 and 63, 87; past the line: 1024 86, 77; 2048 212, 187
+//                     fewer rows (a few K tiles: the sum over two waves is what it costs)  512 13.6, 10.3; 2048 37.8, 22.6
+static int f32_rows_blocks(const FfnArgs& a, int NC) { return (long long)(a.A / 64 + a.E / 2) * tiles_of(NC, FN) >= 1536 ? 2 : 1; }
+static int f32_wgrad_blocks(const FfnArgs& a, int M, int NC) {
+  return (long long)a.E * tiles_of(M, 64) * tiles_of(NC, FN) >= 1024 || a.A < 128 * a.E ? 2 : 1;
+}
+
 template <bool WT, int EPI>
 static void launch_rows_f32(const FfnArgs& a, const void* in, const void* w, const void* bias, int K, int NC, const void* hpre_in,
                             void* out0, void* out1, hipStream_t s) {
-  const dim3 grid((unsigned)(a.A / FM + a.V), tiles_of(NC, FN));      // row tiles: at most one ragged one per bucket
-  hipLaunchKernelGGL((rows_gemm_f32<WT, EPI>), grid, dim3(kF32Threads), 0, s, (const float*)in, (const float*)w,
-                     (const float*)bias, a.voff, a.owner, a.V, K, NC, a.act, (const float*)hpre_in, (float*)out0, (float*)out1);
+  const int mt = f32_rows_blocks(a, NC);
+  // row tiles: at most one ragged one per bucket; an eighth of the tiles per XCD, rounded up
+  const dim3 grid((unsigned)(((long long)(a.A / (mt * 32) + a.V) * tiles_of(NC, FN) / kF32Xcds + 1) * kF32Xcds));
+  if (mt == 2)
+    hipLaunchKernelGGL((rows_gemm_f32<2, WT, EPI>), grid, dim3(kF32Threads), 0, s, (const float*)in, (const float*)w,
+                       (const float*)bias, a.voff, a.owner, a.V, K, NC, a.act, (const float*)hpre_in, (float*)out0, (float*)out1);
+  else
+    hipLaunchKernelGGL((rows_gemm_f32<1, WT, EPI>), grid, dim3(kF32Threads), 0, s, (const float*)in, (const float*)w,
+                       (const float*)bias, a.voff, a.owner, a.V, K, NC, a.act, (const float*)hpre_in, (float*)out0, (float*)out1);
+}
+
+static void launch_wgrad_f32(const FfnArgs& a, const void* L, const void* R, int M, int NC, void* dw, hipStream_t s) {
+  const int mt = f32_wgrad_blocks(a, M, NC);
+  const dim3 grid((tiles_of(NC, FN) * tiles_of(M, mt * 32) + kF32Xcds - 1) / kF32Xcds * kF32Xcds, a.E);
+  if (mt == 2)
+    hipLaunchKernelGGL(wgrad_f32<2>, grid, dim3(kF32Threads), 0, s, (const float*)L, (const float*)R, a.voff, a.owner, a.V, M, NC, (float*)dw);
+  else
+    hipLaunchKernelGGL(wgrad_f32<1>, grid, dim3(kF32Threads), 0, s, (const float*)L, (const float*)R, a.voff, a.owner, a.V, M, NC, (float*)dw);
 }
 
 hipError_t launch_ffn_fwd_f32(const FfnArgs& a, const void* xp, const void* w1, const void* b1, const void* w2,
@@ -307,10 +473,8 @@ hipError_t launch_ffn_bwd_f32(const FfnArgs& a, const void* dyp, const void* xp,
     launch_rows_f32<true, EPI_PLAIN>(a, dhpre, w1, nullptr, a.f, a.d, nullptr, dxp, nullptr, s);
   }
   const float* h = h_kept ? (const float*)h_kept : h_ws;
-  hipLaunchKernelGGL(wgrad_f32, dim3(tiles_of(a.d, FN), tiles_of(a.f, FM), a.E), dim3(kF32Threads), 0, s, h, (const float*)dyp,
-                     a.voff, a.owner, a.V, a.f, a.d, (float*)dw2);
-  hipLaunchKernelGGL(wgrad_f32, dim3(tiles_of(a.f, FN), tiles_of(a.d, FM), a.E), dim3(kF32Threads), 0, s, (const float*)xp,
-                     (const float*)dhpre, a.voff, a.owner, a.V, a.d, a.f, (float*)dw1);
+  launch_wgrad_f32(a, h, dyp, a.f, a.d, dw2, s);
+  launch_wgrad_f32(a, xp, dhpre, a.d, a.f, dw1, s);
   return hipGetLastError();
 }
 

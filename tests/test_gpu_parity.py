@@ -391,6 +391,18 @@ def test_full_backward_reduced_configs(api, name):
     run_full_backward(api, cfg, inp, rep_off, rep_ids, b1=b1, b2=b2)
 
 
+# 64 x 64 and 32 x 64 tiles in either kind of product, ragged in every direction; more buckets than a wave has lanes; buckets that
+# end inside a K tile
+@pytest.mark.parametrize("N,d,f,E,V", [(1600, 136, 2056, 4, 6), (700, 72, 200, 40, 70), (90, 520, 1032, 16, 20), (1500, 64, 96, 3, 9)])
+def test_fp32_tiles(api, N, d, f, E, V):
+    cfg = W.scaled(W.CONFIGS["tiny"], N=N, d=d, f=f, E=E, V=V, k=2, act=W.ACT_GELU_ERF, backward=True, max_rep=4)
+    inp = W.make_layer_inputs(cfg, seed=91)
+    rng = np.random.default_rng(3)
+    b1 = (rng.standard_normal((E, f)) * 0.05).astype(np.float32)
+    b2 = (rng.standard_normal((E, d)) * 0.05).astype(np.float32)
+    run_full_backward(api, cfg, inp, *W.placement_from_loads(np.arange(E, 0, -1), V, 4, shuffle_seed=3), b1=b1, b2=b2)
+
+
 def test_full_backward_is_reproducible(api):
     cfg = SMALL["gpt_small"]
     inp = W.make_layer_inputs(cfg)
