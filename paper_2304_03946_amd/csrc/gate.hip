@@ -5,18 +5,15 @@
 // row operand (32 experts per tile) and 32 tokens as the column operand, hence after the
 // K loop every lane holds half of one token's logits and its partner lane (lane ^ 32) the
 // other half -- the top-k selection is a register scan plus one cross-lane exchange per pick.
-// W_g is first transposed to [E_pad, d_pad] in the workspace (tiny, stays in L2), except in the
-// small-batch kernel with up to 64 experts, which gathers its fragments from W_g as stored.
-// Large batches with up to 64 experts (gate_dma_kernel): every wave owns 32 tokens and the whole contraction; x and
-// W_g^T travel global -> LDS with direct loads that fetch whole 128-byte lines of a row (eight
-// rows per instruction), several 64-wide K tiles in flight per workgroup, and the MFMA fragments
-// are read from LDS.  Otherwise (gate_bf16_kernel): one workgroup per 32 tokens, operands read
-// straight into the MFMA register layout, the contraction split over four waves (or four pairs) and the
-// partial logits summed in a fixed order through LDS.
+// x and W_g travel global -> LDS with direct loads that fetch whole 128-byte lines, and the fragments are read from LDS, those of W_g
+// transposed on the way.
+// From 32768 tokens with up to 64 experts (gate_dma_kernel) every wave owns 32 tokens and the whole contraction, several 64-wide K
+// tiles in flight per workgroup.  Otherwise (gate_quarters_kernel) there is one workgroup per 32 tokens, the contraction split over its
+// four waves and the partial logits summed in a fixed order through LDS.
 // The order of a logit's sum is part of the result: logits that differ by fp32 rounding alone decide a near tie, and with
-// it a token's experts.  Below 32768 tokens, and with more than 64 experts, every kernel adds in quarters: quarter q holds
-// the 64-wide K chunks q, q + 4, .., summed in ascending order, and the logit is q0 + (q1 + (q2 + q3)).  From 32768
-// tokens with up to 64 experts: one sum over all chunks, from a first chunk that depends on the token's workgroup.
+// it a token's experts.  gate_quarters_kernel adds in quarters: quarter q holds
+// the 64-wide K chunks q, q + 4, .., summed in ascending order, and the logit is q0 + (q1 + (q2 + q3)).  gate_dma_kernel: one sum over
+// all chunks, from a first chunk that depends on the token's workgroup.
 //
 // fp32 path: a group of lanes per token, sequential fp32 FMA per logit out of LDS, butterfly arg-max per pick.
 #include <algorithm>
@@ -117,125 +114,6 @@ __device__ __forceinline__ void gate_select_store(f32x16 (&acc)[NT], int t, int 
   }
 }
 
-// One workgroup = 32 tokens.  The contraction is split over four wavefronts (wave w % 4 takes the 64-wide K chunks of
-// quarter w % 4); with G > 1 there are G waves per quarter, each with NT / G of the expert tiles.  Then every partial logit
-// is summed over the quarters through LDS, the pieces dealt to all waves, and wave 0 selects.  What bounds it is the latency
-// of the chunks' round trips, one after another in a wave: where the fragments of W_g are many, a second wave per quarter
-// has half of them to fetch and room for more chunks in flight (launch_gate).
-// DIRECT: `wgt` is W_g itself, [d, E]: a lane gathers the eight values of a fragment with 2-byte
-// loads (stride E) instead of reading a transposed copy -- 32 NT small loads per chunk from a
-// matrix that sits in L2, which saves the launch that writes the copy.  Lanes of experts >= E
-// re-read expert E-1 (their logits are discarded) and rows past d re-read row d-1 (x is zero there).
-template <int NT, int G, bool DIRECT>   // NT tiles of 32 experts, G waves per quarter
-__global__ __launch_bounds__(4 * G * kWave) void gate_bf16_kernel(const bf16_t* __restrict__ x,
-                                                                 const bf16_t* __restrict__ wgt, int N, int d,
-                                                                 int E, int k, int32_t* __restrict__ topk_idx,
-                                                                 float* __restrict__ topk_w) {
-  constexpr int W = 4, NTW = NT / G;                    // quarters; expert tiles of a wave
-  constexpr int kPieces = NT * 4;                       // float4 pieces of a lane's logits
-  __shared__ float4 partial[W][kPieces][kWave];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, quarter = wave % W, r0 = wave / W * NTW;
-  const int j = lane & 31, h = lane >> 5;
-  const int t0 = blockIdx.x * 32;
-
-  f32x16 acc[NTW];
-#pragma unroll
-  for (int r = 0; r < NTW; ++r)
-#pragma unroll
-    for (int n = 0; n < 16; ++n) acc[r][n] = 0.f;
-
-  const bf16_t* xrow = x + (size_t)min(t0 + j, N - 1) * d + 32 * h;   // clamp the ragged last tile
-  const bf16_t* wrow = wgt + (size_t)(r0 * 32 + j) * d + 32 * h;
-  const int nchunks = (d + 63) / 64;
-  // DIRECT: column of W_g for the lane's expert in tile r, at row 32 h
-  const bf16_t* wcol[NTW];
-#pragma unroll
-  for (int r = 0; r < NTW; ++r) wcol[r] = wgt + (size_t)(32 * h) * E + min((r0 + r) * 32 + j, E - 1);
-  auto gather_w = [&](int r, int k0, bool full) -> uint4 {        // W_g[k0 + 32 h + 0..7, expert]
-    Frag f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int kk = full ? k0 + i : min(k0 + i, d - 1 - 32 * h);
-      f.h[i] = wcol[r][(size_t)kk * E];
-    }
-    return f.u;
-  };
-
-  // lane reads k = 64c + 32h + 8s .. +8 of its row for s = 0..3 (64 contiguous bytes); pieces past d are zero
-  auto load_chunk = [&](int c, Frag (&xb)[4], Frag (&wa)[NTW][4]) {
-    if (c * 64 + 64 <= d) {
-#pragma unroll
-      for (int s = 0; s < 4; ++s) xb[s].u = *(const uint4*)(xrow + c * 64 + s * 8);
-#pragma unroll
-      for (int r = 0; r < NTW; ++r)
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-          wa[r][s].u = DIRECT ? gather_w(r, c * 64 + s * 8, true) : *(const uint4*)(wrow + (size_t)r * 32 * d + c * 64 + s * 8);
-    } else {
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const bool ok = c * 64 + 32 * h + s * 8 < d;
-        xb[s].u = ok ? *(const uint4*)(xrow + c * 64 + s * 8) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < NTW; ++r) {
-          if (DIRECT) wa[r][s].u = gather_w(r, c * 64 + s * 8, false);
-          else wa[r][s].u = ok ? *(const uint4*)(wrow + (size_t)r * 32 * d + c * 64 + s * 8) : make_uint4(0, 0, 0, 0);
-        }
-      }
-    }
-  };
-  auto mma_chunk = [&](const Frag (&xb)[4], const Frag (&wa)[NTW][4]) {
-#pragma unroll
-    for (int r = 0; r < NTW; ++r)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[r][s].v, xb[s].v, acc[r], 0, 0, 0);
-  };
-
-  // chunks of loads in flight per wave (register sets used in rotation), as many as the registers hold
-  constexpr int kSets = NTW == 8 ? 1 : NTW == 4 ? 2 : 3;
-  Frag xb[kSets][4], wa[kSets][NTW][4];
-  int c = quarter;
-#pragma unroll
-  for (int q = 0; q < kSets; ++q)
-    if (c + W * q < nchunks) load_chunk(c + W * q, xb[q], wa[q]);
-  for (; c < nchunks; c += W * kSets) {
-#pragma unroll
-    for (int q = 0; q < kSets; ++q)
-      if (c + W * q < nchunks) {
-        mma_chunk(xb[q], wa[q]);
-        if (c + W * (q + kSets) < nchunks) load_chunk(c + W * (q + kSets), xb[q], wa[q]);
-      }
-  }
-
-  // quarter 0 + (1 + (2 + 3)), the pieces dealt to the waves
-#pragma unroll
-  for (int r = 0; r < NTW; ++r)
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      partial[quarter][(r0 + r) * 4 + q][lane] = make_float4(acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]);
-  __syncthreads();
-  for (int i = wave; i < kPieces; i += W * G) {
-    float4 v = partial[W - 1][i][lane];
-#pragma unroll
-    for (int q = W - 2; q >= 0; --q) {
-      const float4 o = partial[q][i][lane];
-      v.x = o.x + v.x; v.y = o.y + v.y; v.z = o.z + v.z; v.w = o.w + v.w;
-    }
-    partial[0][i][lane] = v;
-  }
-  __syncthreads();
-  if (wave != 0) return;
-  f32x16 l[NT];
-#pragma unroll
-  for (int r = 0; r < NT; ++r)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 o = partial[0][r * 4 + q][lane];
-      l[r][4 * q] = o.x; l[r][4 * q + 1] = o.y; l[r][4 * q + 2] = o.z; l[r][4 * q + 3] = o.w;
-    }
-  gate_select_store<NT>(l, t0 + j, N, E, k, topk_idx, topk_w);
-}
-
 // ---------------------------------------------------------------------------------------------
 // Direct-to-LDS gate for up to 64 experts.  One workgroup = WAVES waves x 32 tokens; K tiles of 64
 // through S LDS stages (x tile [32*WAVES][64], W_g^T tile [32*NT][64], rows of 128 bytes whose
@@ -243,8 +121,10 @@ __global__ __launch_bounds__(4 * G * kWave) void gate_bf16_kernel(const bf16_t* 
 // i's 16 bytes at M0 + 16*i, i.e. eight lanes fill one row, so the swizzle is applied by choosing
 // which chunk of the row a lane fetches.  Chunks past d come from a row of zeros (x) or from the
 // zero padding of the transposed weights; token rows past N are clamped (their results are dropped).
-// QUARTERS: one accumulator per quarter of the chunks and gate_bf16_kernel's fragments, so that a token's logits are the
-// same bits in either kernel.
+// STORED: `wgt` is W_g itself, [d, E], E a multiple of four: its K tile is one contiguous piece of memory, transposed on the way out of
+// LDS as in gate_quarters_kernel (no launch that writes a transposed copy: 5 us).
+// S: as many stages as leave room for a second workgroup on a compute unit (65536 x 2048, 64 experts: six stages, one workgroup 49.1,
+// three, two workgroups and no transposing launch 42.6 us; 32768 x 2048 38.7, 26.2).
 // ---------------------------------------------------------------------------------------------
 __device__ const uint4 kGateZeroRow[8] = {};
 typedef __attribute__((address_space(3))) unsigned char gate_lds_t;
@@ -266,7 +146,140 @@ __device__ __forceinline__ void gate_wait_tiles(int tiles) {   // callers keep L
   }
 }
 
-template <int NT, int WAVES, int S, bool QUARTERS>
+// W_g[k0 .. k0 + 7, 32 r + lane % 32] of a K tile as stored ([64][E] in LDS, rows of whole 8-byte pieces); what experts past E get is
+// other rows' values, and past the tile's end the ring's: their logits are discarded.
+__device__ __forceinline__ bf16x8 gate_w_tr(const gate_lds_t* tile, int k0, int r, int E, int lane) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  const gate_lds_t* at = tile + ((k0 + ((lane & 15) >> 2)) * E + r * 32 + (lane & 16) + (lane & 3) * 4) * 2;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(at + 8 * E));
+  return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Quarters kernel: one workgroup per 32 tokens, wave q takes the 64-wide K chunks q, q + 4, ..  A chunk is 32 rows of x (128 bytes
+// each) and 64 rows of W_g as stored, one contiguous piece of memory; both go global -> LDS with direct loads into a ring of S chunks
+// of the wave's own, so nothing waits for another wave and no registers limit what is in flight.  The fragments of W_g are
+// transposed on the way out of LDS, TR: by ds_read_tr16_b64 (rows of W_g are whole 8-byte pieces), else with 2-byte reads.
+// What bounds it: the chunks' trips from L2, S at a time, and for the smallest batches what comes after them (sum over the
+// quarters, selection).  In us, the fragments gathered from global memory with 2-byte loads (more than 64 experts: read from a transposed
+// copy that a launch of its own made), and now; tokens x features, experts:
+//   16 x 1024, 32 6.3, 5.1; 1500 x 1024, 32 7.3, 5.4; 256 x 2048, 64 15.6, 10.0; 8192 x 768, 16 6.5, 5.2; 16384 x 1024, 32 10.9, 6.8;
+//   4096 x 512, 128 14.9, 11.1; 60000 x 2048, 100 183, 85; 4000 x 1024, 256 32.6, 23.1
+// and where the streaming kernel below served fewer than 32768 tokens: 12000 x 2048, 64 23.1, 14.5; 32000 x 512, 64 18.8, 12.3; 30000 x
+// 2048, 32 25.1, 22.1.
+template <int NT, int S, bool TR>
+__global__ __launch_bounds__(4 * kWave) void gate_quarters_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg, int N,
+                                                                  int d, int E, int k, int32_t* __restrict__ topk_idx,
+                                                                  float* __restrict__ topk_w) {
+  constexpr int kXBytes = 32 * 128, kWBytes = NT * 32 * 128, kChunk = kXBytes + kWBytes;
+  constexpr int kWLoads = kWBytes / 1024, L = 4 + kWLoads;
+  constexpr int kPieces = NT * 4;                       // float4 pieces of a lane's logits
+  static_assert((S - 1) * L < 64, "the wait count has six bits");
+  // (the fragments of experts past E reach up to 64 NT bytes past their rows)
+  constexpr int kRing = 4 * S * kChunk, kSums = 4 * kPieces * kWave * 16;
+  __shared__ __align__(1024) unsigned char smem[kRing > kSums ? kRing : kSums];
+  const int lane = threadIdx.x % kWave, q = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int j = lane & 31, h = lane >> 5;
+  const int t0 = blockIdx.x * 32;
+  const int nchunks = (d + 63) / 64, n = (nchunks - q + 3) / 4;      // chunks of the wave
+  const gate_lds_t* const ring = (const gate_lds_t*)smem + q * (S * kChunk);
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)ring);
+
+  // x: instruction i covers rows 8 i .. 8 i + 7, 16-byte pieces XORed with row & 7
+  const int lrow = lane >> 3, lpiece = (lane & 7) ^ lrow;
+  const bf16_t* xsrc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) xsrc[i] = x + (size_t)min(t0 + 8 * i + lrow, N - 1) * d + lpiece * 8;
+  const bf16_t* const zero = (const bf16_t*)kGateZeroRow + (lane & 7) * 8;
+  const long long w_all = (long long)d * E;             // (whole 16-byte pieces: d is a multiple of 8)
+  auto issue = [&](int i) {
+    const int c = q + 4 * i;
+    const unsigned st = lds0 + i % S * kChunk;
+    const bool x_ok = c * 64 + lpiece * 8 < d;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bf16_t* g = x_ok ? xsrc[r] + c * 64 : zero;
+      asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(st + r * 1024) : "memory");
+    }
+    const long long w0 = (long long)c * 64 * E + lane * 8;
+#pragma unroll
+    for (int r = 0; r < kWLoads; ++r) {
+      const long long at = w0 + r * 512;
+      const bf16_t* g = at < w_all ? wg + at : zero;    // past d: zeros, as in x
+      asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(st + kXBytes + r * 1024) : "memory");
+    }
+  };
+
+  f32x16 acc[NT];
+#pragma unroll
+  for (int r = 0; r < NT; ++r)
+#pragma unroll
+    for (int m = 0; m < 16; ++m) acc[r][m] = 0.f;
+#pragma unroll
+  for (int i = 0; i < S; ++i)
+    if (i < n) issue(i);
+  for (int i = 0; i < n; ++i) {
+    gate_wait_tiles<L>(min(S - 1, n - 1 - i));
+    const gate_lds_t* xs = ring + i % S * kChunk;
+    const gate_lds_t* ws = xs + kXBytes;
+    Frag xb[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) xb[s].v = *(const __attribute__((address_space(3))) bf16x8*)(xs + j * 128 + (((s + 4 * h) ^ (j & 7)) << 4));
+#pragma unroll
+    for (int r = 0; r < NT; ++r) {
+      Frag wa[4];                                       // W_g[64 c + 32 h + 8 s + 0..7, 32 r + j]
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        if (TR) {
+          wa[s].v = gate_w_tr(ws, 32 * h + 8 * s, r, E, lane);
+        } else {
+          const gate_lds_t* at = ws + ((32 * h + 8 * s) * E + min(r * 32 + j, E - 1)) * 2;
+#pragma unroll
+          for (int m = 0; m < 8; ++m) wa[s].h[m] = *(const __attribute__((address_space(3))) bf16_t*)(at + m * 2 * E);
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[s].v, xb[s].v, acc[r], 0, 0, 0);
+    }
+    if (i + S < n) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);               // lgkmcnt(0): the slot has been read
+      issue(i + S);
+    }
+  }
+
+  // quarter 0 + (1 + (2 + 3)), the pieces dealt to the waves
+  float4(*partial)[kPieces][kWave] = (float4(*)[kPieces][kWave])smem;
+  __syncthreads();                                      // every wave has left its ring
+#pragma unroll
+  for (int r = 0; r < NT; ++r)
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+      partial[q][r * 4 + m][lane] = make_float4(acc[r][4 * m], acc[r][4 * m + 1], acc[r][4 * m + 2], acc[r][4 * m + 3]);
+  __syncthreads();
+  for (int i = q; i < kPieces; i += 4) {
+    float4 v = partial[3][i][lane];
+#pragma unroll
+    for (int m = 2; m >= 0; --m) {
+      const float4 o = partial[m][i][lane];
+      v.x = o.x + v.x; v.y = o.y + v.y; v.z = o.z + v.z; v.w = o.w + v.w;
+    }
+    partial[0][i][lane] = v;
+  }
+  __syncthreads();
+  if (q != 0) return;
+  f32x16 l[NT];
+#pragma unroll
+  for (int r = 0; r < NT; ++r)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const float4 o = partial[0][r * 4 + m][lane];
+      l[r][4 * m] = o.x; l[r][4 * m + 1] = o.y; l[r][4 * m + 2] = o.z; l[r][4 * m + 3] = o.w;
+    }
+  gate_select_store<NT>(l, t0 + j, N, E, k, topk_idx, topk_w);
+}
+
+template <int NT, int WAVES, int S, bool STORED>
 __global__ __launch_bounds__(WAVES * kWave) void gate_dma_kernel(const bf16_t* __restrict__ x,
                                                                  const bf16_t* __restrict__ wgt, int N, int d,
                                                                  int dpad, int E, int k,
@@ -294,15 +307,16 @@ __global__ __launch_bounds__(WAVES * kWave) void gate_dma_kernel(const bf16_t* _
 #pragma unroll
   for (int q = 0; q < kWLoads; ++q) {
     const int instr = min(q * WAVES + wave, NT * 4 - 1);      // surplus slots repeat the last instruction (same bytes)
-    wsrc[q] = wgt + (size_t)(instr * 8 + lrow) * dpad + lchunk * 8;
+    wsrc[q] = STORED ? wgt + instr * 512 + lane * 8 : wgt + (size_t)(instr * 8 + lrow) * dpad + lchunk * 8;
   }
+  const long long w_all = (long long)d * E;
   const bf16_t* zsrc = (const bf16_t*)kGateZeroRow + (lane & 7) * 8;
   const unsigned lds_base = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(gate_lds_t*)smem);
 
   // Workgroups start their contraction at different K tiles and wrap around, so that the requests in flight on the
   // chip are not all at the same column offset of their rows (measured: -7 % on 65536 tokens x 2048 features).
   // The order of a token's sum then depends on its workgroup, i.e. on the token's index only: still reproducible.
-  const int kshift = QUARTERS ? 0 : (int)((blockIdx.x * 5u) % (unsigned)KT);
+  const int kshift = (int)((blockIdx.x * 5u) % (unsigned)KT);
   auto issue = [&](int kt) {
     const unsigned st = lds_base + (kt % S) * kStage;
     const int ktr = kt + kshift < KT ? kt + kshift : kt + kshift - KT;
@@ -316,57 +330,46 @@ __global__ __launch_bounds__(WAVES * kWave) void gate_dma_kernel(const bf16_t* _
 #pragma unroll
     for (int q = 0; q < kWLoads; ++q) {
       const int instr = min(q * WAVES + wave, NT * 4 - 1);
-      const bf16_t* g = wsrc[q] + k0;
+      const bf16_t* g;
+      if (STORED) g = (long long)k0 * E + instr * 512 + lane * 8 < w_all ? wsrc[q] + (size_t)k0 * E : zsrc;      // past d: zeros
+      else g = wsrc[q] + k0;
       asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(st + kXBytes + instr * 1024) : "memory");
     }
   };
 
-  constexpr int Q = QUARTERS ? 4 : 1;
-  f32x16 acc[Q][NT];
+  f32x16 acc[NT];
 #pragma unroll
-  for (int q = 0; q < Q; ++q)
+  for (int r = 0; r < NT; ++r)
 #pragma unroll
-    for (int r = 0; r < NT; ++r)
-#pragma unroll
-      for (int n = 0; n < 16; ++n) acc[q][r][n] = 0.f;
+    for (int n = 0; n < 16; ++n) acc[r][n] = 0.f;
 
 #pragma unroll
   for (int p = 0; p < S - 1; ++p)
     if (p < KT) issue(p);
-  for (int kt0 = 0; kt0 < KT; kt0 += Q) {
+  for (int kt = 0; kt < KT; ++kt) {
+    // tile kt has landed once at most the younger tiles are still in flight
+    gate_wait_tiles<L>(min(S - 2, KT - 1 - kt));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    if (kt + S - 1 < KT) issue(kt + S - 1);                   // into the stage every wave has just left
+    const gate_lds_t* xs = (const gate_lds_t*)smem + (kt % S) * kStage + wave * 32 * 128;
+    const gate_lds_t* wsm = (const gate_lds_t*)smem + (kt % S) * kStage + kXBytes;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int kt = kt0 + q;
-      if (kt >= KT) break;
-      // tile kt has landed once at most the younger tiles are still in flight
-      gate_wait_tiles<L>(min(S - 2, KT - 1 - kt));
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-      if (kt + S - 1 < KT) issue(kt + S - 1);                   // into the stage every wave has just left
-      const gate_lds_t* xs = (const gate_lds_t*)smem + (kt % S) * kStage + wave * 32 * 128;
-      const gate_lds_t* wsm = (const gate_lds_t*)smem + (kt % S) * kStage + kXBytes;
+    for (int ks = 0; ks < kGateDK / 16; ++ks) {
+      const int chunk = ((2 * ks + h) ^ (j & 7)) << 4;
+      Frag xb;
+      xb.v = *(const __attribute__((address_space(3))) bf16x8*)(xs + j * 128 + chunk);
 #pragma unroll
-      for (int ks = 0; ks < kGateDK / 16; ++ks) {
-        const int chunk = ((QUARTERS ? ks + 4 * h : 2 * ks + h) ^ (j & 7)) << 4;
-        Frag xb;
-        xb.v = *(const __attribute__((address_space(3))) bf16x8*)(xs + j * 128 + chunk);
-#pragma unroll
-        for (int r = 0; r < NT; ++r) {
-          Frag wa;
-          wa.v = *(const __attribute__((address_space(3))) bf16x8*)(wsm + (r * 32 + j) * 128 + chunk);
-          acc[q][r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa.v, xb.v, acc[q][r], 0, 0, 0);
-        }
+      for (int r = 0; r < NT; ++r) {
+        Frag wa;
+        if (STORED) wa.v = gate_w_tr(wsm, 16 * ks + 8 * h, r, E, lane);
+        else wa.v = *(const __attribute__((address_space(3))) bf16x8*)(wsm + (r * 32 + j) * 128 + chunk);
+        acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa.v, xb.v, acc[r], 0, 0, 0);
       }
     }
   }
-  f32x16 l[NT];
-#pragma unroll
-  for (int r = 0; r < NT; ++r)
-#pragma unroll
-    for (int n = 0; n < 16; ++n)
-      l[r][n] = QUARTERS ? acc[0][r][n] + (acc[1 % Q][r][n] + (acc[2 % Q][r][n] + acc[3 % Q][r][n])) : acc[0][r][n];
-  if (t0 < N) gate_select_store<NT>(l, t0 + j, N, E, k, topk_idx, topk_w);
+  if (t0 < N) gate_select_store<NT>(acc, t0 + j, N, E, k, topk_idx, topk_w);
 }
 
 // fp32: LPT lanes per token, lane l of a token's group owns experts l, l + LPT, ... (LPT = the experts rounded up to a
@@ -464,18 +467,6 @@ __global__ __launch_bounds__(kGateThreads) void gate_f32_kernel(const float* __r
   }
 }
 
-// From which size the streaming kernel is ahead: where the split-K kernel needs another round.  Its registers leave a compute
-// unit one workgroup with 33 to 64 experts (8192 tokens a round), three below (24576; the second workgroup of a compute unit
-// already costs as much as streaming from 2048 features on).  Below 256 features the launch that transposes W_g eats it up.  In us,
-// split-K and streaming, tokens x features:
-//   64 experts: 9000 x 64 7.6, 6.8; 9000 x 2048 30.8, 22.5; 17000 x 1024 26.6, 25.1; 32000 x 64 14.1, 10.3; but 17000 x 512 17.3, 17.2
-//   32 experts: 25000 x 256 7.4, 7.1; 25000 x 1024 17.1, 13.4; 32000 x 512 11.5, 9.5; 17000 x 2048 22.2, 20.2;
-//               past the line: 25000 x 128 6.1, 6.2; 32000 x 64 5.7, 5.9; 17000 x 1024 12.7, 12.9; 20000 x 512 7.8, 10.1; 17000 x 64 4.3, 5.7
-static bool gate_streams(int N, int d, int nt) {
-  if (nt > 2) return false;
-  return N >= 32768 || (nt == 2 ? N > 8192 : d >= 2048 ? N > 16384 : d >= 256 && N > 24576);
-}
-
 hipError_t launch_gate(const void* x, const void* wg, int N, int d, int E, int k, int dtype, int32_t* idx, float* w,
                        void* ws, hipStream_t s) {
   if (N == 0) return hipSuccess;
@@ -496,46 +487,50 @@ hipError_t launch_gate(const void* x, const void* wg, int N, int d, int E, int k
   const int epad = nt * 32;
   bf16_t* wgt = (bf16_t*)ws;
   const bf16_t* xb = (const bf16_t*)x;
-  if (gate_streams(N, d, nt)) {
-    // large batches: direct-to-LDS streaming, four waves (two below 65536 tokens) share a weight tile
+  if (N >= 32768 && nt <= 2) {
+    // direct-to-LDS streaming, four waves (two below 65536 tokens) share a weight tile
     const int dpad = gate_dpad(d);
-    hipLaunchKernelGGL(gate_transpose_wg_kernel, dim3((dpad + 255) / 256, epad), dim3(256), 0, s, (const bf16_t*)wg, d,
-                       E, epad, dpad, wgt);
-#define FLEXMOE_GATE_LAUNCH(NT_, WAVES_, S_, Q_)                                                                   \
-  hipLaunchKernelGGL((gate_dma_kernel<NT_, WAVES_, S_, Q_>), dim3((N + 32 * WAVES_ - 1) / (32 * WAVES_)),            \
-                     dim3(WAVES_* kWave), 0, s, xb, wgt, N, d, dpad, E, k, idx, w)
+    const bool stored = E % 4 == 0;
+    if (!stored)
+      hipLaunchKernelGGL(gate_transpose_wg_kernel, dim3((dpad + 255) / 256, epad), dim3(256), 0, s, (const bf16_t*)wg, d,
+                         E, epad, dpad, wgt);
+#define FLEXMOE_GATE_LAUNCH(NT_, WAVES_, S_)                                                                        \
+  if (stored)                                                                                                       \
+    hipLaunchKernelGGL((gate_dma_kernel<NT_, WAVES_, S_, true>), dim3((N + 32 * WAVES_ - 1) / (32 * WAVES_)),        \
+                       dim3(WAVES_* kWave), 0, s, xb, (const bf16_t*)wg, N, d, dpad, E, k, idx, w);                 \
+  else                                                                                                              \
+    hipLaunchKernelGGL((gate_dma_kernel<NT_, WAVES_, S_, false>), dim3((N + 32 * WAVES_ - 1) / (32 * WAVES_)),       \
+                       dim3(WAVES_* kWave), 0, s, xb, wgt, N, d, dpad, E, k, idx, w)
     if (N >= 65536) {
-      if (nt == 1) FLEXMOE_GATE_LAUNCH(1, 4, 6, false);
-      else FLEXMOE_GATE_LAUNCH(2, 4, 6, false);
-    } else if (N >= 32768) {
-      if (nt == 1) FLEXMOE_GATE_LAUNCH(1, 2, 6, false);
-      else FLEXMOE_GATE_LAUNCH(2, 2, 6, false);
+      if (nt == 1) { FLEXMOE_GATE_LAUNCH(1, 4, 4); }
+      else { FLEXMOE_GATE_LAUNCH(2, 4, 3); }
     } else {
-      if (nt == 1) FLEXMOE_GATE_LAUNCH(1, 2, 6, true);
-      else FLEXMOE_GATE_LAUNCH(2, 2, 6, true);
+      if (nt == 1) { FLEXMOE_GATE_LAUNCH(1, 2, 6); }
+      else { FLEXMOE_GATE_LAUNCH(2, 2, 5); }
     }
 #undef FLEXMOE_GATE_LAUNCH
     return hipGetLastError();
   }
-  // small batches (a few waves per compute unit at most) and more than 64 experts: split-K kernel.
-  // Two waves per quarter with 33 to 64 experts and several rounds of chunks (one, two; us; 64 experts): 256 x 2048 20.6,
-  // 15.6; 12000 x 2048 49.8, 32.9; 32000 x 1024 42.5, 36.2; but 16000 x 512 13.2, 13.4.  With more experts two waves lose what the
-  // smaller fragments win: 4096 x 1024, 128 experts 19.6, 20.7; 2000 x 2048, 100 experts 26.3, 29.2.
+  // One chunk per wave and ring where that is all there is, or where more workgroups than compute units (8192 tokens) hide each other's
+  // trips; else as many as fit.  In us, one chunk and more: 9000 x 2048, 64 13.6, 19.7; 16500 x 1024, 64 11.9, 19.8; 32000 x 1024, 32 13.4,
+  // 14.6; 20000 x 512, 128 17.6, 23.8; at most 8192 tokens the same or fewer with more chunks (4096 x 512, 128 11.2, 11.1).
   const dim3 grid((N + 31) / 32);
-  const int g = d >= 512 && nt == 2 ? 2 : 1;
-  const bool direct = nt <= 2;      // the fragments of W_g are gathered from the matrix as stored (one launch)
-  if (!direct)
-    hipLaunchKernelGGL(gate_transpose_wg_kernel, dim3((d + 255) / 256, epad), dim3(256), 0, s, (const bf16_t*)wg, d, E, epad, d, wgt);
-  const bf16_t* wgb = direct ? (const bf16_t*)wg : wgt;
-#define FLEXMOE_GATE_LAUNCH(NT_, G_, DIRECT_) \
-  hipLaunchKernelGGL((gate_bf16_kernel<NT_, G_, DIRECT_>), grid, dim3(4 * G_ * kWave), 0, s, xb, wgb, N, d, E, k, idx, w)
-  switch (nt * 10 + g) {
-    case 11: FLEXMOE_GATE_LAUNCH(1, 1, true); break;
-    case 21: FLEXMOE_GATE_LAUNCH(2, 1, true); break;
-    case 22: FLEXMOE_GATE_LAUNCH(2, 2, true); break;
-    case 41: FLEXMOE_GATE_LAUNCH(4, 1, false); break;
-    default: FLEXMOE_GATE_LAUNCH(8, 1, false); break;
-  }
+  const bool one = d <= 256 || N > 8192;
+#define FLEXMOE_GATE_LAUNCH(NT_, S_)                                                                                                     \
+  if (E % 4 == 0)                                                                                                                        \
+    hipLaunchKernelGGL((gate_quarters_kernel<NT_, S_, true>), grid, dim3(4 * kWave), 0, s, xb, (const bf16_t*)wg, N, d, E, k, idx, w);   \
+  else                                                                                                                                   \
+    hipLaunchKernelGGL((gate_quarters_kernel<NT_, S_, false>), grid, dim3(4 * kWave), 0, s, xb, (const bf16_t*)wg, N, d, E, k, idx, w)
+  if (nt == 1) {
+    if (one) { FLEXMOE_GATE_LAUNCH(1, 1); }
+    else { FLEXMOE_GATE_LAUNCH(1, 4); }
+  } else if (nt == 2) {
+    if (one) { FLEXMOE_GATE_LAUNCH(2, 1); }
+    else { FLEXMOE_GATE_LAUNCH(2, 3); }
+  } else if (nt == 4) {
+    if (one) { FLEXMOE_GATE_LAUNCH(4, 1); }
+    else { FLEXMOE_GATE_LAUNCH(4, 2); }
+  } else { FLEXMOE_GATE_LAUNCH(8, 1); }
 #undef FLEXMOE_GATE_LAUNCH
   return hipGetLastError();
 }

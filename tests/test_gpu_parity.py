@@ -745,6 +745,13 @@ def _route_only(api, idx_np, E, rep_off, rep_ids):
     return {n: t.cpu().numpy() for n, t in out.items()}
 
 
+# chunks per wave 0, 1 and several, with a ring of one and of more; W_g in rows of whole 8-byte pieces or not; both kernels
+@pytest.mark.parametrize("N,d,E,k", [(8193, 520, 6, 2), (8192, 1032, 30, 2), (300, 1096, 61, 2), (8193, 776, 44, 2), (100, 520, 201, 2),
+                                     (200, 1032, 128, 1), (33, 64, 12, 2), (40000, 136, 31, 2), (65537, 72, 62, 2)])
+def test_gate_rings(api, N, d, E, k):
+    test_gate_alone_shapes(api, N, d, E, k)
+
+
 @pytest.mark.parametrize("case", ["one_expert", "fewer_tokens_than_replicas", "k_equals_E", "ragged_unit", "max_sizes"])
 def test_route_adversarial(api, case):
     rng = np.random.default_rng(12)
