@@ -29,6 +29,7 @@
 //    spread between the MFMAs of the current one, and one LDS-only barrier per K tile orders
 //    stage reuse.  What bounds the K loop is the energy of bringing the operands into LDS (the stripped loop
 //    without its direct loads runs 27-41 % faster on random operands, 9-18 % on constant ones: csrc/probe).
+//    (Weight gradients with few rows per expert or few output tiles: 128 x 128 tiles, ffn_bf16_wgrad_small.h.)
 //  * register-staged (rows_gemm_bf16; rows products with any other K that is a multiple of 8): 64-wide K
 //    tiles through registers into two LDS stages, strided operands transposed 8x8 in registers.
 //
@@ -49,7 +50,8 @@
 // Layout of the sources: ffn_bf16_tile.h (tile mapping, fragments, activation tables, epilogues, the
 // register-staged kernel), ffn_bf16_dma.h (direct-to-LDS pipeline, one rows tile on it),
 // ffn_bf16_persist.h (persistent rows kernels and their row-tile table), ffn_bf16_small.h (rows kernels for few rows
-// and their plan), ffn_bf16_wgrad.h (weight-gradient plan and kernels); this file holds the host side.
+// and their plan), ffn_bf16_wgrad.h (weight-gradient plan and kernels), ffn_bf16_wgrad_small.h (128 x 128 weight-gradient tiles); this
+// file holds the host side.
 #include <algorithm>
 
 #include "common.h"
@@ -58,6 +60,7 @@
 #include "ffn_bf16_persist.h"
 #include "ffn_bf16_small.h"
 #include "ffn_bf16_wgrad.h"
+#include "ffn_bf16_wgrad_small.h"
 
 namespace flexmoe {
 
@@ -87,6 +90,21 @@ static int wgrad_seg_tiles(int A, int d, int f) {
 static int wgrad_extra_segments(int A, int V, int seg_tiles) { return seg_tiles ? (A / DK + V) / seg_tiles : 0; }
 static int wgrad_partial_slots(int A, int V, int seg_tiles) { return seg_tiles ? 2 * ((A / DK + V) / seg_tiles) + 1 : 0; }
 
+// Whether a call's weight gradients go to the 128 x 128 tiles of wgrad_gemm_small_bf16, three workgroups per compute unit, instead of
+// the 256 x 256 ones (half the operand traffic per product, but one workgroup per compute unit, whose look-ups, first loads and
+// stores have nothing beside them).  Whole backward passes, f = 4 d unless given, us, 256 and 128:
+//  * the gradient of an expert is at most four 256 x 256 tiles: d 64, E 8, 60000 rows 139, 103; d 128, E 16, 131072 rows 339, 302; d 192, E 12,
+//    10000 rows 115, 87, 131072 rows 516, 492; d 256, E 8, 3200 rows 97, 66, 80000 rows 407, 401;
+//  * the small tiles cover at most 0.8 of what the large ones do (d 320, 384): d 384, E 12, 24000 rows 286, 259, 120000 rows 970, 916; 0.83
+//    (d 640) is past the line: 60000 rows 1060, 1062;
+//  * up to 112 rows per expert: d 1024, E 32, 32 rows 308, 280, 94 rows 382, 366; d 2048, E 64, 32 rows 1896, 1846, 96 rows 2426, 2410;
+//    past the line: 160 rows 470, 477 and 2578, 2684;
+//  * an even share of at most 20 K tiles x output tiles per compute unit: d 512, E 32 (share 16) 249, 230; d 1024, f 2048, E 8 (20) 206, 190;
+//    d 512, f 1024, E 128 (20) 372, 344; past the line: d 512, E 32 (25) 291, 302; d 1024, f 2048, E 8 (31) 276, 283; f 1024, E 128 (32) 428, 434.
+static bool wgrad_small(int A, int d, int f, int E) {
+  const long long large = (long long)((d + BM - 1) / BM) * ((f + BN - 1) / BN), small = (long long)((d + GT - 1) / GT) * ((f + GT - 1) / GT);
+  return large <= 4 || 5 * small <= 16 * large || A <= 112ll * E || A / DK * large <= 20 * kComputeUnits;
+}
 static int wgrad_seg_rows_max(int A, int d, int f, int E, int V) { return E + wgrad_extra_segments(A, V, wgrad_seg_tiles(A, d, f)); }
 
 static int max_row_tiles(int A, int V) { return A / BM + V; }
@@ -336,7 +354,8 @@ static hipError_t launch_rows(const FfnArgs& a, const void* in, const void* w, c
 // product: 0 = dW2 (M = f, NC = d), 1 = dW1 (M = d, NC = f): which of the plan's two work lists it reads.
 static WgradDmaArgs wgrad_dma_args(const FfnArgs& a, const void* L, const void* R, int M, int NC, void* dw,
                                    void* ws_tail, void* ws, unsigned* grid, int product) {
-  const int m_tiles = (M + BM - 1) / BM, n_tiles = (NC + BN - 1) / BN;
+  const int edge = wgrad_small(a.A, a.d, a.f, a.E) ? GT : BM;
+  const int m_tiles = (M + edge - 1) / edge, n_tiles = (NC + edge - 1) / edge;
   const int seg_tiles = wgrad_seg_tiles(a.A, a.d, a.f);
   float* partial = seg_tiles ? (float*)ws_tail : nullptr;
   const int seg_rows_max = wgrad_seg_rows_max(a.A, a.d, a.f, a.E, a.V);
@@ -352,7 +371,7 @@ static void launch_bwd_plan(const FfnArgs& a, void* ws, hipStream_t s) {
   const int seg_rows_max = wgrad_seg_rows_max(a.A, a.d, a.f, a.E, a.V);
   const int row_blocks = a.A > 0 ? plan_blocks(a) : 0;
   const int f_tiles = (a.f + BM - 1) / BM, d_tiles = (a.d + BM - 1) / BM;
-  const bool whole = a.f % BM == 0 && a.d % BN == 0;
+  const bool whole = a.f % BM == 0 && a.d % BN == 0 && !wgrad_small(a.A, a.d, a.f, a.E);
   hipLaunchKernelGGL(ffn_bwd_plan_kernel, dim3(1 + row_blocks), dim3(kGemmThreads), 0, s, a.voff, a.owner, a.E, a.V,
                      wgrad_seg_tiles(a.A, a.d, a.f), seg_rows_max,
                      wgrad_plan_at(wgrad_plan_ws(a, ws), seg_rows_max, a.E, a.V, 0),
@@ -361,22 +380,35 @@ static void launch_bwd_plan(const FfnArgs& a, void* ws, hipStream_t s) {
                      whole ? wgrad_balance_geometry(d_tiles, f_tiles) : WgradBalance{1, 1}, rows_tab_ws(a, ws), small_plan_ws(a, ws));
 }
 
-static void launch_wgrad_reduce(const FfnArgs& a, const WgradDmaArgs& g, hipStream_t s) {
-  if (!g.seg_tiles) return;
-  const int blocks = (int)std::min<size_t>(((size_t)g.M * g.NC / 4 + kGemmThreads - 1) / kGemmThreads, 2048);
-  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(blocks, a.E), dim3(kGemmThreads), 0, s, (const int4*)g.plan.table, g.M, g.NC,
-                     (const float*)g.partial, g.dw);
+// Sums of the partial tiles of `n` products (their [M, NC] have the same number of elements).
+static void launch_wgrad_reduce(const FfnArgs& a, const WgradDmaArgs* g, int n, hipStream_t s) {
+  if (!g->seg_tiles) return;
+  const size_t elems = (size_t)g->M * g->NC;
+  const int blocks = (int)std::min<size_t>((elems / 4 + kGemmThreads - 1) / kGemmThreads, 2048);
+  const WgradReduceArgs r{(const int4*)g->plan.table, {{g[0].partial, g[0].dw}, {g[n - 1].partial, g[n - 1].dw}}};
+  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(blocks, a.E, n), dim3(kGemmThreads), 0, s, r, elems);
 }
 
-static hipError_t launch_wgrad(const FfnArgs& a, const void* L, const void* R, int M, int NC, void* dw, void* ws_tail,
-                               void* ws, hipStream_t s, int product) {
-  unsigned grid;
-  const WgradDmaArgs g = wgrad_dma_args(a, L, R, M, NC, dw, ws_tail, ws, &grid, product);
-  if (M % BM == 0 && NC % BN == 0)      // whole output tiles: one persistent workgroup per compute unit
-    hipLaunchKernelGGL(wgrad_gemm_persist_bf16, dim3(std::min(grid, (unsigned)kComputeUnits)), dim3(kDmaThreads), 0, s, g);
-  else
-    hipLaunchKernelGGL(wgrad_gemm_dma_bf16, dim3(grid), dim3(kDmaThreads), 0, s, g);
-  launch_wgrad_reduce(a, g, s);
+// dW2 = H^T . dYp, dW1 = Xp^T . dHpre: each with its own partial tiles.
+static hipError_t launch_wgrads(const FfnArgs& a, const void* h, const void* dyp, void* dw2, const void* xp, const void* dhpre,
+                                void* dw1, void* ws, hipStream_t s) {
+  void* tail2 = (char*)ws + 2 * align_up((size_t)a.A * a.f * sizeof(bf16_t), 256);
+  void* tail1 = (char*)tail2 + wgrad_tail_bytes(a.A, a.d, a.f, a.V);
+  unsigned grid[2];
+  const WgradDmaArgs g[2] = {wgrad_dma_args(a, h, dyp, a.f, a.d, dw2, tail2, ws, &grid[0], 0),
+                             wgrad_dma_args(a, xp, dhpre, a.d, a.f, dw1, tail1, ws, &grid[1], 1)};
+  if (wgrad_small(a.A, a.d, a.f, a.E)) {
+    hipLaunchKernelGGL(wgrad_gemm_small_bf16, dim3(grid[0] + grid[1]), dim3(kGradThreads), 0, s, WgradSmallArgs{{g[0], g[1]}, grid[0]});
+    launch_wgrad_reduce(a, g, 2, s);
+    return hipGetLastError();
+  }
+  for (int i = 0; i < 2; ++i) {
+    if (a.f % BM == 0 && a.d % BN == 0)      // whole output tiles: one persistent workgroup per compute unit
+      hipLaunchKernelGGL(wgrad_gemm_persist_bf16, dim3(std::min(grid[i], (unsigned)kComputeUnits)), dim3(kDmaThreads), 0, s, g[i]);
+    else
+      hipLaunchKernelGGL(wgrad_gemm_dma_bf16, dim3(grid[i]), dim3(kDmaThreads), 0, s, g[i]);
+    launch_wgrad_reduce(a, &g[i], 1, s);
+  }
   return hipGetLastError();
 }
 
@@ -437,20 +469,15 @@ hipError_t launch_ffn_bwd_bf16(const FfnArgs& a, const void* dyp, const void* xp
                  : launch_rows<true, EPI_DH>(a, dyp, w2, nullptr, a.d, a.f, hpre, dhpre, h_ws, ws, s);
     if (err != hipSuccess) return err;
   }
-  // dW2 = H^T . dYp, dW1 = Xp^T . dHpre: each with its own partial tiles.  (One launch for dXp, dW2 and dW1, which
-  // filled the partly empty last rounds of the three grids, was measured against three persistent launches: the
-  // latter are 2 % faster on the GPT-medium-like backward pass and 4.5 % on the Swin-like one.)
-  void* ws_tail2 = (char*)ws + 2 * align_up((size_t)a.A * a.f * sizeof(bf16_t), 256);
-  void* ws_tail1 = (char*)ws_tail2 + wgrad_tail_bytes(a.A, a.d, a.f, a.V);
   if (a.A > 0) {
     // dXp = dHpre . W1^T; W1_e is [d, f], contraction index f contiguous
     err = launch_rows<true, EPI_PLAIN>(a, dhpre, w1, nullptr, a.f, a.d, nullptr, dxp, nullptr, ws, s, nullptr, 1,
                                        rows_split_ws(a, ws), scatter_src);
     if (err != hipSuccess) return err;
   }
-  err = launch_wgrad(a, h, dyp, a.f, a.d, dw2, ws_tail2, ws, s, 0);
-  if (err != hipSuccess) return err;
-  return launch_wgrad(a, xp, dhpre, a.d, a.f, dw1, ws_tail1, ws, s, 1);
+  // (One launch for dXp, dW2 and dW1, which filled the partly empty last rounds of the three grids of 256 x 256 tiles, was measured
+  // against three persistent launches: the latter are 2 % faster on the GPT-medium-like backward pass and 4.5 % on the Swin-like one.)
+  return launch_wgrads(a, h, dyp, dw2, xp, dhpre, dw1, ws, s);
 }
 
 }  // namespace flexmoe

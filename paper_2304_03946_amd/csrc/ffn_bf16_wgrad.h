@@ -671,15 +671,20 @@ __global__ __launch_bounds__(kDmaThreads) void wgrad_gemm_persist_bf16(const Wgr
 }
 
 // dW_e = sum of the expert's partial tiles in segment order, for the experts that were split.
-// Grid: (element blocks of the [M, NC] matrix, load rank); `table` as left by the GEMM kernel.
-__global__ __launch_bounds__(kGemmThreads) void wgrad_reduce_kernel(const int4* __restrict__ table, int M, int NC,
-                                                                    const float* __restrict__ partial,
-                                                                    bf16_t* __restrict__ dw) {
-  const int4 t = table[blockIdx.y];             // {expert, segments, first slot}
+// Grid: (element blocks of the [M, NC] matrix, load rank, product); `table` as left by the plan.
+struct WgradReduceArgs {
+  const int4* table;
+  struct {
+    const float* partial;
+    bf16_t* dw;
+  } p[2];
+};
+__global__ __launch_bounds__(kGemmThreads) void wgrad_reduce_kernel(const WgradReduceArgs a, size_t elems) {
+  const int4 t = a.table[blockIdx.y];           // {expert, segments, first slot}
   if (t.y <= 1) return;
-  const size_t n4 = (size_t)M * NC / 4;
-  const float4* p = (const float4*)(partial + (size_t)t.z * M * NC);
-  uint2* out = (uint2*)(dw + (size_t)t.x * M * NC);
+  const size_t n4 = elems / 4;
+  const float4* p = (const float4*)(a.p[blockIdx.z].partial + (size_t)t.z * elems);
+  uint2* out = (uint2*)(a.p[blockIdx.z].dw + (size_t)t.x * elems);
   for (size_t i = (size_t)blockIdx.x * kGemmThreads + threadIdx.x; i < n4; i += (size_t)gridDim.x * kGemmThreads) {
     float4 s4 = p[i];
     for (int sgm = 1; sgm < t.y; ++sgm) {

@@ -262,7 +262,16 @@ BANDS = {
     "bands": W.scaled(W.CONFIGS["gpt_m"], N=900, d=264, f=1144, E=4, V=6, max_rep=3),
     "bands_many": W.scaled(W.CONFIGS["gpt_m"], N=2600, d=256, f=2304, E=4, V=6, max_rep=3),
 }
+# weight gradients on either side of the line between 128 x 128 and 256 x 256 tiles: one chunk of columns and buckets shorter than a K
+# tile, experts without tokens; ragged tiles and segments; past the line ragged, and whole with balanced work lists and segments
+GRADS = {
+    "grads_least": W.scaled(W.CONFIGS["gpt_m"], N=17, d=8, f=16, E=24, V=30, max_rep=4),
+    "grads_ragged": W.scaled(W.CONFIGS["gpt_m"], N=2500, d=136, f=1160, E=5, V=8, max_rep=4),
+    "grads_ragged_many": W.scaled(W.CONFIGS["gpt_m"], N=10500, d=392, f=1000, E=6, V=9, max_rep=4),
+    "grads_balance_many": W.scaled(SMALL["wgrad_balance"], N=10500),
+}
 SMALL.update(BANDS)
+SMALL.update(GRADS)
 SMALL.update(MANY)
 
 
