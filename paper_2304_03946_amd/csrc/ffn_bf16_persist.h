@@ -186,7 +186,7 @@ __global__ __launch_bounds__(kDmaThreads) void rows_gemm_persist_bf16(const Rows
   __shared__ __align__(1024) unsigned char stage2[kDmaStageBytes];
   __shared__ __align__(1024) unsigned char stage3[kDmaStageBytes];
   constexpr bool kLut = epilogue_uses_lut<EPI, ACT>();
-  __shared__ __align__(1024) unsigned char lut_lds[kLut ? kLutBytes : 16];
+  __shared__ __align__(1024) unsigned char lut_lds[kLut ? lut_lds_bytes<EPI>() : 16];
   __shared__ int smap_lds[EPI == EPI_PLAIN ? BM : 1];
   lds_byte_t* const s0 = (lds_byte_t*)stage0;
   lds_byte_t* const s1 = (lds_byte_t*)stage1;
@@ -232,16 +232,14 @@ __global__ __launch_bounds__(kDmaThreads) void rows_gemm_persist_bf16(const Rows
   if (!find_tile(seq, &idx, G, &id)) return;
   const lds_byte_t* lut = nullptr;
   if (kLut) lut = (const lds_byte_t*)lut_lds;
-  if (kLut && wave < 4) {
-    // the table rides in front of the first operand tiles (four waves fetch a quarter each): its direct loads are the
-    // oldest in those waves' queues, so the first wait of the K loop covers them and its barrier publishes them
-    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lut) + wave * (kLutBytes / 4);
-    const unsigned char* g = (const unsigned char*)g_act_lut[ACT == FLEXMOE_GELU_ERF ? 0 : 1] + wave * (kLutBytes / 4) +
-                             (threadIdx.x & 63) * 16;
-#pragma unroll
-    for (int q = 0; q < kLutBytes / 4 / 1024; ++q) {
-      const unsigned char* gq = g + q * 1024;
-      asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" FLEXMOE_DMA_CPOL ::"v"(gq), "s"(lds0 + q * 1024) : "memory");
+  if (kLut) {
+    // the table rides in front of the first operand tiles: its direct loads are the oldest in the waves' queues, so the
+    // first wait of the K loop covers them and its barrier publishes them
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lut);
+    const unsigned char* g = lut_source<EPI>(ACT == FLEXMOE_GELU_ERF ? 0 : 1) + (threadIdx.x & 63) * 16;
+    for (int i = wave; i < lut_lds_bytes<EPI>() / 1024; i += kDmaWaves) {
+      const unsigned char* gi = g + i * 1024;
+      asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" FLEXMOE_DMA_CPOL ::"v"(gi), "s"(lds0 + i * 1024) : "memory");
     }
   }
   RowTile t = fetch_tile(id);

@@ -385,12 +385,9 @@ __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const S
 
     const bool use_lut = EPI != EPI_PLAIN && !EVAL && p.lut >= 0;
     if (use_lut) {
-      // the stages are free: the activation table (28 KB, from L2) goes there
-#pragma unroll
-      for (int q = 0; q < kLutBytes / 1024 / kSmallWaves; ++q) {
-        const int i = wave * (kLutBytes / 1024 / kSmallWaves) + q;
-        small_load_at((const bf16_t*)((const char*)g_act_lut[p.lut] + i * 1024 + lane * 16), lds0 + i * 1024);
-      }
+      // the stages are free: the activation table (14 KB, EPI_DH 28, from L2) goes there
+      const unsigned char* g = lut_source<EPI>(p.lut) + lane * 16;
+      for (int i = wave; i < lut_lds_bytes<EPI>() / 1024; i += kSmallWaves) small_load_at((const bf16_t*)(g + i * 1024), lds0 + i * 1024);
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
     }
@@ -434,7 +431,8 @@ __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const S
               for (int q = 0; q < 4; ++q) {
                 const uint32_t zu = __float_as_uint(z[q]);
                 if (use_lut) {
-                  lut_act_both(sm, zu, &a[q], &dv[q]);
+                  if (EPI == EPI_DHQ) dv[q] = lut_act_d(sm, zu);
+                  else lut_act_both(sm, zu, &a[q], &dv[q]);
                 } else {
                   small_act<EVAL>(p.act, z[q], &a[q], &dv[q]);
                 }

@@ -221,28 +221,30 @@ __device__ __forceinline__ void unpack4(uint2 u, float* v) {
 // so one table over the bf16 magnitudes serves both signs.  r and q vanish (below 1e-13) from
 // |z| = 8 on and r(a) -> -a/2, q -> -1/2 as a -> 0: magnitudes are clamped to [2^-24, 8], which
 // costs an absolute error below 2^-25.  Entries are computed in double precision when the library is
-// built (gen_act_lut.py writes act_lut_data.inc) and live in the code object as constant {r, q} fp32
-// pairs: 3457 entries, padded to 28 KB so that the GEMM kernels can pull the table into LDS with
-// whole 1 KB direct loads.  Nothing is filled in at run time: no first-call set-up, no host-side state.
+// built (gen_act_lut.py writes act_lut_data.inc) and live in the code object as constant fp32
+// tables of r and of q: 3457 entries each, padded to 14 KB so that the GEMM kernels can pull them into LDS with
+// whole 1 KB direct loads.  The forward pass takes r, the backward pass of a layer that kept H takes q: a table of its own for each
+// halves what is copied, and 64 lanes' look-ups spread over all LDS banks (as {r, q} pairs they met in every second one).
+// @LUTFIG  Nothing is filled in at run time: no first-call set-up, no host-side state.
 constexpr int kLutLo = 103 << 7;                    // bf16 bits of 2^-24
 constexpr int kLutHi = 130 << 7;                    // bf16 bits of 8.0
-constexpr int kLutBytes = 28 * 1024;
-constexpr int kLutEntries = kLutBytes / 8;
+constexpr int kLutBytes = 14 * 1024;                // of one table
+constexpr int kLutEntries = kLutBytes / 4;
 static_assert(kLutHi - kLutLo + 1 <= kLutEntries, "table does not fit its padding");
-struct ActLutEntry {
-  float r, q;
-};
-__device__ __align__(1024) const ActLutEntry g_act_lut[2][kLutEntries] = {      // [0] erf form, [1] tanh form
+__device__ __align__(1024) const float g_act_lut[2][2][kLutEntries] = {      // [0] erf form, [1] tanh form; of either [0] r, [1] q
 #include "act_lut_data.inc"
 };
-static_assert(sizeof(g_act_lut) == 2 * kLutBytes, "generated table and layout constants disagree");
+static_assert(sizeof(g_act_lut) == 4 * kLutBytes, "generated table and layout constants disagree");
 
-// Table entry for the bf16 value whose fp32 bit pattern is zu (LDS copy of one table).
+// What an epilogue copies to LDS, and its first table: r (EPI_FWD1), q (EPI_DHQ), r and behind it q (EPI_DH).
+template <int EPI> constexpr int lut_lds_bytes() { return EPI == EPI_DH ? 2 * kLutBytes : kLutBytes; }
+template <int EPI> __device__ __forceinline__ const unsigned char* lut_source(int form) { return (const unsigned char*)g_act_lut[form][EPI == EPI_DHQ ? 1 : 0]; }
+// Offset in a table of the bf16 value whose fp32 bit pattern is zu.
 typedef __attribute__((address_space(3))) unsigned char lds_byte_t;
 typedef __attribute__((address_space(3))) int lds_int_t;
 __device__ __forceinline__ uint32_t lut_offset(uint32_t zu) {
   const uint32_t m = (zu >> 16) & 0x7fffu;
-  return (min(max(m, (uint32_t)kLutLo), (uint32_t)kLutHi) - kLutLo) << 3;
+  return (min(max(m, (uint32_t)kLutLo), (uint32_t)kLutHi) - kLutLo) << 2;
 }
 // max(z, 0) on the bit pattern: as a signed integer every negative float (and -0) is below zero
 // and every positive float keeps its order, so one integer max does it (no NaN canonicalisation).
@@ -252,12 +254,13 @@ __device__ __forceinline__ float lut_act(const lds_byte_t* lut, uint32_t zu) {
   return relu_bits(zu) + r;
 }
 __device__ __forceinline__ void lut_act_both(const lds_byte_t* lut, uint32_t zu, float* a, float* da) {
-  const f32x2_t rq = *(const __attribute__((address_space(3))) f32x2_t*)(lut + lut_offset(zu));
-  *a = relu_bits(zu) + rq[0];
-  *da = (int32_t)zu < 0 ? -rq[1] : 1.f + rq[1];
+  const lds_byte_t* at = lut + lut_offset(zu);
+  const float r = *(const __attribute__((address_space(3))) float*)at, q = *(const __attribute__((address_space(3))) float*)(at + kLutBytes);
+  *a = relu_bits(zu) + r;
+  *da = (int32_t)zu < 0 ? -q : 1.f + q;
 }
 __device__ __forceinline__ float lut_act_d(const lds_byte_t* lut, uint32_t zu) {
-  const float q = *(const __attribute__((address_space(3))) float*)(lut + lut_offset(zu) + 4);
+  const float q = *(const __attribute__((address_space(3))) float*)(lut + lut_offset(zu));
   return (int32_t)zu < 0 ? -q : 1.f + q;
 }
 template <int EPI, int ACT> constexpr bool epilogue_uses_lut() { return EPI != EPI_PLAIN && ACT != FLEXMOE_RELU; }
@@ -534,7 +537,7 @@ __device__ __forceinline__ void rows_mainloop(bf16_t* smem, f32x16 (&acc)[MB][NB
 }
 
 // Epilogue of the rows kernels: bias, then plain store / pre-activation + activation / dH*act' + H.
-// LUT: the activation comes from the LDS copy `lut` of the activation table ({r, q} pairs, see
+// LUT: the activation comes from the LDS copy `lut` of the activation tables it takes (see
 // above); otherwise it is evaluated arithmetically.
 // FULL: all 256 rows of the tile and all 128 columns of the wave's block exist (no store predicates).
 // SCATTER (plain epilogue): tile row r is stored as row smap[r] of out0.

@@ -3,8 +3,8 @@
 Both GELU forms are z*F(z) with F(z) + F(-z) = 1, so on the bf16 magnitudes a = 2^-24 .. 8
     GELU(z)  = max(z, 0) + r(|z|),            r(a) = -a F(-a)
     GELU'(z) = [z >= 0] + sign(z) * q(|z|),    q(a) = a F'(a) - F(-a)
-Entry i holds {r, q} in fp32 for the magnitude with bf16 bits kLutLo + i (clamped to kLutHi), computed
-here in double precision; table 0 is the erf form (F = standard normal CDF), table 1 the tanh form.
+Entry i belongs to the magnitude with bf16 bits kLutLo + i (clamped to kLutHi), computed here in double precision and
+stored in fp32: first the erf form (F = standard normal CDF), then the tanh form, of each a table of r and one of q.
 The layout constants must agree with ffn_bf16_tile.h (a static_assert there checks the entry count).
 Run by build.py before the HIP sources are compiled; the output is a build artefact.
 """
@@ -14,8 +14,8 @@ import sys
 
 LUT_LO = 103 << 7          # bf16 bits of 2^-24
 LUT_HI = 130 << 7          # bf16 bits of 8.0
-LUT_BYTES = 28 * 1024
-ENTRIES = LUT_BYTES // 8
+LUT_BYTES = 14 * 1024
+ENTRIES = LUT_BYTES // 4
 
 
 def bf16_value(bits: int) -> float:
@@ -44,10 +44,13 @@ def main(path: str) -> None:
         out.write("// generated by gen_act_lut.py -- do not edit\n")
         out.write(f"// {ENTRIES} entries per table\n")
         for form in (0, 1):
+            pairs = [entry(form, bf16_value(min(LUT_LO + i, LUT_HI))) for i in range(ENTRIES)]
             out.write("{\n")
-            for i in range(ENTRIES):
-                r, q = entry(form, bf16_value(min(LUT_LO + i, LUT_HI)))
-                out.write(f"{{{f32_hex(r)}, {f32_hex(q)}}},\n")
+            for which in (0, 1):
+                out.write("{\n")
+                for pair in pairs:
+                    out.write(f32_hex(pair[which]) + ",\n")
+                out.write("},\n")
             out.write("},\n")
 
 
