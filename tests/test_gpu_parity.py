@@ -792,6 +792,19 @@ def test_route_adversarial(api, case):
         assert np.array_equal(got[name][:arr.shape[0]], arr), (case, name)
 
 
+# one round of 64 assignments per wave and four, the line to two launches, units of four rounds, of eight, and longer ones that are no
+# whole number of batches; experts with fewer assignments than replicas next to hot ones
+@pytest.mark.parametrize("N,E,V,k", [(512, 9, 20, 2), (513, 9, 20, 2), (4096, 64, 128, 1), (4097, 65, 129, 1), (32769, 5, 300, 2), (300001, 40, 48, 2)])
+def test_route_rounds(api, N, E, V, k):
+    rng = np.random.default_rng(N)
+    first = np.minimum(rng.geometric(0.3, N) - 1, E - 1)
+    idx = ((first[:, None] + np.arange(k) * (1 + rng.integers(0, E // k, N))[:, None]) % E).astype(np.int32)
+    rep_off, rep_ids = W.placement_from_loads(np.arange(1, E + 1), V, 64, shuffle_seed=4)
+    got = _route_only(api, idx, E, rep_off, rep_ids)
+    for name, arr in O.route(idx, E, rep_off, rep_ids).items():
+        assert np.array_equal(got[name][:arr.shape[0]], arr), name
+
+
 def test_route_empty_batch(api):
     got = _route_only(api, np.zeros((0, 2), dtype=np.int32), 3, [0, 1, 2, 4], [0, 1, 2, 3])
     assert got["expert_count"].tolist() == [0, 0, 0] and got["vexpert_off"].tolist() == [0, 0, 0, 0, 0]
