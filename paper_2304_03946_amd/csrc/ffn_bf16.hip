@@ -189,6 +189,19 @@ static int small_rows_most(int d, int f, int E, int V) {
 static int small_rows(int A, int d, int f, int E, int V) {
   return A > small_rows_most(d, f, E, V) ? 0 : A <= kSmall32Rows * E ? 32 : 64;
 }
+// Whether dXp and the weight gradients share a launch: both take the small tiles, dXp's tiles fit the two workgroups per compute unit
+// that the launch has, and the weight gradients are few enough that a third workgroup per compute unit, which the launch's
+// larger LDS rules out, counts less than the tail of dXp and the launch saved.  Whole backward passes, us, launches of their own and one:
+// d 128, f 512, E 16, 1536 rows 47, 34; d 256, f 1024, E 8, 2048 rows 62, 50, 8000 rows 85, 79; d 192, f 768, E 12, 12000 rows (400 tiles) 105, 104;
+// d 512, f 2048, E 32, 1024 rows 89, 82; d 768, f 3072, E 16, 1536 rows 114, 106, 4096 rows (480 tiles) 224, 221; d 1024, f 2048, E 8, 2048 rows 100, 96.
+// Past the lines: d 1024, f 2048, E 8, 5120 rows (704 tiles) 191, 193; d 768, f 3072, E 16, 10240 rows (1056) 401, 405; d 512, f 1024, E 128 (8192
+// tiles of weight gradients), 4096 rows 219, 224; d 1024, f 4096, E 32 (16384), 1024 rows 284, 294; d 2048, f 8192, E 64, 2048 rows 1835, 1951.
+static bool bwd_products_merged(const FfnArgs& a) {
+  if (!small_rows(a.A, a.d, a.f, a.E, a.V) || !wgrad_small(a.A, a.d, a.f, a.E)) return false;
+  const long long d_tiles = (a.d + GT - 1) / GT, f_tiles = (a.f + GT - 1) / GT;
+  return (a.A / 64 + a.E) * d_tiles <= kSmallSplitTarget && 2 * a.E * d_tiles * f_tiles <= 6144;
+}
+
 // Partial tiles that a product with contraction K and NC columns can leave at most (see small_segments): none for short
 // contractions.
 static long long small_slots(int A, int E, int bm, int K, int NC) {
@@ -261,10 +274,10 @@ static void launch_small_t(int bm, const SmallArgs& p, unsigned grid, hipStream_
   if (bm == 32) hipLaunchKernelGGL((rows_gemm_small_bf16<32, WT, EPI, EVAL>), dim3(grid), dim3(kSmallThreads), 0, s, p);
   else hipLaunchKernelGGL((rows_gemm_small_bf16<64, WT, EPI, EVAL>), dim3(grid), dim3(kSmallThreads), 0, s, p);
 }
-template <bool WT, int EPI>
-static hipError_t launch_small(const FfnArgs& a, const void* in, const void* w, const void* bias, int K, int NC,
-                               const void* hpre_in, void* out0, void* out1, void* ws, hipStream_t s, const int32_t* gsrc,
-                               int gk, const int32_t* scatter_rows) {
+template <int EPI>
+static SmallArgs small_args(const FfnArgs& a, const void* in, const void* w, const void* bias, int K, int NC, const void* hpre_in,
+                            void* out0, void* out1, void* ws, const int32_t* gsrc, int gk, const int32_t* scatter_rows, int* bm,
+                            unsigned* grid) {
   float* partial;
   const SmallPlan pl = small_plan_ws(a, ws, &partial);
   // The table as in the 256 x 256 kernels: where the contraction is whole 128-wide rounds.  Otherwise the activation is
@@ -275,14 +288,24 @@ static hipError_t launch_small(const FfnArgs& a, const void* in, const void* w, 
                     (const bf16_t*)hpre_in, (bf16_t*)out0, (bf16_t*)out1, gsrc, gk, scatter_rows, a.act, lut, partial, pl.counters};
   // two workgroups per compute unit walk the tiles
   const long long most = (long long)(a.A / pl.bm + a.E) * p.col_tiles;
-  const unsigned grid = (unsigned)std::min<long long>(kSmallSplitTarget, std::max<long long>(most * kSmallSplitMax, 1));
+  *grid = (unsigned)std::min<long long>(kSmallSplitTarget, std::max<long long>(most * kSmallSplitMax, 1));
+  *bm = pl.bm;
+  return p;
+}
+template <bool WT, int EPI>
+static hipError_t launch_small(const FfnArgs& a, const void* in, const void* w, const void* bias, int K, int NC,
+                               const void* hpre_in, void* out0, void* out1, void* ws, hipStream_t s, const int32_t* gsrc,
+                               int gk, const int32_t* scatter_rows) {
+  int bm;
+  unsigned grid;
+  const SmallArgs p = small_args<EPI>(a, in, w, bias, K, NC, hpre_in, out0, out1, ws, gsrc, gk, scatter_rows, &bm, &grid);
   if constexpr (EPI != EPI_PLAIN) {
-    if (gelu && lut < 0) {
-      launch_small_t<WT, EPI, true>(pl.bm, p, grid, s);
+    if (a.act != FLEXMOE_RELU && p.lut < 0) {
+      launch_small_t<WT, EPI, true>(bm, p, grid, s);
       return hipGetLastError();
     }
   }
-  launch_small_t<WT, EPI, false>(pl.bm, p, grid, s);
+  launch_small_t<WT, EPI, false>(bm, p, grid, s);
   return hipGetLastError();
 }
 
@@ -389,19 +412,40 @@ static void launch_wgrad_reduce(const FfnArgs& a, const WgradDmaArgs* g, int n, 
   hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(blocks, a.E, n), dim3(kGemmThreads), 0, s, r, elems);
 }
 
-// dW2 = H^T . dYp, dW1 = Xp^T . dHpre: each with its own partial tiles.
-static hipError_t launch_wgrads(const FfnArgs& a, const void* h, const void* dyp, void* dw2, const void* xp, const void* dhpre,
-                                void* dw1, void* ws, hipStream_t s) {
+// dXp = dHpre . W1^T (W1_e is [d, f], contraction index f contiguous), dW2 = H^T . dYp, dW1 = Xp^T . dHpre: the weight gradients
+// each with its own partial tiles.
+static hipError_t launch_bwd_products(const FfnArgs& a, const void* h, const void* dyp, void* dw2, const void* xp, const void* dhpre,
+                                      void* dw1, const void* w1, void* dxp, const int32_t* scatter_src, void* ws, hipStream_t s) {
   void* tail2 = (char*)ws + 2 * align_up((size_t)a.A * a.f * sizeof(bf16_t), 256);
   void* tail1 = (char*)tail2 + wgrad_tail_bytes(a.A, a.d, a.f, a.V);
   unsigned grid[2];
   const WgradDmaArgs g[2] = {wgrad_dma_args(a, h, dyp, a.f, a.d, dw2, tail2, ws, &grid[0], 0),
                              wgrad_dma_args(a, xp, dhpre, a.d, a.f, dw1, tail1, ws, &grid[1], 1)};
-  if (wgrad_small(a.A, a.d, a.f, a.E)) {
-    hipLaunchKernelGGL(wgrad_gemm_small_bf16, dim3(grid[0] + grid[1]), dim3(kGradThreads), 0, s, WgradSmallArgs{{g[0], g[1]}, grid[0]});
+  const bool small = wgrad_small(a.A, a.d, a.f, a.E);
+  const WgradSmallArgs both{{g[0], g[1]}, grid[0]};
+  if (a.A > 0 && bwd_products_merged(a)) {
+    int bm;
+    unsigned rows_grid;
+    const SmallArgs p = small_args<EPI_PLAIN>(a, dhpre, w1, nullptr, a.f, a.d, nullptr, dxp, nullptr, ws, nullptr, 1, scatter_src, &bm, &rows_grid);
+    rows_grid = (rows_grid + kXcds - 1) / kXcds * kXcds;
+    const dim3 blocks(rows_grid + grid[0] + grid[1]);
+    if (bm == 32) hipLaunchKernelGGL(bwd_products_small_bf16<32>, blocks, dim3(kGradThreads), 0, s, p, both, rows_grid);
+    else hipLaunchKernelGGL(bwd_products_small_bf16<64>, blocks, dim3(kGradThreads), 0, s, p, both, rows_grid);
     launch_wgrad_reduce(a, g, 2, s);
     return hipGetLastError();
   }
+  if (a.A > 0) {
+    const hipError_t err = launch_rows<true, EPI_PLAIN>(a, dhpre, w1, nullptr, a.f, a.d, nullptr, dxp, nullptr, ws, s, nullptr, 1,
+                                                        rows_split_ws(a, ws), scatter_src);
+    if (err != hipSuccess) return err;
+  }
+  if (small) {
+    hipLaunchKernelGGL(wgrad_gemm_small_bf16, dim3(grid[0] + grid[1]), dim3(kGradThreads), 0, s, both);
+    launch_wgrad_reduce(a, g, 2, s);
+    return hipGetLastError();
+  }
+  // (One launch for dXp, dW2 and dW1, which filled the partly empty last rounds of the three grids of 256 x 256 tiles, was measured
+  // against three persistent launches: the latter are 2 % faster on the GPT-medium-like backward pass and 4.5 % on the Swin-like one.)
   for (int i = 0; i < 2; ++i) {
     if (a.f % BM == 0 && a.d % BN == 0)      // whole output tiles: one persistent workgroup per compute unit
       hipLaunchKernelGGL(wgrad_gemm_persist_bf16, dim3(std::min(grid[i], (unsigned)kComputeUnits)), dim3(kDmaThreads), 0, s, g[i]);
@@ -469,15 +513,7 @@ hipError_t launch_ffn_bwd_bf16(const FfnArgs& a, const void* dyp, const void* xp
                  : launch_rows<true, EPI_DH>(a, dyp, w2, nullptr, a.d, a.f, hpre, dhpre, h_ws, ws, s);
     if (err != hipSuccess) return err;
   }
-  if (a.A > 0) {
-    // dXp = dHpre . W1^T; W1_e is [d, f], contraction index f contiguous
-    err = launch_rows<true, EPI_PLAIN>(a, dhpre, w1, nullptr, a.f, a.d, nullptr, dxp, nullptr, ws, s, nullptr, 1,
-                                       rows_split_ws(a, ws), scatter_src);
-    if (err != hipSuccess) return err;
-  }
-  // (One launch for dXp, dW2 and dW1, which filled the partly empty last rounds of the three grids of 256 x 256 tiles, was measured
-  // against three persistent launches: the latter are 2 % faster on the GPT-medium-like backward pass and 4.5 % on the Swin-like one.)
-  return launch_wgrads(a, h, dyp, dw2, xp, dhpre, dw1, ws, s);
+  return launch_bwd_products(a, h, dyp, dw2, xp, dhpre, dw1, w1, dxp, scatter_src, ws, s);
 }
 
 }  // namespace flexmoe

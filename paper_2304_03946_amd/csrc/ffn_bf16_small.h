@@ -33,6 +33,7 @@ template <int BM> struct SmallCfg {
   static constexpr int kABytes = BM * SK * 2;
   static constexpr int kStage = kABytes + kSmallWBytes;
   static constexpr int S = 81920 / kStage;               // stages: half of a compute unit's LDS
+  static constexpr int kLds = S * kStage;
   static constexpr int kALoads = BM / 8 / kSmallWaves;   // direct loads per wave and stage: rows operand ...
   static constexpr int kWLoads = kSmallWBytes / 1024 / kSmallWaves;      // ... and weights
   static constexpr int kLoads = kALoads + kWLoads;
@@ -195,11 +196,11 @@ template <int L> __device__ __forceinline__ void small_wait(int tiles) {
 
 // EPI as in rows_epilogue_t.  WT: W_e is [NC, K] (else [K, NC]).  EVAL: GELU is evaluated, not read from a table (kernels of their
 // own: with both in one, the 1500-token step of d 1024 took 658 us instead of 650).
+// `block` of `blocks` that walk the product's tiles; smem: SmallCfg<BM>::kLds bytes.
 template <int BM, bool WT, int EPI, bool EVAL>
-__global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const SmallArgs p) {
+__device__ __forceinline__ void rows_small_block(const SmallArgs& p, unsigned char* smem, unsigned block, unsigned blocks) {
   typedef SmallCfg<BM> C;
   constexpr int S = C::S, RB = BM / 16, NB2 = SN / kSmallWaves / 16;      // 16-row and 16-column blocks of a wave
-  __shared__ __align__(1024) unsigned char smem[S * C::kStage];
   lds_byte_t* const sm = (lds_byte_t*)smem;
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)sm);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const S
     lw = C::kABytes + k * 256 + (((wave * (NB2 * 2) + ((fr & 3) >> 1)) ^ x) << 4) + 8 * (fr & 1);
   }
 
-  for (unsigned idx = blockIdx.x; idx < total; idx += gridDim.x) {
+  for (unsigned idx = block; idx < total; idx += blocks) {
     int rt, ct, seg = 0;
     if (nseg > 1) {
       seg = (int)(idx % nseg);
@@ -445,6 +446,12 @@ __global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const S
       }
     }
   }
+}
+
+template <int BM, bool WT, int EPI, bool EVAL>
+__global__ __launch_bounds__(kSmallThreads, 2) void rows_gemm_small_bf16(const SmallArgs p) {
+  __shared__ __align__(1024) unsigned char smem[SmallCfg<BM>::kLds];
+  rows_small_block<BM, WT, EPI, EVAL>(p, smem, blockIdx.x, gridDim.x);
 }
 
 }  // namespace flexmoe

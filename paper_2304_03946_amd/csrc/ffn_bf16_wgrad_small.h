@@ -19,7 +19,7 @@ namespace flexmoe {
 //    dmat_chunk); outputs go through a wave-private patch, so that a store instruction fills whole 128-byte lines.
 // What bounds it: 1500 tokens (k 2) of d 1024, f 4096, 32 experts: the 537 MB of both gradients' stores (109 us at the rate of a
 // large copy).  Whole backward pass there 382 -> 366 us; d 256, f 1024, 8 experts, 3200 rows 97 -> 66; d 128, f 512, 16 experts, 4096 rows
-// 79 -> 54 (two launches instead of four, six times as many tiles in flight).
+// 79 -> 54, with dXp in the same launch 44 (two launches instead of four, six times as many tiles in flight).
 // Work list, segments and the order of the sums are those of the 256 x 256 kernels (the same instruction, K tiles in the same
 // order): the same bits.
 // =============================================================================================
@@ -28,6 +28,7 @@ constexpr int kGradThreads = 4 * kWave;
 constexpr int kGradStages = 3;
 constexpr int kGradOpBytes = DK * GT * 2;                // one operand's K tile: 8 KB
 constexpr int kGradStageBytes = 2 * kGradOpBytes;
+constexpr int kGradLds = kGradStages * kGradStageBytes;
 constexpr int kGradLoads = 4;                            // direct loads per wave and stage: two of either operand
 
 struct WgradSmallArgs {
@@ -38,17 +39,17 @@ struct WgradSmallArgs {
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(kGradThreads, 3) void wgrad_gemm_small_bf16(const WgradSmallArgs a) {
-  __shared__ __align__(1024) unsigned char smem[kGradStages * kGradStageBytes];
+// smem: kGradLds bytes
+__device__ __forceinline__ void wgrad_small_block(const WgradSmallArgs& a, unsigned char* smem, unsigned block) {
   lds_byte_t* const sm = (lds_byte_t*)smem;
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)sm);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int fr = lane & 15, fg = lane >> 4;
-  const bool second = blockIdx.x >= a.grid0;
+  const bool second = block >= a.grid0;
   const WgradDmaArgs& p = a.p[second ? 1 : 0];
   const int M = p.M, NC = p.NC;
   int grow, nt;
-  if (!patched_tile(blockIdx.x - (second ? a.grid0 : 0u), p.seg_rows_max * p.m_tiles, p.n_tiles, &grow, &nt)) return;
+  if (!patched_tile(block - (second ? a.grid0 : 0u), p.seg_rows_max * p.m_tiles, p.n_tiles, &grow, &nt)) return;
   const i32x4_t job = ((ConstInt4Ptr)p.plan.jobs)[grow / p.m_tiles];
   const int e = job[0], seg = job[1], nseg = job[2];
   if (e < 0) return;
@@ -189,6 +190,20 @@ __global__ __launch_bounds__(kGradThreads, 3) void wgrad_gemm_small_bf16(const W
       }
     }
   }
+}
+
+__global__ __launch_bounds__(kGradThreads, 3) void wgrad_gemm_small_bf16(const WgradSmallArgs a) {
+  __shared__ __align__(1024) unsigned char smem[kGradLds];
+  wgrad_small_block(a, smem, blockIdx.x);
+}
+
+// dXp and both weight gradients, which depend on nothing of each other: the first `rows_grid` workgroups (a multiple of kXcds) walk
+// dXp's tiles, and the weight gradients' fill the compute units as they finish.
+// (Backward pass of d 128, f 512, 16 experts, 1536 rows 47 -> 34 us.)
+template <int BM> __global__ __launch_bounds__(kGradThreads, 2) void bwd_products_small_bf16(const SmallArgs p, const WgradSmallArgs a, unsigned rows_grid) {
+  __shared__ __align__(1024) unsigned char smem[SmallCfg<BM>::kLds > kGradLds ? SmallCfg<BM>::kLds : kGradLds];
+  if (blockIdx.x < rows_grid) rows_small_block<BM, true, EPI_PLAIN, false>(p, smem, blockIdx.x, rows_grid);
+  else wgrad_small_block(a, smem, blockIdx.x - rows_grid);
 }
 
 }  // namespace flexmoe
