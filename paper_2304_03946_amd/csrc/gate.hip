@@ -25,8 +25,6 @@ namespace flexmoe {
 constexpr int kGateThreads = 256;
 constexpr float kNegInf = -__builtin_huge_valf();
 
-static int gate_epad(int E) { return (int)align_up((size_t)E, 32); }
-
 constexpr int kGateDK = 64;                          // K tile of the direct-to-LDS gate kernel
 static int gate_dpad(int d) { return (int)align_up((size_t)d, kGateDK); }
 
