@@ -412,8 +412,13 @@ static void launch_wgrad_reduce(const FfnArgs& a, const WgradDmaArgs* g, int n, 
   hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(blocks, a.E, n), dim3(kGemmThreads), 0, s, r, elems);
 }
 
+static bool overlap(const void* p, const void* q, size_t bytes_p, size_t bytes_q) {
+  return (uintptr_t)p < (uintptr_t)q + bytes_q && (uintptr_t)q < (uintptr_t)p + bytes_p;
+}
+
 // dXp = dHpre . W1^T (W1_e is [d, f], contraction index f contiguous), dW2 = H^T . dYp, dW1 = Xp^T . dHpre: the weight gradients
-// each with its own partial tiles.
+// each with its own partial tiles.  In this order, so that a caller who needs w1, h or dyp no longer may have a gradient written over
+// them: products that share a launch only do where the later one's output is nothing that the earlier one reads.
 static hipError_t launch_bwd_products(const FfnArgs& a, const void* h, const void* dyp, void* dw2, const void* xp, const void* dhpre,
                                       void* dw1, const void* w1, void* dxp, const int32_t* scatter_src, void* ws, hipStream_t s) {
   void* tail2 = (char*)ws + 2 * align_up((size_t)a.A * a.f * sizeof(bf16_t), 256);
@@ -421,9 +426,10 @@ static hipError_t launch_bwd_products(const FfnArgs& a, const void* h, const voi
   unsigned grid[2];
   const WgradDmaArgs g[2] = {wgrad_dma_args(a, h, dyp, a.f, a.d, dw2, tail2, ws, &grid[0], 0),
                              wgrad_dma_args(a, xp, dhpre, a.d, a.f, dw1, tail1, ws, &grid[1], 1)};
-  const bool small = wgrad_small(a.A, a.d, a.f, a.E);
+  const size_t w_bytes = (size_t)a.E * a.d * a.f * sizeof(bf16_t), row_bytes = (size_t)a.A * sizeof(bf16_t);
+  const bool joint = !overlap(dw1, h, w_bytes, row_bytes * a.f) && !overlap(dw1, dyp, w_bytes, row_bytes * a.d);
   const WgradSmallArgs both{{g[0], g[1]}, grid[0]};
-  if (a.A > 0 && bwd_products_merged(a)) {
+  if (a.A > 0 && joint && bwd_products_merged(a) && !overlap(dw1, w1, w_bytes, w_bytes) && !overlap(dw2, w1, w_bytes, w_bytes)) {
     int bm;
     unsigned rows_grid;
     const SmallArgs p = small_args<EPI_PLAIN>(a, dhpre, w1, nullptr, a.f, a.d, nullptr, dxp, nullptr, ws, nullptr, 1, scatter_src, &bm, &rows_grid);
@@ -439,8 +445,13 @@ static hipError_t launch_bwd_products(const FfnArgs& a, const void* h, const voi
                                                         rows_split_ws(a, ws), scatter_src);
     if (err != hipSuccess) return err;
   }
-  if (small) {
-    hipLaunchKernelGGL(wgrad_gemm_small_bf16, dim3(grid[0] + grid[1]), dim3(kGradThreads), 0, s, both);
+  if (wgrad_small(a.A, a.d, a.f, a.E)) {
+    if (joint) {
+      hipLaunchKernelGGL(wgrad_gemm_small_bf16, dim3(grid[0] + grid[1]), dim3(kGradThreads), 0, s, both);
+    } else {
+      for (int i = 0; i < 2; ++i)
+        hipLaunchKernelGGL(wgrad_gemm_small_bf16, dim3(grid[i]), dim3(kGradThreads), 0, s, WgradSmallArgs{{g[i], g[i]}, grid[i]});
+    }
     launch_wgrad_reduce(a, g, 2, s);
     return hipGetLastError();
   }

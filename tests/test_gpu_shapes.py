@@ -253,3 +253,40 @@ def test_offsets_of_a_very_wide_layer(api):  # noqa: F811
     for c in range(0, f, 1 << 22):
         assert torch.equal(hpre[:, c:c + (1 << 22)].float(), x.float() @ w1[0, :, c:c + (1 << 22)].float()), c
     assert not yp.any()
+
+
+# dXp, dW2 and dW1 in one launch, dW2 and dW1 in one, and in launches of their own (256 x 256 tiles)
+@pytest.mark.parametrize("A,d,f,E", [(512, 64, 256, 2), (256, 128, 256, 2), (40000, 64, 128, 2), (256, 512, 2048, 2), (10000, 512, 2048, 2)])
+def test_weight_gradients_over_what_is_read_no_longer(api, A, d, f, E):  # noqa: F811
+    """dXp, dW2, dW1 are computed in this order: w1, h and dyp may be overwritten by what comes after their last use."""
+    B, layer_mod = api
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(A + d)
+    w1, w2, x, dyp = (torch.empty(s, **bf).normal_(0, std, generator=g) for s, std in
+                      (((E, d, f), 0.05), ((E, f, d), 0.05), ((A, d), 1.0), ((A, d), 1.0)))
+    hpre, h, yp = torch.empty((A, f), **bf), torch.empty((A, f), **bf), torch.empty((A, d), **bf)
+    ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, E, 1, E, B.BF16), dtype=torch.uint8, device="cuda")
+    voff, owner = i32([0, A // 3, A]), i32([0, 1])
+    B.flexmoe_expert_ffn_fwd(x, voff, owner, w1, None, w2, None, B.GELU_ERF, hpre, yp, ws, h=h)
+
+    def bwd(over=None, with_dw2=False):
+        """The products, with dw1 (or dw2) at the start of a copy of the tensor `over`."""
+        t = {"w1": w1.clone(), "w2": w2.clone(), "h": h.clone(), "dyp": dyp.clone()}
+        dxp, dw1, dw2 = torch.zeros((A, d), **bf), torch.zeros((E, d, f), **bf), torch.zeros((E, f, d), **bf)
+        if over is not None and t[over].numel() < w1.numel():      # (a tensor smaller than the gradient: with room behind it)
+            room = torch.empty(w1.numel(), **bf)
+            room[:t[over].numel()] = t[over].flatten()
+            base, t[over] = room, room[:t[over].numel()].view(t[over].shape)
+        elif over is not None:
+            base = t[over].flatten()
+        if over is not None:
+            view = base[:w1.numel()]
+            dw1, dw2 = (dw1, view.view(E, f, d)) if with_dw2 else (view.view(E, d, f), dw2)
+        B.flexmoe_expert_ffn_bwd(t["dyp"], x, hpre, t["w1"], t["w2"], voff, owner, B.GELU_ERF, dxp, dw1, dw2, ws, h=t["h"])
+        return dxp, dw1, dw2
+    want = bwd()
+    assert all(t.any() for t in want)
+    for over, with_dw2 in (("w1", False), ("w1", True), ("w2", False), ("w2", True), ("h", False), ("dyp", False)):
+        for _ in range(3):
+            assert all(torch.equal(a, b) for a, b in zip(bwd(over, with_dw2), want)), (over, with_dw2)
