@@ -105,6 +105,10 @@ static bool wgrad_small(int A, int d, int f, int E) {
   const long long large = (long long)((d + BM - 1) / BM) * ((f + BN - 1) / BN), small = (long long)((d + GT - 1) / GT) * ((f + GT - 1) / GT);
   return large <= 4 || 5 * small <= 16 * large || A <= 112ll * E || A / DK * large <= 20 * kComputeUnits;
 }
+// HIP takes fewer than 2^32 threads in a dimension of a grid.  Both products in one launch are twice what either is: layers of 8 to
+// 32 features with 2^30 columns over all experts (they fit the card's memory with few rows) need the launches apart.
+constexpr long long kMaxGradBlocks = (1ll << 32) / kGradThreads - 1;
+static bool wgrad_joint(unsigned blocks2, unsigned blocks1) { return (long long)blocks2 + blocks1 <= kMaxGradBlocks; }
 static int wgrad_seg_rows_max(int A, int d, int f, int E, int V) { return E + wgrad_extra_segments(A, V, wgrad_seg_tiles(A, d, f)); }
 
 static int max_row_tiles(int A, int V) { return A / BM + V; }
@@ -388,19 +392,25 @@ static WgradDmaArgs wgrad_dma_args(const FfnArgs& a, const void* L, const void* 
                       (bf16_t*)dw};
 }
 
+// How the work lists of dW2 and dW1 are balanced (only the persistent kernels skip the holes that balancing leaves in a list).
+static void wgrad_balance(const FfnArgs& a, WgradBalance* geo) {
+  const int f_tiles = (a.f + BM - 1) / BM, d_tiles = (a.d + BM - 1) / BM;
+  const bool whole = a.f % BM == 0 && a.d % BN == 0 && !wgrad_small(a.A, a.d, a.f, a.E);
+  geo[0] = whole ? wgrad_balance_geometry(f_tiles, d_tiles) : WgradBalance{1, 1};
+  geo[1] = whole ? wgrad_balance_geometry(d_tiles, f_tiles) : WgradBalance{1, 1};
+}
+
 // The work list both weight-gradient products of a backward call read and (with tokens) the row-tile table
 // of its rows products: one small launch.
 static void launch_bwd_plan(const FfnArgs& a, void* ws, hipStream_t s) {
   const int seg_rows_max = wgrad_seg_rows_max(a.A, a.d, a.f, a.E, a.V);
   const int row_blocks = a.A > 0 ? plan_blocks(a) : 0;
-  const int f_tiles = (a.f + BM - 1) / BM, d_tiles = (a.d + BM - 1) / BM;
-  const bool whole = a.f % BM == 0 && a.d % BN == 0 && !wgrad_small(a.A, a.d, a.f, a.E);
+  WgradBalance geo[2];
+  wgrad_balance(a, geo);
   hipLaunchKernelGGL(ffn_bwd_plan_kernel, dim3(1 + row_blocks), dim3(kGemmThreads), 0, s, a.voff, a.owner, a.E, a.V,
                      wgrad_seg_tiles(a.A, a.d, a.f), seg_rows_max,
                      wgrad_plan_at(wgrad_plan_ws(a, ws), seg_rows_max, a.E, a.V, 0),
-                     // (only the persistent kernels skip the holes that balancing leaves in a list)
-                     whole ? wgrad_balance_geometry(f_tiles, d_tiles) : WgradBalance{1, 1},
-                     whole ? wgrad_balance_geometry(d_tiles, f_tiles) : WgradBalance{1, 1}, rows_tab_ws(a, ws), small_plan_ws(a, ws));
+                     geo[0], geo[1], rows_tab_ws(a, ws), small_plan_ws(a, ws));
 }
 
 // Sums of the partial tiles of `n` products (their [M, NC] have the same number of elements).
@@ -427,7 +437,7 @@ static hipError_t launch_bwd_products(const FfnArgs& a, const void* h, const voi
   const WgradDmaArgs g[2] = {wgrad_dma_args(a, h, dyp, a.f, a.d, dw2, tail2, ws, &grid[0], 0),
                              wgrad_dma_args(a, xp, dhpre, a.d, a.f, dw1, tail1, ws, &grid[1], 1)};
   const size_t w_bytes = (size_t)a.E * a.d * a.f * sizeof(bf16_t), row_bytes = (size_t)a.A * sizeof(bf16_t);
-  const bool joint = !overlap(dw1, h, w_bytes, row_bytes * a.f) && !overlap(dw1, dyp, w_bytes, row_bytes * a.d);
+  const bool joint = wgrad_joint(grid[0], grid[1]) && !overlap(dw1, h, w_bytes, row_bytes * a.f) && !overlap(dw1, dyp, w_bytes, row_bytes * a.d);
   const WgradSmallArgs both{{g[0], g[1]}, grid[0]};
   if (a.A > 0 && joint && bwd_products_merged(a) && !overlap(dw1, w1, w_bytes, w_bytes) && !overlap(dw2, w1, w_bytes, w_bytes)) {
     int bm;
@@ -528,6 +538,29 @@ hipError_t launch_ffn_bwd_bf16(const FfnArgs& a, const void* dyp, const void* xp
 }
 
 }  // namespace flexmoe
+
+// For tests: which kernels a bf16 call of these sizes takes (operands that do not overlap).  out[0] row tiles of the few-rows kernels
+// (0: the 256 x 256 ones); [1] weight gradients on 128 x 128 tiles; [2] both in one launch; [3] dXp in that launch, too; [4] K tiles of a
+// segment (0: no cutting); [5], [6] bins over which dW2's and dW1's work lists are dealt out (1: not balanced); [7] most threads of
+// one weight-gradient launch.
+extern "C" void flexmoe_debug_bf16_paths(int A, int d, int f, int E, int V, long long* out) {
+  using namespace flexmoe;
+  const FfnArgs a{A, d, f, E, V, FLEXMOE_RELU, nullptr, nullptr};
+  const bool small = wgrad_small(A, d, f, E);
+  unsigned grid[2];
+  wgrad_dma_args(a, nullptr, nullptr, f, d, nullptr, nullptr, nullptr, &grid[0], 0);
+  wgrad_dma_args(a, nullptr, nullptr, d, f, nullptr, nullptr, nullptr, &grid[1], 1);
+  const bool joint = small && wgrad_joint(grid[0], grid[1]);
+  WgradBalance geo[2];
+  wgrad_balance(a, geo);
+  out[0] = small_rows(A, d, f, E, V);
+  out[1] = small;
+  out[2] = joint;
+  out[3] = A > 0 && joint && bwd_products_merged(a);
+  out[4] = wgrad_seg_tiles(A, d, f);
+  for (int i = 0; i < 2; ++i) out[5 + i] = geo[i].groups * geo[i].per_slot;
+  out[7] = (joint ? (long long)grid[0] + grid[1] : std::max(grid[0], grid[1])) * (small ? kGradThreads : kDmaThreads);
+}
 
 #ifdef FLEXMOE_TILE_PHASES
 // Profiling build only: copies the per-workgroup phase counters of the persistent GEMM kernels (5 x 256 x 4 uint64,
