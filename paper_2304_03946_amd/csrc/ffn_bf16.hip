@@ -105,8 +105,9 @@ static bool wgrad_small(int A, int d, int f, int E) {
   const long long large = (long long)((d + BM - 1) / BM) * ((f + BN - 1) / BN), small = (long long)((d + GT - 1) / GT) * ((f + GT - 1) / GT);
   return large <= 4 || 5 * small <= 16 * large || A <= 112ll * E || A / DK * large <= 20 * kComputeUnits;
 }
-// HIP takes fewer than 2^32 threads in a dimension of a grid.  Both products in one launch are twice what either is: layers of 8 to
-// 32 features with 2^30 columns over all experts (they fit the card's memory with few rows) need the launches apart.
+// A grid's dimension is fewer than 2^32 threads: of more, HIP runs what is left modulo 2^32, and reports nothing.  Both products in one
+// launch are twice what either is: layers of 8 to 32 features with 2^30 columns over all experts (they fit the card's memory with few
+// rows) need the launches apart.
 constexpr long long kMaxGradBlocks = (1ll << 32) / kGradThreads - 1;
 static bool wgrad_joint(unsigned blocks2, unsigned blocks1) { return (long long)blocks2 + blocks1 <= kMaxGradBlocks; }
 static int wgrad_seg_rows_max(int A, int d, int f, int E, int V) { return E + wgrad_extra_segments(A, V, wgrad_seg_tiles(A, d, f)); }

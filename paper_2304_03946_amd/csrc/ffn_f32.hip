@@ -13,6 +13,7 @@
 // one: fp32 training step of 1000 tokens (d 256, f 1024, 8 experts) 30, 29, 31, 27 us for its rows products and 28, 28 for its weight
 // gradients, now 25, 25, 26, 24 and 22, 22; 4096 tokens (d 512, f 2048) 221, 228, 233, 229, 203, 201 -> 207, 198, 219, 195, 187, 185; 100
 // tokens of that layer 26, 52, 27, 49, 20, 20 -> 16, 27, 17, 26, 23, 22; weight gradients of a hot expert (d 128, f 512, 8192 rows) 84 -> 46.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -211,19 +212,20 @@ __device__ __forceinline__ bool f32_tile(const int32_t* __restrict__ voff, const
 
 // C[p, n] = sum_k In[p, k] * W_e[k, n]   (WT == false, W_e is [K, NC])
 //         = sum_k In[p, k] * W_e[n, k]   (WT == true,  W_e is [NC, K])
+// for `col_tiles` tiles of 64 columns from tile ct0 on.
 template <int MT, bool WT, int EPI>
 __global__ __launch_bounds__(kF32Threads, 2) void rows_gemm_f32(const float* __restrict__ in, const float* __restrict__ w,
                                                                 const float* __restrict__ bias,
                                                                 const int32_t* __restrict__ voff,
                                                                 const int32_t* __restrict__ owner, int V, int K, int NC,
-                                                                int act, const float* __restrict__ hpre_in,
+                                                                int ct0, int col_tiles, int act, const float* __restrict__ hpre_in,
                                                                 float* __restrict__ out0, float* __restrict__ out1) {
   typedef F32Loop<MT, true, WT> Loop;
   __shared__ __align__(1024) unsigned char smem[Loop::kLds];
   __shared__ int s_tile[4];
   int row0, rows, e, ct;
-  if (!f32_tile<MT * 32>(voff, owner, V, (NC + FN - 1) / FN, s_tile, &row0, &rows, &e, &ct)) return;
-  const int n0 = ct * FN, cols = min(FN, NC - n0);
+  if (!f32_tile<MT * 32>(voff, owner, V, col_tiles, s_tile, &row0, &rows, &e, &ct)) return;
+  const int n0 = (ct0 + ct) * FN, cols = min(FN, NC - n0);
   const float* we = w + (size_t)e * K * NC;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 
@@ -433,15 +435,21 @@ static int f32_wgrad_blocks(const FfnArgs& a, int M, int NC) {
 template <bool WT, int EPI>
 static void launch_rows_f32(const FfnArgs& a, const void* in, const void* w, const void* bias, int K, int NC, const void* hpre_in,
                             void* out0, void* out1, hipStream_t s) {
-  const int mt = f32_rows_blocks(a, NC);
-  // row tiles: at most one ragged one per bucket; an eighth of the tiles per XCD, rounded up
-  const dim3 grid((unsigned)(((long long)(a.A / (mt * 32) + a.V) * tiles_of(NC, FN) / kF32Xcds + 1) * kF32Xcds));
-  if (mt == 2)
-    hipLaunchKernelGGL((rows_gemm_f32<2, WT, EPI>), grid, dim3(kF32Threads), 0, s, (const float*)in, (const float*)w,
-                       (const float*)bias, a.voff, a.owner, a.V, K, NC, a.act, (const float*)hpre_in, (float*)out0, (float*)out1);
-  else
-    hipLaunchKernelGGL((rows_gemm_f32<1, WT, EPI>), grid, dim3(kF32Threads), 0, s, (const float*)in, (const float*)w,
-                       (const float*)bias, a.voff, a.owner, a.V, K, NC, a.act, (const float*)hpre_in, (float*)out0, (float*)out1);
+  const int mt = f32_rows_blocks(a, NC), cols = (int)tiles_of(NC, FN);
+  // row tiles: at most one ragged one per bucket; an eighth of the tiles per XCD, rounded up.  Fewer than 2^32 threads in a launch (of
+  // more, HIP runs what is left modulo 2^32, and reports nothing): layers of millions of columns take several.
+  const long long row_tiles = a.A / (mt * 32) + a.V;
+  const int most = (int)std::max((((1ll << 32) / kF32Threads - 1) / kF32Xcds * kF32Xcds) / row_tiles, 1ll);
+  for (int ct0 = 0; ct0 < cols; ct0 += most) {
+    const int n = std::min(most, cols - ct0);
+    const dim3 grid((unsigned)((row_tiles * n + kF32Xcds - 1) / kF32Xcds * kF32Xcds));
+    if (mt == 2)
+      hipLaunchKernelGGL((rows_gemm_f32<2, WT, EPI>), grid, dim3(kF32Threads), 0, s, (const float*)in, (const float*)w, (const float*)bias,
+                         a.voff, a.owner, a.V, K, NC, ct0, n, a.act, (const float*)hpre_in, (float*)out0, (float*)out1);
+    else
+      hipLaunchKernelGGL((rows_gemm_f32<1, WT, EPI>), grid, dim3(kF32Threads), 0, s, (const float*)in, (const float*)w, (const float*)bias,
+                         a.voff, a.owner, a.V, K, NC, ct0, n, a.act, (const float*)hpre_in, (float*)out0, (float*)out1);
+  }
 }
 
 static void launch_wgrad_f32(const FfnArgs& a, const void* L, const void* R, int M, int NC, void* dw, hipStream_t s) {

@@ -1,4 +1,4 @@
-"""Which bf16 kernels a call takes, and whether HIP takes the launches: host arithmetic of the library, no GPU."""
+"""Which bf16 kernels a call takes, and the size of their launches: host arithmetic of the library, no GPU."""
 import ctypes
 
 import pytest
@@ -20,7 +20,8 @@ def paths(A, d, f, E, V):
 @pytest.mark.parametrize("E", [4, 16, 256])
 @pytest.mark.parametrize("columns", [2 ** 29, 2 ** 30 - 2048, 2 ** 30, 2 ** 30 + 2 ** 29, 2 ** 31 - 2 ** 19])
 def test_weight_gradients_of_very_many_columns_can_be_launched(d, E, columns):
-    """All experts' columns: a product of its own is two threads each, which HIP takes (below 2^32); both in one launch are four."""
+    """All experts' columns: a product of its own is two threads each, both in one launch are four.  HIP runs a grid of 2^32 threads
+    and more modulo 2^32, without an error."""
     f = columns // E // 8 * 8
     for A in (1, 64, 4096):
         p = paths(A, d, f, E, E)

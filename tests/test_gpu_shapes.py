@@ -290,3 +290,27 @@ def test_weight_gradients_over_what_is_read_no_longer(api, A, d, f, E):  # noqa:
     for over, with_dw2 in (("w1", False), ("w1", True), ("w2", False), ("w2", True), ("h", False), ("dyp", False)):
         for _ in range(3):
             assert all(torch.equal(a, b) for a, b in zip(bwd(over, with_dw2), want)), (over, with_dw2)
+
+
+def test_fp32_products_of_more_tiles_than_a_launch_takes(api):  # noqa: F811
+    """512 vExperts, each with room for a row tile, times 2^15 column tiles: 2^32 threads in one grid.  Whole numbers: exact sums."""
+    B, layer_mod = api
+    A, d, f, E, V = 16, 8, 1 << 21, 2, 512
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x, dyp = (torch.empty((A, d), device="cuda").random_(-1, 2, generator=g) for _ in range(2))
+    w1, w2 = torch.empty((E, d, f), device="cuda").random_(-2, 3, generator=g), torch.empty((E, f, d), device="cuda").random_(-1, 2, generator=g)
+    hpre, h = torch.full((A, f), 7.0, device="cuda"), torch.full((A, f), 7.0, device="cuda")
+    yp, dxp, dw1, dw2 = torch.full((A, d), 7.0, device="cuda"), torch.full((A, d), 7.0, device="cuda"), torch.empty_like(w1), torch.empty_like(w2)
+    ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, E, 1, V, B.F32), dtype=torch.uint8, device="cuda")
+    voff, owner = i32([0] * 100 + [10] * 300 + [A] * 113), i32([0] * 200 + [1] * 312)      # rows in buckets 99 and 399
+    B.flexmoe_expert_ffn_fwd(x, voff, owner, w1, None, w2, None, B.RELU, hpre, yp, ws, h=h)
+    B.flexmoe_expert_ffn_bwd(dyp, x, hpre, w1, w2, voff, owner, B.RELU, dxp, dw1, dw2, ws, h=h)
+    for e, rows in ((0, slice(0, 10)), (1, slice(10, A))):
+        z = x[rows].double() @ w1[e].double()
+        assert torch.equal(hpre[rows].double(), z) and torch.equal(h[rows].double(), z.clamp(min=0))
+        assert torch.equal(yp[rows].double(), z.clamp(min=0) @ w2[e].double())
+        dz = (dyp[rows].double() @ w2[e].double().t()) * (z > 0)
+        assert torch.equal(dxp[rows].double(), dz @ w1[e].double().t())
+        assert torch.equal(dw1[e].double(), x[rows].double().t() @ dz)
+        assert torch.equal(dw2[e].double(), z.clamp(min=0).t() @ dyp[rows].double())
