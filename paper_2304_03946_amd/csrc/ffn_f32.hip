@@ -5,7 +5,8 @@
 // tiles would leave most of the chip without work: two waves per 32 x 32, one for the even 32-wide K tiles and one for the odd, whose
 // sums are added at the end.  K tiles travel global -> LDS with direct loads through four (three) stages; two workgroups per compute
 // unit.  Within sixteen k an instruction's lane groups hold four consecutive ones each, so that a K-contiguous operand is read
-// from LDS as 16-byte vectors.  The order of a sum depends on the sizes only: results are reproducible.
+// from LDS as 16-byte vectors.  Every sum is that of the even K tiles in ascending order plus that of the odd ones, whichever tile it
+// belongs to: a row's outputs do not depend on how many other rows there are.
 //
 // What bounds it: 1024 cycles of matrix instructions per K tile and wave where the chip is full (4352 tiles: 207 us for [8192, 512] x
 // [512, 2048], 83 TFLOP/s of 157), else what a workgroup does before its first K tile, the K tiles' latency, and workgroups that do not
@@ -92,9 +93,38 @@ template <int MT, bool KC0, bool KC1> struct F32Loop {
   static __device__ __forceinline__ unsigned dst0(int wave, int q) { return sub0(wave, q) * kSubBytes + piece0(wave, q) * 1024; }
   static __device__ __forceinline__ unsigned dst1(int wave, int q) { return sub1(wave, q) * kSubBytes + Op0::kBytes + piece1(wave, q) * 1024; }
 
+  // stage kt is in LDS, and every wave has left the one before it
+  static __device__ __forceinline__ void ready(int kt, int KT) {
+    switch (min(S - 2, KT - 1 - kt)) {               // younger stages in flight
+      case 0: f32_wait_vmcnt<0>(); break;
+      case 1: f32_wait_vmcnt<kLoads>(); break;
+      default: f32_wait_vmcnt<2 * kLoads>(); break;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  }
+  static __device__ __forceinline__ void multiply(const lds_t* st, F32Acc& acc, int wave, int lane) {
+#pragma unroll
+    for (int kk = 0; kk < FK / 16; ++kk) {
+      float a[2][4], b[2][4];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) Op0::frag(a[i], st, (MT == 2 ? (wave >> 1) * 32 : 0) + i * 16, kk, lane);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) Op1::frag(b[j], st + Op0::kBytes, (wave & 1) * 32 + j * 16, kk, lane);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][q], a[i][q], acc[i][j], 0, 0, 0);
+    }
+  }
+
   // KT stages; issue(s, lds address) starts the wave's loads of one.
   // acc[i][j]: row 16 i + lane % 16, columns 16 j + 4 (lane / 16) .. of the wave's block.  MT == 1: on return the wave with the even K tiles
   // has the sums of the block's first 16 columns, the other one of the rest.
+  // Either way a sum is that of the even K tiles, ascending, plus that of the odd ones: MT == 2 keeps the two in accumulators of their own.
   template <typename Issue>
   static __device__ __forceinline__ void run(lds_t* sm, F32Acc& acc, int KT, Issue issue) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -106,30 +136,30 @@ template <int MT, bool KC0, bool KC1> struct F32Loop {
 #pragma unroll
     for (int s = 0; s < S - 1; ++s)
       if (s < KT) issue(s, lds0 + s * kStageBytes);
-    for (int kt = 0; kt < KT; ++kt) {
-      switch (min(S - 2, KT - 1 - kt)) {             // younger stages in flight
-        case 0: f32_wait_vmcnt<0>(); break;
-        case 1: f32_wait_vmcnt<kLoads>(); break;
-        default: f32_wait_vmcnt<2 * kLoads>(); break;
+    if (MT == 2) {
+      F32Acc odd;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) odd[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int kt = 0; kt < KT; kt += 2) {
+        ready(kt, KT);
+        if (kt + S - 1 < KT) issue(kt + S - 1, lds0 + (kt + S - 1) % S * kStageBytes);
+        multiply(sm + kt % S * kStageBytes, acc, wave, lane);
+        if (kt + 1 == KT) break;
+        ready(kt + 1, KT);
+        if (kt + S < KT) issue(kt + S, lds0 + (kt + S) % S * kStageBytes);
+        multiply(sm + (kt + 1) % S * kStageBytes, odd, wave, lane);
       }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-      if (kt + S - 1 < KT) issue(kt + S - 1, lds0 + (kt + S - 1) % S * kStageBytes);
-      const lds_t* st = sm + kt % S * kStageBytes + (MT == 1 ? (wave >> 1) * kSubBytes : 0);
 #pragma unroll
-      for (int kk = 0; kk < FK / 16; ++kk) {
-        float a[2][4], b[2][4];
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) Op0::frag(a[i], st, (MT == 2 ? (wave >> 1) * 32 : 0) + i * 16, kk, lane);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) Op1::frag(b[j], st + Op0::kBytes, (wave & 1) * 32 + j * 16, kk, lane);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][q], a[i][q], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < 2; ++j) acc[i][j] += odd[i][j];
+    } else {
+      for (int kt = 0; kt < KT; ++kt) {
+        ready(kt, KT);
+        if (kt + S - 1 < KT) issue(kt + S - 1, lds0 + (kt + S - 1) % S * kStageBytes);
+        multiply(sm + kt % S * kStageBytes + (wave >> 1) * kSubBytes, acc, wave, lane);
       }
     }
     if (MT == 1) {

@@ -314,3 +314,31 @@ def test_fp32_products_of_more_tiles_than_a_launch_takes(api):  # noqa: F811
         assert torch.equal(dxp[rows].double(), dz @ w1[e].double().t())
         assert torch.equal(dw1[e].double(), x[rows].double().t() @ dz)
         assert torch.equal(dw2[e].double(), z.clamp(min=0).t() @ dyp[rows].double())
+
+
+# a row among 300 (32 x 64 tiles) and among 25000 (64 x 64 tiles in all four products); whole K tiles, an odd number of them, a ragged one
+@pytest.mark.parametrize("d,f", [(256, 1024), (264, 1048), (224, 1000)])
+def test_fp32_rows_do_not_depend_on_the_batch(api, d, f):  # noqa: F811
+    B, layer_mod = api
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(d)
+    most, few = 25000, 300
+    x, dyp = (torch.empty((most, d), device="cuda").normal_(0, 1, generator=g) for _ in range(2))
+    w1, w2 = torch.empty((1, d, f), device="cuda").normal_(0, 0.05, generator=g), torch.empty((1, f, d), device="cuda").normal_(0, 0.05, generator=g)
+
+    def layer(A, E):
+        """Rows 0 .. A - 1 with expert 0; E - 1 experts without rows behind it."""
+        c = lambda t: torch.cat([t, torch.zeros((E - 1,) + t.shape[1:], device="cuda")])
+        out = [torch.empty((A, n), device="cuda") for n in (f, f, d, d)]
+        dw1, dw2 = torch.empty((E, d, f), device="cuda"), torch.empty((E, f, d), device="cuda")
+        ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, E, 1, E, B.F32), dtype=torch.uint8, device="cuda")
+        voff, owner = i32([0] + [A] * E), i32(list(range(E)))
+        hpre, h, yp, dxp = out
+        B.flexmoe_expert_ffn_fwd(x[:A], voff, owner, c(w1), None, c(w2), None, B.GELU_ERF, hpre, yp, ws, h=h)
+        B.flexmoe_expert_ffn_bwd(dyp[:A], x[:A], hpre, c(w1), c(w2), voff, owner, B.GELU_ERF, dxp, dw1, dw2, ws, h=h)
+        return out, (dw1[0], dw2[0])
+    (many, _), (small, grads) = layer(most, 1), layer(few, 1)
+    for a, b in zip(many, small):
+        assert torch.equal(a[:few], b)
+    # the weight gradients likewise: 64 x 64 tiles where the rows per expert are few
+    assert all(torch.equal(a, b) for a, b in zip(layer(few, 4)[1], grads))
