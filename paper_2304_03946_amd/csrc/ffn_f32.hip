@@ -133,9 +133,8 @@ template <int MT, bool KC0, bool KC1> struct F32Loop {
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < S - 1; ++s)
-      if (s < KT) issue(s, lds0 + s * kStageBytes);
+#pragma unroll 1
+    for (int s = 0; s < min(S - 1, KT); ++s) issue(s, lds0 + s * kStageBytes);
     if (MT == 2) {
       F32Acc odd;
 #pragma unroll
@@ -335,12 +334,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void wgrad_f32(const float* __restr
   __shared__ __align__(1024) unsigned char smem[Loop::kLds];
   __shared__ int s_first[FLEXMOE_MAX_VEXPERTS], s_end[FLEXMOE_MAX_VEXPERTS];      // first row - rows before it, rows up to its end
   __shared__ int s_n;
-  // XCD x takes the x-th eighth of every expert's output tiles, cut along the longer side: each half of the operands comes into one L2,
-  // the other into all
-  const int mt = (M + MT * 32 - 1) / (MT * 32), nt = (NC + FN - 1) / FN;
-  const int e = blockIdx.y, t = (int)(blockIdx.x % kF32Xcds * (gridDim.x / kF32Xcds) + blockIdx.x / kF32Xcds);
-  if (t >= mt * nt) return;
-  const int m0 = (mt >= nt ? t / nt : t % mt) * (MT * 32), n0 = (mt >= nt ? t % nt : t / mt) * FN;
+  const int e = blockIdx.z, m0 = blockIdx.y * (MT * 32), n0 = blockIdx.x * FN;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (wave == 0) {                  // the expert's non-empty buckets, ascending
     int n = 0, total = 0;
@@ -413,27 +407,35 @@ __global__ __launch_bounds__(kF32Threads, 2) void wgrad_f32(const float* __restr
                  lds + Loop::dst1(wave, q));
       return;
     }
+    // rows of several buckets: a lane's loads each look for theirs among the stage's buckets
+    int pl[Loop::kL0], pr[Loop::kL1], fl[Loop::kL0], fr[Loop::kL1];      // row of the contraction; what leads from there to the row of L and R
 #pragma unroll
     for (int q = 0; q < Loop::kL0; ++q) {
-      const int i = Loop::piece0(wave, q), p = p0 + Loop::sub0(wave, q) * FK + Loop::Op0::k(i, lane);
-      const float* l = (const float*)&kF32Zero;
-      if (p < T) {
-        int b = bu;
-        while (p >= s_end[b]) ++b;
-        l = L + (size_t)(s_first[b] + p) * M + min(m0 + Loop::Op0::out(i, lane), M - 4);
-      }
-      f32_load(l, lds + Loop::dst0(wave, q));
+      pl[q] = p0 + Loop::sub0(wave, q) * FK + Loop::Op0::k(Loop::piece0(wave, q), lane);
+      fl[q] = bu_first;
     }
 #pragma unroll
     for (int q = 0; q < Loop::kL1; ++q) {
-      const int i = Loop::piece1(wave, q), p = p0 + Loop::sub1(wave, q) * FK + Loop::Op1::k(i, lane);
-      const float* r = (const float*)&kF32Zero;
-      if (p < T) {
-        int b = bu;
-        while (p >= s_end[b]) ++b;
-        r = R + (size_t)(s_first[b] + p) * NC + min(n0 + Loop::Op1::out(i, lane), NC - 4);
-      }
-      f32_load(r, lds + Loop::dst1(wave, q));
+      pr[q] = p0 + Loop::sub1(wave, q) * FK + Loop::Op1::k(Loop::piece1(wave, q), lane);
+      fr[q] = bu_first;
+    }
+    for (int b = bu, end = bu_end; end < p0 + kStep && ++b < nb;) {
+      const int first = __builtin_amdgcn_readfirstlane(s_first[b]), next = __builtin_amdgcn_readfirstlane(s_end[b]);
+#pragma unroll
+      for (int q = 0; q < Loop::kL0; ++q) fl[q] = pl[q] >= end ? first : fl[q];
+#pragma unroll
+      for (int q = 0; q < Loop::kL1; ++q) fr[q] = pr[q] >= end ? first : fr[q];
+      end = next;
+    }
+#pragma unroll
+    for (int q = 0; q < Loop::kL0; ++q) {
+      const float* l = L + (size_t)(fl[q] + pl[q]) * M + min(m0 + Loop::Op0::out(Loop::piece0(wave, q), lane), M - 4);
+      f32_load(pl[q] < T ? l : (const float*)&kF32Zero, lds + Loop::dst0(wave, q));
+    }
+#pragma unroll
+    for (int q = 0; q < Loop::kL1; ++q) {
+      const float* r = R + (size_t)(fr[q] + pr[q]) * NC + min(n0 + Loop::Op1::out(Loop::piece1(wave, q), lane), NC - 4);
+      f32_load(pr[q] < T ? r : (const float*)&kF32Zero, lds + Loop::dst1(wave, q));
     }
   };
   F32Acc acc;
@@ -452,14 +454,19 @@ __global__ __launch_bounds__(kF32Threads, 2) void wgrad_f32(const float* __restr
 static unsigned tiles_of(int n, int t) { return (unsigned)((n + t - 1) / t); }
 
 // 32-row blocks of a workgroup's tile: two (64 x 64 tiles) where there are enough tiles for the chip, else one, with the contraction
-// over two waves.  In us, one and two blocks, by 64 x 64 tiles:
-//   rows products  144 (K 1024) 24.7, 27.9; 576 (K 256) 25.0, 28.1; 672 (K 512) 37, 48; 1088 (K 2048) 198, 217; 1600 (K 512) 89, 89;
-//                  past the line: 2176 (K 256) 72, 66; 4352 (K 512) 221, 208; but 1088 (K 128) 27.9, 26.5
-//   weight gradients, 250 rows per expert and more  128 46, 78; 512 22.4, 26.8 and 63, 87; past the line: 1024 86, 77; 2048 212, 187
-//                     fewer rows (a few K tiles: the sum over two waves is what it costs)  512 13.6, 10.3; 2048 37.8, 22.6
-static int f32_rows_blocks(const FfnArgs& a, int NC) { return (long long)(a.A / 64 + a.E / 2) * tiles_of(NC, FN) >= 1536 ? 2 : 1; }
+// over two waves.
+// Rows products, in us, one and two blocks, by 64 x 64 tiles:
+//   144 (K 1024) 24.7, 27.9; 576 (K 256) 25.0, 28.1; 672 (K 512) 37, 48; 1088 (K 2048) 198, 217; 1600 (K 512) 89, 89;
+//   past the line: 2176 (K 256) 72, 66; 4352 (K 512) 221, 208; but 1088 (K 128) 27.9, 26.5
+// Weight gradients: one for fewer than 1024 tiles of 64 x 64 over all experts and from 30 (300 tiles and more: 120) rows per expert on, by
+// rows per expert, one over two:  below 120 tiles  8 rows 1.04, 20 0.93, 60 0.83, 200 0.67;  300 - 500  20 1.23, 60 1.05, 130 0.85;
+// 800 - 1024  60 1.17, 130 0.99, 300 0.75;  past the line: 1024 - 2000  60 1.31, 300 1.09
+static int f32_rows_blocks(const FfnArgs& a, int NC) {
+  return (long long)(a.A / 64 + a.E / 2) * tiles_of(NC, FN) >= 1536 ? 2 : 1;
+}
 static int f32_wgrad_blocks(const FfnArgs& a, int M, int NC) {
-  return (long long)a.E * tiles_of(M, 64) * tiles_of(NC, FN) >= 1024 || a.A < 128 * a.E ? 2 : 1;
+  const long long tiles = (long long)a.E * tiles_of(M, 64) * tiles_of(NC, FN);
+  return tiles >= 1024 || a.A < (tiles < 300 ? 30 : 120) * a.E ? 2 : 1;
 }
 
 template <bool WT, int EPI>
@@ -484,7 +491,7 @@ static void launch_rows_f32(const FfnArgs& a, const void* in, const void* w, con
 
 static void launch_wgrad_f32(const FfnArgs& a, const void* L, const void* R, int M, int NC, void* dw, hipStream_t s) {
   const int mt = f32_wgrad_blocks(a, M, NC);
-  const dim3 grid((tiles_of(NC, FN) * tiles_of(M, mt * 32) + kF32Xcds - 1) / kF32Xcds * kF32Xcds, a.E);
+  const dim3 grid(tiles_of(NC, FN), tiles_of(M, mt * 32), a.E);
   if (mt == 2)
     hipLaunchKernelGGL(wgrad_f32<2>, grid, dim3(kF32Threads), 0, s, (const float*)L, (const float*)R, a.voff, a.owner, a.V, M, NC, (float*)dw);
   else

@@ -342,3 +342,29 @@ def test_fp32_rows_do_not_depend_on_the_batch(api, d, f):  # noqa: F811
         assert torch.equal(a[:few], b)
     # the weight gradients likewise: 64 x 64 tiles where the rows per expert are few
     assert all(torch.equal(a, b) for a, b in zip(layer(few, 4)[1], grads))
+
+
+# 64 x 64 tiles (few rows per expert) and 32 x 64 ones; buckets of none to a few rows, so that many meet in a K tile, and rows of several K tiles
+@pytest.mark.parametrize("A,E,V,d,f", [(1, 1, 1, 8, 8), (50, 2, 37, 40, 72), (59, 2, 512, 72, 136), (150, 2, 70, 72, 136), (700, 3, 130, 264, 40), (700, 3, 5, 136, 520), (900, 40, 512, 64, 64)])
+def test_fp32_weight_gradients_over_short_buckets(api, A, E, V, d, f):  # noqa: F811
+    """Whole numbers: exact sums."""
+    B, layer_mod = api
+    rng = np.random.default_rng(A + V)
+    owner = np.concatenate([np.arange(E), rng.integers(E, size=V - E)])
+    rng.shuffle(owner)
+    rows = np.bincount(rng.integers(V, size=A) // 2 * 2 % V, minlength=V)      # (every other bucket is empty)
+    voff = np.concatenate([[0], np.cumsum(rows)])
+    i32 = lambda v: torch.from_numpy(np.asarray(v, dtype=np.int32)).cuda()
+    g = torch.Generator(device="cuda").manual_seed(A)
+    x, dyp, hpre = (torch.empty(s, device="cuda").random_(-2, 3, generator=g) for s in ((A, d), (A, d), (A, f)))
+    w1, w2 = (torch.empty(s, device="cuda").random_(-2, 3, generator=g) for s in ((E, d, f), (E, f, d)))
+    dxp, dw1, dw2 = torch.empty((A, d), device="cuda"), torch.full((E, d, f), 7.0, device="cuda"), torch.full((E, f, d), 7.0, device="cuda")
+    ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, E, 1, V, B.F32), dtype=torch.uint8, device="cuda")
+    B.flexmoe_expert_ffn_bwd(dyp, x, hpre, w1, w2, i32(voff), i32(owner), B.RELU, dxp, dw1, dw2, ws)
+    of = torch.from_numpy(np.repeat(owner, rows)).cuda()
+    for e in range(E):
+        t = of == e
+        dz = (dyp[t].double() @ w2[e].double().t()) * (hpre[t] > 0)
+        assert torch.equal(dw2[e].double(), hpre[t].double().clamp(min=0).t() @ dyp[t].double())
+        assert torch.equal(dw1[e].double(), x[t].double().t() @ dz)
+        assert torch.equal(dxp[t].double(), dz @ w1[e].double().t())
