@@ -295,13 +295,20 @@ __global__ __launch_bounds__(kF32Threads, 2) void rows_gemm_f32(const float* __r
   F32Acc acc;
   Loop::run((lds_t*)smem, acc, (K + kStep - 1) / kStep, issue);
 
+  auto row_at = [&](int x) { return (MT == 2 ? (wave >> 1) * 32 : 0) + (x >> 1) * 16 + (lane & 15); };
+  auto col_at = [&](int x) { return n0 + (wave & 1) * 32 + (x & 1) * 16 + 4 * (lane >> 4); };
+  auto stored = [&](int x) { return row_at(x) < rows && col_at(x) < NC && (MT == 2 || (x & 1) == (wave >> 1)); };
+  float4 hp[4];
+  if (EPI == EPI_DH) {              // (one trip to memory, not one after another)
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+      if (stored(x)) hp[x] = *(const float4*)(hpre_in + (size_t)(row0 + row_at(x)) * NC + col_at(x));
+  }
 #pragma unroll
   for (int x = 0; x < 4; ++x) {
-    const int i = x >> 1, j = x & 1;
-    const int row = (MT == 2 ? (wave >> 1) * 32 : 0) + i * 16 + (lane & 15);
-    const int col = n0 + (wave & 1) * 32 + j * 16 + 4 * (lane >> 4);
-    if (row >= rows || col >= NC || (MT == 1 && j != (wave >> 1))) continue;
-    const size_t o = (size_t)(row0 + row) * NC + col;
+    if (!stored(x)) continue;
+    const int i = x >> 1, j = x & 1, col = col_at(x);
+    const size_t o = (size_t)(row0 + row_at(x)) * NC + col;
     float c[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) c[q] = acc[i][j][q];
@@ -315,7 +322,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void rows_gemm_f32(const float* __r
     } else if (EPI == EPI_PLAIN) {
       *(float4*)(out0 + o) = make_float4(c[0], c[1], c[2], c[3]);
     } else {                        // out0 = dHpre, out1 = act(Hpre) unless the forward pass kept it
-      const float4 z = *(const float4*)(hpre_in + o);
+      const float4 z = hp[x];
       *(float4*)(out0 + o) = make_float4(c[0] * act_deriv(z.x, act), c[1] * act_deriv(z.y, act), c[2] * act_deriv(z.z, act),
                                          c[3] * act_deriv(z.w, act));
       if (out1) *(float4*)(out1 + o) = make_float4(act_apply(z.x, act), act_apply(z.y, act), act_apply(z.z, act), act_apply(z.w, act));
@@ -455,14 +462,19 @@ static unsigned tiles_of(int n, int t) { return (unsigned)((n + t - 1) / t); }
 
 // 32-row blocks of a workgroup's tile: two (64 x 64 tiles) where there are enough tiles for the chip, else one, with the contraction
 // over two waves.
-// Rows products, in us, one and two blocks, by 64 x 64 tiles:
-//   144 (K 1024) 24.7, 27.9; 576 (K 256) 25.0, 28.1; 672 (K 512) 37, 48; 1088 (K 2048) 198, 217; 1600 (K 512) 89, 89;
-//   past the line: 2176 (K 256) 72, 66; 4352 (K 512) 221, 208; but 1088 (K 128) 27.9, 26.5
+// Rows products: two from 280 tiles of 64 x 64 on where the contraction is short (a 32-row tile's first loads and its sum over two
+// waves weigh more), from 1200 otherwise; and always one where buckets are so short that 32-row tiles are hardly more.  In us, one and two:
+//   K 32, NC 128: 208 tiles 8.8, 9.2;              past the line: 408 12.0, 8.4; 1502 28.4, 18.4
+//   K 128, NC 512: 256 9.4, 11.8;                                 408 13.8, 13.0; 1508 38.7, 31.7
+//   K 256, NC 1024: 512 18.8, 24.8; 1088 33.9, 34.3;              1508 45.9, 42.7
+//   K 1024, NC 1024: 608 61, 82;                                  1504 136, 128
+//   short buckets (16 rows, 512 of them, K 256, NC 256)  2048 tiles 41, 60
 // Weight gradients: one for fewer than 1024 tiles of 64 x 64 over all experts and from 30 (300 tiles and more: 120) rows per expert on, by
 // rows per expert, one over two:  below 120 tiles  8 rows 1.04, 20 0.93, 60 0.83, 200 0.67;  300 - 500  20 1.23, 60 1.05, 130 0.85;
 // 800 - 1024  60 1.17, 130 0.99, 300 0.75;  past the line: 1024 - 2000  60 1.31, 300 1.09
-static int f32_rows_blocks(const FfnArgs& a, int NC) {
-  return (long long)(a.A / 64 + a.E / 2) * tiles_of(NC, FN) >= 1536 ? 2 : 1;
+static int f32_rows_blocks(const FfnArgs& a, int K, int NC) {
+  const long long one = std::max(a.V, a.A / 32 + a.V / 2), two = std::max(a.V, a.A / 64 + a.V / 2);      // row tiles of that many blocks
+  return two * tiles_of(NC, FN) >= (K <= 224 ? 280 : 1200) && 10 * one >= 16 * two ? 2 : 1;
 }
 static int f32_wgrad_blocks(const FfnArgs& a, int M, int NC) {
   const long long tiles = (long long)a.E * tiles_of(M, 64) * tiles_of(NC, FN);
@@ -472,7 +484,7 @@ static int f32_wgrad_blocks(const FfnArgs& a, int M, int NC) {
 template <bool WT, int EPI>
 static void launch_rows_f32(const FfnArgs& a, const void* in, const void* w, const void* bias, int K, int NC, const void* hpre_in,
                             void* out0, void* out1, hipStream_t s) {
-  const int mt = f32_rows_blocks(a, NC), cols = (int)tiles_of(NC, FN);
+  const int mt = f32_rows_blocks(a, K, NC), cols = (int)tiles_of(NC, FN);
   // row tiles: at most one ragged one per bucket; an eighth of the tiles per XCD, rounded up.  Fewer than 2^32 threads in a launch (of
   // more, HIP runs what is left modulo 2^32, and reports nothing): layers of millions of columns take several.
   const long long row_tiles = a.A / (mt * 32) + a.V;
