@@ -93,17 +93,21 @@ static int wgrad_partial_slots(int A, int V, int seg_tiles) { return seg_tiles ?
 // Whether a call's weight gradients go to the 128 x 128 tiles of wgrad_gemm_small_bf16, three workgroups per compute unit, instead of
 // the 256 x 256 ones (half the operand traffic per product, but one workgroup per compute unit, whose look-ups, first loads and
 // stores have nothing beside them).  Whole backward passes, f = 4 d unless given, us, 256 and 128:
-//  * the gradient of an expert is at most four 256 x 256 tiles: d 64, E 8, 60000 rows 139, 103; d 128, E 16, 131072 rows 339, 302; d 192, E 12,
-//    10000 rows 115, 87, 131072 rows 516, 492; d 256, E 8, 3200 rows 97, 66, 80000 rows 407, 401;
-//  * the small tiles cover at most 0.8 of what the large ones do (d 320, 384): d 384, E 12, 24000 rows 286, 259, 120000 rows 970, 916; 0.83
-//    (d 640) is past the line: 60000 rows 1060, 1062;
+//  * the gradient of an expert is at most four 256 x 256 tiles, and a compute unit's even share of K tiles x output tiles at most 180, or 100
+//    with four tiles: d 64, E 8, 60000 rows 139, 103; d 192, E 12, 10000 rows 115, 87, 420000 rows (share 154) 1263, 1207; d 256, E 8, 3200 rows
+//    97, 66, 42000 rows (20) 216, 206, 130000 rows (63) 540, 523; past the line: d 192, E 12, 520000 rows (190) 1430, 1443; d 256, E 8,
+//    230000 rows (112) 831, 843; E 64, 260000 rows (127) 863, 931; d 512, f 512, E 8, 400000 rows (195) 1167, 1244.  (In between the large tiles
+//    have their moments, where they fill their last round: d 512, f 512, 60000 rows 234, 243; d 504, f 504 296, 317);
+//  * the small tiles cover at most 0.8 of what the large ones do (d up to 128, 320, 384): d 128, E 8, 520000 rows 859, 760; d 384, E 12, 24000
+//    rows 286, 259, 260000 rows 1887, 1791; d 640, f 1920, E 8, 60000 rows 813, 754; 0.83 (d 640, f 2560) is past the line: 60000 rows 1060, 1062;
 //  * up to 112 rows per expert: d 1024, E 32, 32 rows 308, 280, 94 rows 382, 366; d 2048, E 64, 32 rows 1896, 1846, 96 rows 2426, 2410;
 //    past the line: 160 rows 470, 477 and 2578, 2684;
 //  * an even share of at most 20 K tiles x output tiles per compute unit: d 512, E 32 (share 16) 249, 230; d 1024, f 2048, E 8 (20) 206, 190;
-//    d 512, f 1024, E 128 (20) 372, 344; past the line: d 512, E 32 (25) 291, 302; d 1024, f 2048, E 8 (31) 276, 283; f 1024, E 128 (32) 428, 434.
+//    d 512, f 1024, E 128 (20) 372, 344; past the line: d 512, E 32 (25) 291, 302; d 1024, f 2048, E 8 (31) 276, 283;
+//    d 512, f 1024, E 128 (32) 428, 434.
 static bool wgrad_small(int A, int d, int f, int E) {
   const long long large = (long long)((d + BM - 1) / BM) * ((f + BN - 1) / BN), small = (long long)((d + GT - 1) / GT) * ((f + GT - 1) / GT);
-  return large <= 4 || 5 * small <= 16 * large || A <= 112ll * E || A / DK * large <= 20 * kComputeUnits;
+  return 5 * small <= 16 * large || A <= 112ll * E || A / DK * large <= (large <= 3 ? 180 : large == 4 ? 100 : 20) * kComputeUnits;
 }
 // A grid's dimension is fewer than 2^32 threads: of more, HIP runs what is left modulo 2^32, and reports nothing.  Both products in one
 // launch are twice what either is: layers of 8 to 32 features with 2^30 columns over all experts (they fit the card's memory with few

@@ -27,3 +27,13 @@ def test_weight_gradients_of_very_many_columns_can_be_launched(d, E, columns):
         p = paths(A, d, f, E, E)
         assert p["threads"] < 2 ** 32, p
     assert paths(64, d, 512, E, E)["joint"]
+
+
+# sizes on either side of each line between the 128 x 128 and the 256 x 256 weight-gradient tiles: at most three tiles of 256 x 256 and a share
+# of 180 K tiles x tiles per compute unit; four tiles and 100; more and 20; little padding; 112 rows per expert
+@pytest.mark.parametrize("A,d,f,E,small", [
+    (491520, 192, 768, 12, True), (491520 + 5 * 32, 192, 768, 12, False), (204800, 256, 1024, 8, True), (204832, 256, 1024, 8, False),
+    (400000, 512, 512, 8, False), (20480, 512, 1024, 8, True), (20512, 512, 1024, 8, False), (1 << 20, 384, 1536, 8, True),
+    (1 << 20, 128, 8192, 8, True), (112 * 64, 2048, 8192, 64, True), (112 * 64 + 1, 2048, 8192, 64, False)])
+def test_line_of_the_weight_gradient_tiles(A, d, f, E, small):
+    assert paths(A, d, f, E, E)["small_gradients"] == small
