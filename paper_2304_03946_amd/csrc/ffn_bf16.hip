@@ -105,7 +105,9 @@ static int wgrad_partial_slots(int A, int V, int seg_tiles) { return seg_tiles ?
 //  * an even share of at most 20 K tiles x output tiles per compute unit: d 512, E 32 (share 16) 249, 230; d 1024, f 2048, E 8 (20) 206, 190;
 //    d 512, f 1024, E 128 (20) 372, 344; past the line: d 512, E 32 (25) 291, 302; d 1024, f 2048, E 8 (31) 276, 283;
 //    d 512, f 1024, E 128 (32) 428, 434.
+// Not for layers of 2^26 columns and more: an operand's 32-bit offsets are bytes here (elements in the 256 x 256 kernels), of up to 31 rows.
 static bool wgrad_small(int A, int d, int f, int E) {
+  if (std::max(d, f) >= 1 << 26) return false;
   const long long large = (long long)((d + BM - 1) / BM) * ((f + BN - 1) / BN), small = (long long)((d + GT - 1) / GT) * ((f + GT - 1) / GT);
   return 5 * small <= 16 * large || A <= 112ll * E || A / DK * large <= (large <= 3 ? 180 : large == 4 ? 100 : 20) * kComputeUnits;
 }

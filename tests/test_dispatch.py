@@ -37,3 +37,10 @@ def test_weight_gradients_of_very_many_columns_can_be_launched(d, E, columns):
     (1 << 20, 128, 8192, 8, True), (112 * 64, 2048, 8192, 64, True), (112 * 64 + 1, 2048, 8192, 64, False)])
 def test_line_of_the_weight_gradient_tiles(A, d, f, E, small):
     assert paths(A, d, f, E, E)["small_gradients"] == small
+
+
+def test_weight_gradients_of_layers_wider_than_byte_offsets():
+    """32 rows of 2^26 columns and more: the 128 x 128 tiles count 32-bit offsets in bytes, the 256 x 256 ones in elements."""
+    for d, f in ((8, 2 ** 26), (8, 70_000_000), (2 ** 26 + 8, 8)):
+        assert not paths(32, d, f, 1, 1)["small_gradients"]
+    assert paths(32, 8, 2 ** 26 - 8, 1, 1)["small_gradients"]
