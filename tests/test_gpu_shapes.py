@@ -8,6 +8,7 @@ from paper_2304_03946_amd import workloads as W
 from test_gpu_parity import api, check_gate, run_stagewise, upload  # noqa: F401  (api: module fixture)
 
 pytestmark = pytest.mark.gpu
+F32 = dict(dtype=torch.float32, device="cuda")
 
 
 def stagewise(api, cfg, seed=3):  # noqa: F811
@@ -298,10 +299,10 @@ def test_fp32_products_of_more_tiles_than_a_launch_takes(api):  # noqa: F811
     A, d, f, E, V = 16, 8, 1 << 21, 2, 512
     i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
     g = torch.Generator(device="cuda").manual_seed(2)
-    x, dyp = (torch.empty((A, d), device="cuda").random_(-1, 2, generator=g) for _ in range(2))
-    w1, w2 = torch.empty((E, d, f), device="cuda").random_(-2, 3, generator=g), torch.empty((E, f, d), device="cuda").random_(-1, 2, generator=g)
-    hpre, h = torch.full((A, f), 7.0, device="cuda"), torch.full((A, f), 7.0, device="cuda")
-    yp, dxp, dw1, dw2 = torch.full((A, d), 7.0, device="cuda"), torch.full((A, d), 7.0, device="cuda"), torch.empty_like(w1), torch.empty_like(w2)
+    x, dyp = (torch.empty((A, d), **F32).random_(-1, 2, generator=g) for _ in range(2))
+    w1, w2 = torch.empty((E, d, f), **F32).random_(-2, 3, generator=g), torch.empty((E, f, d), **F32).random_(-1, 2, generator=g)
+    hpre, h = torch.full((A, f), 7.0, **F32), torch.full((A, f), 7.0, **F32)
+    yp, dxp, dw1, dw2 = torch.full((A, d), 7.0, **F32), torch.full((A, d), 7.0, **F32), torch.empty_like(w1), torch.empty_like(w2)
     ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, E, 1, V, B.F32), dtype=torch.uint8, device="cuda")
     voff, owner = i32([0] * 100 + [10] * 300 + [A] * 113), i32([0] * 200 + [1] * 312)      # rows in buckets 99 and 399
     B.flexmoe_expert_ffn_fwd(x, voff, owner, w1, None, w2, None, B.RELU, hpre, yp, ws, h=h)
@@ -323,14 +324,14 @@ def test_fp32_rows_do_not_depend_on_the_batch(api, d, f):  # noqa: F811
     i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
     g = torch.Generator(device="cuda").manual_seed(d)
     most, few = 25000, 300
-    x, dyp = (torch.empty((most, d), device="cuda").normal_(0, 1, generator=g) for _ in range(2))
-    w1, w2 = torch.empty((1, d, f), device="cuda").normal_(0, 0.05, generator=g), torch.empty((1, f, d), device="cuda").normal_(0, 0.05, generator=g)
+    x, dyp = (torch.empty((most, d), **F32).normal_(0, 1, generator=g) for _ in range(2))
+    w1, w2 = torch.empty((1, d, f), **F32).normal_(0, 0.05, generator=g), torch.empty((1, f, d), **F32).normal_(0, 0.05, generator=g)
 
     def layer(A, E):
         """Rows 0 .. A - 1 with expert 0; E - 1 experts without rows behind it."""
-        c = lambda t: torch.cat([t, torch.zeros((E - 1,) + t.shape[1:], device="cuda")])
-        out = [torch.empty((A, n), device="cuda") for n in (f, f, d, d)]
-        dw1, dw2 = torch.empty((E, d, f), device="cuda"), torch.empty((E, f, d), device="cuda")
+        c = lambda t: torch.cat([t, torch.zeros((E - 1,) + t.shape[1:], **F32)])
+        out = [torch.empty((A, n), **F32) for n in (f, f, d, d)]
+        dw1, dw2 = torch.empty((E, d, f), **F32), torch.empty((E, f, d), **F32)
         ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, E, 1, E, B.F32), dtype=torch.uint8, device="cuda")
         voff, owner = i32([0] + [A] * E), i32(list(range(E)))
         hpre, h, yp, dxp = out
@@ -356,9 +357,9 @@ def test_fp32_weight_gradients_over_short_buckets(api, A, E, V, d, f):  # noqa: 
     voff = np.concatenate([[0], np.cumsum(rows)])
     i32 = lambda v: torch.from_numpy(np.asarray(v, dtype=np.int32)).cuda()
     g = torch.Generator(device="cuda").manual_seed(A)
-    x, dyp, hpre = (torch.empty(s, device="cuda").random_(-2, 3, generator=g) for s in ((A, d), (A, d), (A, f)))
-    w1, w2 = (torch.empty(s, device="cuda").random_(-2, 3, generator=g) for s in ((E, d, f), (E, f, d)))
-    dxp, dw1, dw2 = torch.empty((A, d), device="cuda"), torch.full((E, d, f), 7.0, device="cuda"), torch.full((E, f, d), 7.0, device="cuda")
+    x, dyp, hpre = (torch.empty(s, **F32).random_(-2, 3, generator=g) for s in ((A, d), (A, d), (A, f)))
+    w1, w2 = (torch.empty(s, **F32).random_(-2, 3, generator=g) for s in ((E, d, f), (E, f, d)))
+    dxp, dw1, dw2 = torch.empty((A, d), **F32), torch.full((E, d, f), 7.0, **F32), torch.full((E, f, d), 7.0, **F32)
     ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, E, 1, V, B.F32), dtype=torch.uint8, device="cuda")
     B.flexmoe_expert_ffn_bwd(dyp, x, hpre, w1, w2, i32(voff), i32(owner), B.RELU, dxp, dw1, dw2, ws)
     of = torch.from_numpy(np.repeat(owner, rows)).cuda()
