@@ -257,7 +257,8 @@ MANY = {
     "balance_many": W.scaled(SMALL["wgrad_balance"], N=7300),
     "experts_many": W.scaled(SMALL["max_experts"], N=9000),
 }
-# nine column tiles, which no strip of the tile grid divides: of 128 columns (few rows) and of 256, in all products of a step
+# nine column tiles, which no strip of the tile grid divides: of 128 columns in all products of a step with few rows, of 256 in the
+# rows products of many
 BANDS = {
     "bands": W.scaled(W.CONFIGS["gpt_m"], N=900, d=264, f=1144, E=4, V=6, max_rep=3),
     "bands_many": W.scaled(W.CONFIGS["gpt_m"], N=2600, d=256, f=2304, E=4, V=6, max_rep=3),

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2304_03946_amd import workloads as W
+from test_dispatch import paths
 from test_gpu_parity import api, check_gate, run_stagewise, upload  # noqa: F401  (api: module fixture)
 
 pytestmark = pytest.mark.gpu
@@ -16,13 +17,74 @@ def stagewise(api, cfg, seed=3):  # noqa: F811
     run_stagewise(api, cfg, inp, *W.placement_from_loads(W.prior_loads(cfg, seed), cfg.V, cfg.max_rep, shuffle_seed=11))
 
 
-# one job per 1/8 and 1/4 of a patch: the work lists are dealt out over 64 and 32 bins (several lanes rows of the
-# minimum); two patches per job: 4 bins; 70 jobs: the second pass of 64; segments of
-# 16 K tiles: the first size that is cut and the last that is not, and 32 K tiles from a share of 8 on
+# 128 x 128 weight-gradient tiles (the work lists in load order): several jobs per patch, 70 jobs, and segments of 16 K tiles:
+# the first size that is cut and the last that is not, and 32 K tiles from a share of 8 on
 @pytest.mark.parametrize("N,d,f,E,V", [(2100, 256, 1024, 12, 17), (1300, 256, 2048, 6, 9), (4200, 512, 1024, 5, 8), (3000, 256, 512, 70, 80),
                                        (1024, 136, 264, 3, 5), (1023, 136, 264, 3, 5), (16500, 136, 264, 3, 5)])
 def test_weight_gradient_work_lists(api, N, d, f, E, V):  # noqa: F811
     stagewise(api, W.scaled(W.CONFIGS["gpt_m"], N=N, d=d, f=f, E=E, V=V, max_rep=3))
+
+
+def exact_step(api, A, d, f, E, V, seed=1):  # noqa: F811
+    """One expert FFN, forward and backward, of whole numbers, on skewed buckets (some experts and buckets empty): every sum is exact in
+    fp32, so every output is the exact sum rounded once, in whatever order and tiles it was computed."""
+    B, layer_mod = api
+    rng = np.random.default_rng(seed)
+    owner = np.concatenate([np.arange(E), rng.integers(E, size=V - E)])
+    rng.shuffle(owner)
+    share = rng.random(V) ** 3 * (rng.random(V) < 0.9)
+    share[rng.integers(V)] += 0.5
+    rows = rng.multinomial(A, share / share.sum())
+    i32 = lambda v: torch.from_numpy(np.asarray(v, dtype=np.int32)).cuda()
+    voff, own = i32(np.concatenate([[0], np.cumsum(rows)])), i32(owner)
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x, dyp, w1, w2 = (torch.empty(s, **bf).random_(-1, 2, generator=g) for s in ((A, d), (A, d), (E, d, f), (E, f, d)))
+    hpre, h, yp, dxp, dw1, dw2 = (torch.full(s, 7.0, **bf) for s in ((A, f), (A, f), (A, d), (A, d), (E, d, f), (E, f, d)))
+    ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, E, 1, V, B.BF16), dtype=torch.uint8, device="cuda")
+    B.flexmoe_expert_ffn_fwd(x, voff, own, w1, None, w2, None, B.RELU, hpre, yp, ws, h=h)
+    B.flexmoe_expert_ffn_bwd(dyp, x, hpre, w1, w2, voff, own, B.RELU, dxp, dw1, dw2, ws, h=h)
+    of = torch.from_numpy(np.repeat(owner, rows)).cuda()
+    same = lambda got, want: torch.equal(got, want.bfloat16())
+    for e in range(E):
+        t = (of == e).nonzero()[:, 0]
+        z = x[t].float() @ w1[e].float()
+        assert same(hpre[t], z) and same(h[t], z.clamp(min=0)), e
+        dz = ((dyp[t].float() @ w2[e].float().t()) * (z > 0)).bfloat16().float()
+        assert same(yp[t], h[t].float() @ w2[e].float()) and same(dxp[t], dz @ w1[e].float().t()), e
+        assert same(dw2[e], h[t].float().t() @ dyp[t].float()) and same(dw1[e], x[t].float().t() @ dz), e
+
+
+# 256 x 256 weight-gradient tiles, whole: the work lists dealt out over 64 bins down to 2, in one pass of the wave and (70 experts) in
+# several, cut into segments or not, and in load order where the tile grid is irregular; nine column tiles, in bands, whole and ragged;
+# ragged ones in strips, with 300 buckets
+@pytest.mark.parametrize("A,d,f,E,V,bins,seg", [
+    (210000, 256, 1024, 12, 17, 64, 102), (20600, 512, 1024, 5, 8, 32, 32), (21000, 512, 1024, 70, 80, 32, 32), (10400, 512, 2048, 6, 9, 16, 32),
+    (5300, 1024, 2048, 5, 7, 8, 32), (2700, 1024, 4096, 3, 5, 4, 0), (4200, 1024, 4096, 3, 5, 4, 32), (1500, 2048, 4096, 2, 3, 2, 0),
+    (11000, 768, 1280, 6, 9, 1, 32), (18400, 256, 2304, 4, 6, 1, 32), (9300, 392, 2200, 4, 6, 1, 32), (21000, 392, 1000, 6, 300, 1, 32)])
+def test_large_weight_gradient_tiles(api, A, d, f, E, V, bins, seg):  # noqa: F811
+    p = paths(A, d, f, E, V)
+    assert not p["small_gradients"] and p["bins2"] == p["bins1"] == bins and p["seg_tiles"] == seg
+    exact_step(api, A, d, f, E, V)
+
+
+# rows products past the few-rows kernels' line, with nine column tiles of 256: register-staged (d no multiple of 128) and persistent ones
+@pytest.mark.parametrize("A,d,f,E,V", [(9000, 264, 2304, 4, 6), (9000, 256, 2304, 4, 6)])
+def test_bands_of_column_tiles_in_the_rows_products(api, A, d, f, E, V):  # noqa: F811
+    assert paths(A, d, f, E, V)["few_rows"] == 0
+    exact_step(api, A, d, f, E, V)
+
+
+# dXp and both weight gradients in one launch up to 512 row tiles x column tiles of dXp and 6144 tiles of weight gradients: the last
+# sizes and the first past them, with 32-row and 64-row tiles, ragged ones among them
+@pytest.mark.parametrize("A,d,f,E,V,rows,merged", [
+    (3647, 1024, 2048, 8, 10, 64, True), (3648, 1024, 2048, 8, 10, 64, False), (300, 512, 1024, 96, 110, 32, True),
+    (300, 512, 1024, 97, 110, 32, False), (3000, 264, 776, 30, 40, 64, True), (11605, 192, 768, 12, 15, 64, True), (11606, 192, 768, 12, 15, 0, False)])
+def test_lines_of_the_merged_backward_launch(api, A, d, f, E, V, rows, merged):  # noqa: F811
+    p = paths(A, d, f, E, V)
+    assert p["small_gradients"] and p["few_rows"] == rows and p["merged"] == merged
+    for _ in range(3):      # the segment counters are left as they were found
+        exact_step(api, A, d, f, E, V)
 
 
 # rows kernels for few rows per expert or little output: 32-row tiles (at most 4 rows per expert on average; N = 1: two
@@ -94,12 +156,16 @@ def test_fp32_gate(api, N, d, E, k):  # noqa: F811
     check_gate(idx.cpu().numpy(), w.cpu().numpy(), x, wg, k, W.DT_F32)
 
 
-# bf16 gate: the last size of the split-K kernel and the first of the streaming one, fewer chunks of features than waves,
-# a partial last chunk, padded expert tiles, W_g as stored and transposed.  (check_gate wants at most 5 % of the tokens within
+# bf16 gate.  Both sides of the lines between one chunk in flight per wave and several (256 features, 8192 tokens), between the quarters
+# and the streaming kernel and its two widths (32768 and 65536 tokens, up to 64 experts); fewer chunks of features than waves, a partial
+# last chunk, padded expert tiles; experts in whole groups of four (W_g transposed by the LDS reads) and not, in every kernel.
+# (check_gate wants at most 5 % of the tokens within
 # its error bound of a tie; the bound grows as d^1.5, 5e-4 at d = 520, against gaps of about 0.2 between k + 1 neighbouring
 # logits: about 1 % per pick at d = 520 but 3 % at d = 1032, so the larger d come with k = 1.)
 @pytest.mark.parametrize("N,d,E,k", [(8192, 520, 64, 2), (8193, 520, 64, 2), (16384, 72, 20, 1), (16385, 72, 20, 1), (24577, 248, 20, 1), (24577, 256, 20, 1), (33, 512, 33, 2),
-                                     (400, 1032, 100, 1), (400, 520, 128, 2), (1, 8, 48, 8), (165, 504, 64, 3), (500, 776, 256, 1)])
+                                     (400, 1032, 100, 1), (400, 520, 128, 2), (1, 8, 48, 8), (165, 504, 64, 3), (500, 776, 256, 1),
+                                     (32767, 136, 64, 1), (32768, 136, 64, 1), (65535, 72, 64, 1), (65536, 72, 64, 1), (32768, 72, 30, 1), (65536, 72, 37, 1), (32768, 136, 4, 1),
+                                     (8193, 520, 128, 1), (300, 136, 100, 1), (300, 520, 101, 1), (8193, 136, 101, 1), (300, 264, 30, 2), (500, 264, 6, 2), (300, 264, 250, 1)])
 def test_bf16_gate(api, N, d, E, k):  # noqa: F811
     binding, layer_mod = api
     rng = np.random.default_rng(N + E)
