@@ -85,10 +85,8 @@ static int wgrad_seg_tiles(int A, int d, int f) {
   const long long seg = std::max(share, least);
   return 4 * seg <= k_tiles ? (int)seg : 0;
 }
-// Upper bounds over all load distributions: extra segments (beyond one per expert), and partial
-// tile sets (segments of experts that have more than one).
+// Upper bound over all load distributions: extra segments (beyond one per expert).
 static int wgrad_extra_segments(int A, int V, int seg_tiles) { return seg_tiles ? (A / DK + V) / seg_tiles : 0; }
-static int wgrad_partial_slots(int A, int V, int seg_tiles) { return seg_tiles ? 2 * ((A / DK + V) / seg_tiles) + 1 : 0; }
 
 // Whether a call's weight gradients go to the 128 x 128 tiles of wgrad_gemm_small_bf16, three workgroups per compute unit, instead of
 // the 256 x 256 ones (half the operand traffic per product, but one workgroup per compute unit, whose look-ups, first loads and
@@ -203,9 +201,10 @@ static int small_rows(int A, int d, int f, int E, int V) {
 // Whether dXp and the weight gradients share a launch: both take the small tiles, dXp's tiles fit the two workgroups per compute unit
 // that the launch has, and the weight gradients are few enough that a third workgroup per compute unit, which the launch's
 // larger LDS rules out, counts less than the tail of dXp and the launch saved.  Whole backward passes, us, launches of their own and one:
-// d 128, f 512, E 16, 1536 rows 47, 34; d 256, f 1024, E 8, 2048 rows 62, 50, 8000 rows 85, 79; d 192, f 768, E 12, 12000 rows (400 tiles) 105, 104;
-// d 512, f 2048, E 32, 1024 rows 89, 82; d 768, f 3072, E 16, 1536 rows 114, 106, 4096 rows (480 tiles) 224, 221; d 1024, f 2048, E 8, 2048 rows 100, 96.
-// Past the lines: d 1024, f 2048, E 8, 5120 rows (704 tiles) 191, 193; d 768, f 3072, E 16, 10240 rows (1056) 401, 405; d 512, f 1024, E 128 (8192
+// d 128, f 512, E 16, 1536 rows 47, 34; d 256, f 1024, E 8, 2048 rows 62, 50, 8000 rows 85, 79; d 256, f 256, E 4, 11000 rows (352 tiles) 50, 48; d 128, f 256, E 3,
+// 25400 rows (400) 67, 65; d 448, f 1216, E 18, 6000 rows (448) 84, 78; d 512, f 2048, E 32, 1024 rows 89, 82; d 768, f 3072, E 16, 1536 rows 114, 106, 4096
+// rows (480) 224, 221; d 1024, f 2048, E 8, 2048 rows 100, 96; the ratio over 120 layers inside the lines 0.75 - 0.98.
+// Past the lines: d 1024, f 2048, E 8, 5120 rows (704 tiles) 191, 193; d 512, f 1024, E 128 (8192
 // tiles of weight gradients), 4096 rows 219, 224; d 1024, f 4096, E 32 (16384), 1024 rows 284, 294; d 2048, f 8192, E 64, 2048 rows 1835, 1951.
 static bool bwd_products_merged(const FfnArgs& a) {
   if (!small_rows(a.A, a.d, a.f, a.E, a.V) || !wgrad_small(a.A, a.d, a.f, a.E)) return false;

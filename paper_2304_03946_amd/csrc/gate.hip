@@ -122,7 +122,8 @@ __device__ __forceinline__ void gate_select_store(f32x16 (&acc)[NT], int t, int 
 // STORED: `wgt` is W_g itself, [d, E], E a multiple of four: its K tile is one contiguous piece of memory, transposed on the way out of
 // LDS as in gate_quarters_kernel (no launch that writes a transposed copy: 5 us).
 // S: as many stages as leave room for a second workgroup on a compute unit (65536 x 2048, 64 experts: six stages, one workgroup 49.1,
-// three, two workgroups and no transposing launch 42.6 us; 32768 x 2048 38.7, 26.2).
+// three, two workgroups and no transposing launch 42.6 us; 32768 x 2048 38.7, 26.2; from the transposed copy, up to 32 experts the same
+// as before: 40000 x 1024, 30 24.7, 24.7, 50000 x 512, 30 16.0, 16.3; more 40000 x 1024, 61 33.7, 27.2).
 // ---------------------------------------------------------------------------------------------
 __device__ const uint4 kGateZeroRow[8] = {};
 typedef __attribute__((address_space(3))) unsigned char gate_lds_t;
@@ -164,6 +165,8 @@ __device__ __forceinline__ bf16x8 gate_w_tr(const gate_lds_t* tile, int k0, int 
 // copy that a launch of its own made), and now; tokens x features, experts:
 //   16 x 1024, 32 6.3, 5.1; 1500 x 1024, 32 7.3, 5.4; 256 x 2048, 64 15.6, 10.0; 8192 x 768, 16 6.5, 5.2; 16384 x 1024, 32 10.9, 6.8;
 //   4096 x 512, 128 14.9, 11.1; 60000 x 2048, 100 183, 85; 4000 x 1024, 256 32.6, 23.1
+// and with experts in no whole groups of four (2-byte reads) 16 x 1024, 61 8.3, 8.4; 300 x 64, 61 5.0, 5.2; 1500 x 1024, 30 7.2, 6.0; 3000 x 4096, 61 27.0,
+//   21.3; 8192 x 768, 13 6.5, 5.7; 16384 x 1024, 6 11.0, 7.2; 40000 x 1024, 101 72, 40; 1500 x 1024, 250 28.2, 22.1
 // and where the streaming kernel below served fewer than 32768 tokens: 12000 x 2048, 64 23.1, 14.5; 32000 x 512, 64 18.8, 12.3; 30000 x
 // 2048, 32 25.1, 22.1.
 template <int NT, int S, bool TR>
