@@ -793,9 +793,9 @@ def test_route_adversarial(api, case):
         assert np.array_equal(got[name][:arr.shape[0]], arr), (case, name)
 
 
-# one round of 64 assignments per wave and four, the line to two launches, units of four rounds, of eight, and longer ones that are no
+# one to four rounds of 64 assignments per wave, the line to two launches, units of four rounds, of eight, and longer ones that are no
 # whole number of batches; experts with fewer assignments than replicas next to hot ones
-@pytest.mark.parametrize("N,E,V,k", [(512, 9, 20, 2), (513, 9, 20, 2), (4096, 64, 128, 1), (4097, 65, 129, 1), (32769, 5, 300, 2), (300001, 40, 48, 2)])
+@pytest.mark.parametrize("N,E,V,k", [(512, 9, 20, 2), (513, 9, 20, 2), (1024, 9, 20, 2), (1025, 9, 20, 2), (1536, 9, 20, 2), (4096, 64, 128, 1), (4097, 65, 129, 1), (32769, 5, 300, 2), (300001, 40, 48, 2)])
 def test_route_rounds(api, N, E, V, k):
     rng = np.random.default_rng(N)
     first = np.minimum(rng.geometric(0.3, N) - 1, E - 1)
