@@ -66,8 +66,8 @@ static_assert(FLEXMOE_MAX_VEXPERTS < 1 << 15, "two such numbers share a word");
 // division per assignment, by a product with the divisor's reciprocal: the high word of x floor((2^32 - 1) / d) is
 // floor(x / d) or one less.
 // (Whole router, one round after another with two divisions each and the histograms summed a few loads at a time, and now, us: 16384
-// assignments of 128 experts 17.1, 12.2; 32768 of 32 13.0, 10.2; 131072 of 64 27.7, 18.6; 72000 of 256 46.2, 26.4; in one workgroup 4000
-// of 64 10.0, 9.0.)
+// assignments of 128 experts 16.8, 11.4; 32768 of 32 12.8, 9.6; 131072 of 64 27.2, 16.3; 72000 of 256 45.7, 24.3; 5000 of 2 10.3, 10.1; in one
+// workgroup 4096 of 64 8.7, 8.0.)
 template <int R>
 __device__ __forceinline__ void place_rounds(int base, const int (&ev)[R], int lane, int32_t* wbase_w, const i32x4* share,
                                              const uint16_t* rids, const int32_t* vdelta, int32_t* __restrict__ dest,
@@ -186,7 +186,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_assign_kernel(
       for (int ub = part; ub < units; ub += parts * kBatch) {
         int c[kBatch];
 #pragma unroll
-        for (int b = 0; b < kBatch; ++b) c[b] = hist[(size_t)min(ub + b * parts, units - 1) * E + e];
+        for (int b = 0; b < kBatch; ++b)
+          if (ub - part + b * parts < units) c[b] = hist[(size_t)min(ub + b * parts, units - 1) * E + e];      // (uniform: no loads past the units)
 #pragma unroll
         for (int b = 0; b < kBatch; ++b) {
           const int u = ub + b * parts;
