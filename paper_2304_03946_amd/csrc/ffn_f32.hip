@@ -331,17 +331,17 @@ __global__ __launch_bounds__(kF32Threads, 2) void rows_gemm_f32(const float* __r
 }
 
 // dW_e[m, n] = sum over the vExperts v of e (ascending v), rows p of v: L[p, m] * R[p, n].  The rows of all of the
-// expert's buckets are one contraction: K tile kt holds rows 32 kt .. of the buckets laid behind each other.
+// expert's buckets are one contraction: K tile kt holds rows 32 kt .. of the buckets laid behind each other.  Output rows from m_first on.
 template <int MT>
 __global__ __launch_bounds__(kF32Threads, 2) void wgrad_f32(const float* __restrict__ L, const float* __restrict__ R,
                                                             const int32_t* __restrict__ voff,
                                                             const int32_t* __restrict__ owner, int V, int M, int NC,
-                                                            float* __restrict__ dw) {
+                                                            int m_first, float* __restrict__ dw) {
   typedef F32Loop<MT, false, false> Loop;
   __shared__ __align__(1024) unsigned char smem[Loop::kLds];
   __shared__ int s_first[FLEXMOE_MAX_VEXPERTS], s_end[FLEXMOE_MAX_VEXPERTS];      // first row - rows before it, rows up to its end
   __shared__ int s_n;
-  const int e = blockIdx.z, m0 = blockIdx.y * (MT * 32), n0 = blockIdx.x * FN;
+  const int e = blockIdx.z, m0 = m_first + (int)blockIdx.y * (MT * 32), n0 = blockIdx.x * FN;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (wave == 0) {                  // the expert's non-empty buckets, ascending
     int n = 0, total = 0;
@@ -503,11 +503,15 @@ static void launch_rows_f32(const FfnArgs& a, const void* in, const void* w, con
 
 static void launch_wgrad_f32(const FfnArgs& a, const void* L, const void* R, int M, int NC, void* dw, hipStream_t s) {
   const int mt = f32_wgrad_blocks(a, M, NC);
-  const dim3 grid(tiles_of(NC, FN), tiles_of(M, mt * 32), a.E);
-  if (mt == 2)
-    hipLaunchKernelGGL(wgrad_f32<2>, grid, dim3(kF32Threads), 0, s, (const float*)L, (const float*)R, a.voff, a.owner, a.V, M, NC, (float*)dw);
-  else
-    hipLaunchKernelGGL(wgrad_f32<1>, grid, dim3(kF32Threads), 0, s, (const float*)L, (const float*)R, a.voff, a.owner, a.V, M, NC, (float*)dw);
+  // a grid's second dimension ends at 65535 workgroups: layers of millions of columns take several launches
+  const int m_tiles = (int)tiles_of(M, mt * 32), most = 65535;
+  for (int m0 = 0; m0 < m_tiles; m0 += most) {
+    const dim3 grid(tiles_of(NC, FN), (unsigned)std::min(most, m_tiles - m0), a.E);
+    if (mt == 2)
+      hipLaunchKernelGGL(wgrad_f32<2>, grid, dim3(kF32Threads), 0, s, (const float*)L, (const float*)R, a.voff, a.owner, a.V, M, NC, m0 * 64, (float*)dw);
+    else
+      hipLaunchKernelGGL(wgrad_f32<1>, grid, dim3(kF32Threads), 0, s, (const float*)L, (const float*)R, a.voff, a.owner, a.V, M, NC, m0 * 32, (float*)dw);
+  }
 }
 
 hipError_t launch_ffn_fwd_f32(const FfnArgs& a, const void* xp, const void* w1, const void* b1, const void* w2,

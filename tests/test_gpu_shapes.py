@@ -383,6 +383,22 @@ def test_fp32_products_of_more_tiles_than_a_launch_takes(api):  # noqa: F811
         assert torch.equal(dw2[e].double(), z.clamp(min=0).t() @ dyp[rows].double())
 
 
+def test_fp32_weight_gradients_of_very_many_tiles(api):  # noqa: F811
+    """65538 tiles of 64 columns, in the columns of dW1 and the rows of dW2.  Whole numbers: exact sums."""
+    B, layer_mod = api
+    A, d, f = 3, 8, 65538 * 64
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x, dyp, hpre = (torch.empty(s, **F32).random_(-2, 3, generator=g) for s in ((A, d), (A, d), (A, f)))
+    w1, w2 = torch.empty((1, d, f), **F32).random_(-2, 3, generator=g), torch.empty((1, f, d), **F32).random_(-1, 2, generator=g)
+    dxp, dw1, dw2 = torch.empty((A, d), **F32), torch.full((1, d, f), 7.0, **F32), torch.full((1, f, d), 7.0, **F32)
+    ws = torch.empty(B.flexmoe_workspace_bytes(A, d, f, 1, 1, 1, B.F32), dtype=torch.uint8, device="cuda")
+    B.flexmoe_expert_ffn_bwd(dyp, x, hpre, w1, w2, i32([0, A]), i32([0]), B.RELU, dxp, dw1, dw2, ws)
+    dz = (dyp.double() @ w2[0].double().t()) * (hpre > 0)
+    assert torch.equal(dw2[0].double(), hpre.double().clamp(min=0).t() @ dyp.double()) and torch.equal(dw1[0].double(), x.double().t() @ dz)
+    assert torch.equal(dxp.double(), dz @ w1[0].double().t())
+
+
 # a row among 300 (32 x 64 tiles) and among 25000 (64 x 64 tiles in all four products); whole K tiles, an odd number of them, a ragged one
 @pytest.mark.parametrize("d,f", [(256, 1024), (264, 1048), (224, 1000)])
 def test_fp32_rows_do_not_depend_on_the_batch(api, d, f):  # noqa: F811
