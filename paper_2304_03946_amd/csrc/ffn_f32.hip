@@ -12,8 +12,8 @@
 // [512, 2048], 83 TFLOP/s of 157), else what a workgroup does before its first K tile, the K tiles' latency, and workgroups that do not
 // come out even over the compute units.  With 64 x 64 tiles alone, loads behind a branch each and two trips to memory before the first
 // one: fp32 training step of 1000 tokens (d 256, f 1024, 8 experts) 30, 29, 31, 27 us for its rows products and 28, 28 for its weight
-// gradients, now 25, 25, 26, 24 and 22, 22; 4096 tokens (d 512, f 2048) 221, 228, 233, 229, 203, 201 -> 207, 198, 219, 195, 187, 185; 100
-// tokens of that layer 26, 52, 27, 49, 20, 20 -> 16, 27, 17, 26, 23, 22; weight gradients of a hot expert (d 128, f 512, 8192 rows) 84 -> 46.
+// gradients, now 26, 25, 25, 24 and 22, 21; 8192 rows of 8 experts (d 512, f 2048) 215, 216, 226, 219, 204, 203 -> 206, 203, 216, 197, 197, 195; 200
+// rows of that layer 24, 50, 25, 48, 18, 17 -> 16, 26, 15, 25, 18, 18; weight gradients of one expert with 8192 rows (d 128, f 512) 216 -> 111.
 #include <algorithm>
 #include <type_traits>
 
