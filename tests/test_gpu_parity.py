@@ -237,8 +237,8 @@ SMALL = {
     # three and six column tiles: patches of the tile grid that start and end inside a row of their column strip
     # (32 is no multiple of the strip's width), in all four rows products and both weight gradients
     "strip_patches": W.scaled(W.CONFIGS["bert"], N=2600, d=768, f=1536, E=6, V=9, max_rep=2, backward=True),
-    # whole 256 x 256 weight-gradient tiles with two patches per job (d = 512, f = 1024) and skewed loads: the
-    # work lists are dealt out over the XCD groups by load, with holes the persistent kernel skips
+    # skewed loads on whole tiles; with the rows of grads_balance_many (below) the 256 x 256 weight-gradient tiles, two patches
+    # per job: the work lists are dealt out over the XCD groups by load, with holes the persistent kernel skips
     "wgrad_balance": W.scaled(W.CONFIGS["gpt_m"], N=2500, d=512, f=1024, E=8, V=13, max_rep=4),
     # the library's limits: 256 experts, 512 vExperts, 8 experts per token -- hundreds of buckets of a few dozen rows
     # (every one a ragged tile, many experts with a handful of tokens, the bucket lookups at their widest)
@@ -246,7 +246,8 @@ SMALL = {
 }
 # The layers above have few rows for their experts or little output, so their rows products take the kernels for that (all but
 # split_tail); the same kinds of layers with enough rows for the 256 x 256 kernels: register-staged (contractions that
-# are no multiple of 128), persistent, both in one layer, top-1, ragged strips, balanced work lists, the library's limits
+# are no multiple of 128), persistent, both in one layer, top-1, ragged strips, the library's limits (their weight gradients take the 128 x 128
+# tiles, but for strip_many's)
 MANY = {
     "bert_many": W.scaled(SMALL["bert_small"], N=8100),
     "gpt_many": W.scaled(SMALL["gpt_small"], N=10400),
